@@ -66,6 +66,49 @@ DeviceGuard::~DeviceGuard() {
   if (prev >= 0) (void)hipSetDevice(prev);
 }
 
+// The direct kernel's own vectors (byte offsets, skip counts in the low two
+// bits): contracted offsets of X and Y in its order, then for each operand
+// the rows and contracted offsets of its pre-packed form -- block (tile, kb)
+// of BR x bk elements, [row][k] -- so that the same kernel reads either and
+// sums in the same order.  v: the plan's indexing vectors in elements.
+static void direct_vectors(famlies_plan_s* p, const std::vector<int64_t>* v, std::vector<uint32_t>* out) {
+  const Analysis& an = p->an;
+  const int u = 16 / an.esize;
+  const int64_t es = an.esize, ks = 4 * u;
+  KRuns kr;
+  const bool padded = padded_k_length(an, u) > 0;
+  if (padded) padded_k_runs(an, u, &kr);
+  const int64_t n = padded ? (int64_t)kr.index.size() : an.K;
+  const int64_t np = ceil_div(n, ks) * ks;  // == p->direct_k rounded up to whole steps
+  const int bk = p->cfg.bk;
+  const int64_t nkb = ceil_div(an.K, bk);
+  std::vector<int64_t> elem[2];
+  for (int op = 0; op < 2; ++op) {
+    const std::vector<int64_t>& k = v[1 + op];
+    elem[op].resize((size_t)n);
+    for (int64_t i = 0; i < n; ++i) elem[op][(size_t)i] = k[(size_t)(padded ? kr.index[(size_t)i] : i)];
+    (op ? p->dy_vec : p->dx_vec) = contiguous_k_runs(elem[op], n, u);
+    out[op].assign((size_t)np, 0);
+    const int br = op ? p->cfg.bn : p->cfg.bm;
+    std::vector<uint32_t>& pr = out[2 + 2 * op];
+    std::vector<uint32_t>& pk = out[3 + 2 * op];
+    const int64_t rows = (int64_t)v[3 * op].size();
+    pr.resize((size_t)rows);
+    for (int64_t r = 0; r < rows; ++r) pr[(size_t)r] = (uint32_t)((r / br * nkb * br * bk + r % br * bk) * es);
+    pk.assign((size_t)np, 0);
+    std::vector<int64_t> packed((size_t)n);
+    for (int64_t i = 0; i < n; ++i) {
+      const uint32_t skip = padded ? kr.skip[(size_t)i] : 0;
+      const int64_t k1 = padded ? kr.index[(size_t)i] : i;
+      out[op][(size_t)i] = (uint32_t)(uint64_t)(elem[op][(size_t)i] * es) | skip;
+      packed[(size_t)i] = k1 / bk * br * bk + k1 % bk;
+      pk[(size_t)i] = (uint32_t)(packed[(size_t)i] * es) | skip;
+    }
+    p->pk_vec[op] = contiguous_k_runs(packed, n, u);
+    p->pk_fits[op] = rows * nkb * bk * es < ((int64_t)1 << 32);
+  }
+}
+
 template <typename OffT>
 static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int64_t kp, std::vector<char>* image) {
   const Analysis& an = p->an;
@@ -87,6 +130,9 @@ static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int
   const int64_t shift[6] = {an.x_lo, 0, 0, an.y_lo, an.c_lo_mn, 0};
   size_t n6 = 0;
   for (int i = 0; i < 6; ++i) n6 += v[i].size();
+  std::vector<uint32_t> extra[6];
+  if (p->direct.bm) direct_vectors(p, v, extra);
+  for (const auto& x : extra) n6 += x.size();
   const size_t b6 = (n6 * sizeof(OffT) + 7) & ~(size_t)7;
   const size_t total = b6 + 3 * (size_t)an.L * sizeof(int64_t);
   std::vector<char>& host = *image;
@@ -103,6 +149,10 @@ static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int
       else
         o[pos++] = (OffT)x;
     }
+  }
+  for (int i = 0; i < 6; ++i) {
+    (i < 2 ? p->dk_pos[i] : p->pk_pos[i - 2]) = pos;
+    for (uint32_t x : extra[i]) o[pos++] = (OffT)x;
   }
   int64_t* lb = reinterpret_cast<int64_t*>(host.data() + b6);
   for (int i = 0; i < 3; ++i) {
@@ -164,7 +214,7 @@ static PlainArgs<OffT> make_args(const famlies_plan_s* p, const void* x, const v
 // *image is left empty when C has no elements.
 static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int dtype, int compute,
                                    const famlies_tensor* A, const famlies_tensor* B, const famlies_tensor* C,
-                                   const TileCfg* force, std::vector<char>* image) {
+                                   const TileCfg* force, std::vector<char>* image, bool allow_direct = true) {
   Analysis an;
   std::string err;
   int st = analyze(dtype, compute, A, B, C, &an, &err);
@@ -216,6 +266,18 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   finalize_split(&p->cfg, an.K, ntiles, &p->kchunk, &p->head);
   if (ntiles * p->cfg.split * an.L >= ((int64_t)1 << 31))
     return fail(FAMLIES_ERR_UNSUPPORTED, "the tile grid exceeds 2^31 workgroups");
+  if (allow_direct && !force && !p->table_hit && !i8 && !ns && p->index_bits == 32 && !p->elem32) {
+    p->direct = choose_direct(h, an, p->cfg);
+    if (p->direct.bm) {
+      const int u = 16 / an.esize, ks = 4 * u;
+      DirectCfg& d = p->direct;
+      const int64_t kr = padded_k_length(an, u);
+      p->direct_k = kr ? kr : an.K;
+      if (an.L > 1) d.split = 1;
+      d.kchunk = (int)(ceil_div(ceil_div(p->direct_k, d.split), ks) * ks);
+      d.split = (int)ceil_div(p->direct_k, d.kchunk);
+    }
+  }
   image->clear();
   p->work_bytes = 0;
   if (an.M == 0 || an.N == 0) return FAMLIES_OK;
@@ -235,6 +297,10 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
                        : (size_t)p->cfg.split * (size_t)(ntiles - p->head) * (size_t)p->cfg.bm *
                              (size_t)p->cfg.bn * (size_t)an.esize;
   }
+  if (p->direct.bm && p->direct.split > 1)
+    p->work_bytes = std::max(p->work_bytes, (size_t)p->direct.split * (size_t)ceil_div(an.M, p->direct.bm) *
+                                                (size_t)ceil_div(an.N, p->direct.bn) *
+                                                (size_t)(p->direct.bm * p->direct.bn) * (size_t)an.esize);
   return FAMLIES_OK;
 }
 
@@ -274,7 +340,7 @@ famlies_status make_plan(famlies_handle h, famlies_plan* out, int dtype, int com
 }
 
 void log_plan(const famlies_plan_s* p) {
-  log_decision("plan", p->an, p->cfg, p->elem32 ? -32 : p->index_bits, p->x_vec, p->y_vec, p->work_bytes,
+  log_decision("plan", p->an, p->cfg, p->direct, p->elem32 ? -32 : p->index_bits, p->x_vec, p->y_vec, p->work_bytes,
                p->table_hit);
 }
 
@@ -478,7 +544,26 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
       a.y = y;
       a.y_nkb = (int32_t)((an.K + L.bk - 1) / L.bk);
     }
-    e = launch_plain(an.dtype, a, L, s);
+    if (p->direct.bm && L.kind == PlainLaunch::kMain && (!xp || p->pk_fits[0]) && (!yp || p->pk_fits[1])) {
+      const DirectCfg& d = p->direct;
+      const uint32_t* o = static_cast<const uint32_t*>(p->d_off);
+      a.xk = o + (xp ? p->pk_pos[1] : p->dk_pos[0]);
+      a.yk = o + (yp ? p->pk_pos[3] : p->dk_pos[1]);
+      if (xp) a.xmn = o + p->pk_pos[0];
+      if (yp) a.ymn = o + p->pk_pos[2];
+      const int64_t xplane = xp ? (int64_t)a.tiles_m * a.x_nkb * L.bm * L.bk : 0;
+      const int64_t yplane = yp ? (int64_t)a.tiles_n * a.y_nkb * L.bn * L.bk : 0;
+      a.K = (int32_t)p->direct_k;
+      a.tiles_m = (int32_t)ceil_div(an.M, d.bm);
+      a.tiles_n = (int32_t)ceil_div(an.N, d.bn);
+      a.splits = d.split;
+      a.kchunk = d.kchunk;
+      a.head = 0;
+      e = launch_direct(an.dtype, a, d, xp ? p->pk_vec[0] : p->dx_vec, yp ? p->pk_vec[1] : p->dy_vec, xplane, yplane, s);
+      if (e == hipSuccess && d.split > 1) e = launch_splitk_reduce(an.dtype, a, d.bm, d.bn, s);
+    } else {
+      e = launch_plain(an.dtype, a, L, s);
+    }
   } else {
     e = launch_plain(an.dtype, make_args<int64_t>(p, x, y, C, alpha, beta), L, s);
   }
@@ -519,7 +604,15 @@ static famlies_status contract_noalloc_impl(famlies_handle htok, int dtype, int 
   std::vector<char> image;
   famlies_status st = prepare_plan(h, &p, dtype, compute, A, B, C, nullptr, &image);
   if (st != FAMLIES_OK) return st;
-  const size_t off_bytes = (image.size() + 255) & ~(size_t)255;
+  size_t off_bytes = (image.size() + 255) & ~(size_t)255;
+  if (p.direct.bm && off_bytes + p.work_bytes > kNoAllocScratchBytes) {
+    // the direct kernel's extra vectors do not fit: plan without it
+    p = famlies_plan_s();
+    p.owns_device = false;
+    st = prepare_plan(h, &p, dtype, compute, A, B, C, nullptr, &image, false);
+    if (st != FAMLIES_OK) return st;
+    off_bytes = (image.size() + 255) & ~(size_t)255;
+  }
   if (off_bytes + p.work_bytes > kNoAllocScratchBytes)
     return fail(FAMLIES_ERR_UNSUPPORTED,
                 "famlies_contract_noalloc: the call needs " + std::to_string(off_bytes + p.work_bytes) +

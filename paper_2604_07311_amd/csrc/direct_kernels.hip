@@ -1,0 +1,287 @@
+// Small and narrow FP64 / FP32 contractions: operands straight from global
+// memory into MFMA registers.
+//
+// A wave owns a (16 MB) x (16 NB) tile of C (kernel view) over a share of K
+// and loads each operand element into the lane that multiplies it, through
+// the same block-scatter indexing vectors as the tiled kernels; there is no
+// LDS staging and no barrier in the K loop.  The waves of a workgroup either
+// share one tile, each taking every wk-th K step (their partial tiles are
+// summed through LDS in wave order, so results do not depend on timing), or
+// (wk = 1) own a tile each.
+//
+// What bounds it: with few tiles, the latency of a wave's K steps (so K is
+// spread over the four waves and three steps are in flight); with many, L2,
+// since every operand element is read once per tile of the other side
+// (9 TB/s measured).  The LDS-tiled kernel at these sizes pays a barrier and
+// a memory round trip per K slice, a second launch to sum its K ranges, and
+// 64 x 64 tiles of which a narrow problem fills a quarter or less.  Measured
+// per call on MI355X, tiled -> direct: FP64 256^3 11.0 -> 5.8 us, FP64 64 x
+// 676 x 676 13.1 -> 7.3, FP32 240^3 10.9 -> 5.2, FP32 144 x 2500 x 2500 with
+// runs of 50 50 -> 37, 400 dot products of 5184 167 -> 20, FP64 16 x 675840 x
+// 64 142 -> 108 (4.0 TB/s of what it must move).  Sixteen waves per tile were
+// slower than four on all but the dot products; 64 x 64 wave tiles (one wave
+// per SIMD) lose to the tiled kernel wherever they beat 32 x 32.
+#include "launch.hpp"
+#include "device.hpp"
+
+namespace famlies {
+
+template <typename T>
+struct Mfma16;
+template <>
+struct Mfma16<double> {  // v_mfma_f64_16x16x4_f64
+  using Acc = f64x4;
+  __device__ __forceinline__ static Acc mma(double a, double b, Acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  __device__ __forceinline__ static int row(int l, int r) { return (l / 16) + 4 * r; }
+};
+template <>
+struct Mfma16<float> {  // v_mfma_f32_16x16x4_f32
+  using Acc = f32x4;
+  __device__ __forceinline__ static Acc mma(float a, float b, Acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  __device__ __forceinline__ static int row(int l, int r) { return 4 * (l / 16) + r; }
+};
+
+// One operand of a wave: NBK blocks of 16 rows; lane l holds row l % 16 of
+// each block and, per K step of 4 U indices, the U consecutive ones of group
+// l / 16 (U elements are 16 bytes).  VEC: those U elements are consecutive
+// in memory and are read with one load (at element alignment); otherwise one
+// load per element.  D steps in flight, one register slot each.
+template <typename T, int NBK, bool VEC, int D>
+struct DirectOperand {
+  static constexpr int U = 16 / (int)sizeof(T);
+  static constexpr int NK = VEC ? 1 : U;  // contracted offsets per step
+  typedef T vec_t __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
+  typedef uint32_t off_t __attribute__((ext_vector_type(NK)));
+  uint32_t mn[NBK];
+  off_t ko[D];  // byte offsets, each with its entry's skip count in the low two bits
+  T v[D][NBK][U];
+
+  __device__ __forceinline__ void init(const uint32_t* __restrict__ rows, int row0) {
+#pragma unroll
+    for (int i = 0; i < NBK; ++i) mn[i] = rows[row0 + 16 * i];
+  }
+  // contracted offsets of this lane's run at k (a multiple of U)
+  template <int S>
+  __device__ __forceinline__ void fetch(const uint32_t* __restrict__ ks, int k) {
+    ko[S] = *reinterpret_cast<const off_t*>(ks + k);
+  }
+  template <int S>
+  __device__ __forceinline__ void load(const T* __restrict__ base) {
+#pragma unroll
+    for (int i = 0; i < NBK; ++i) {
+      if constexpr (VEC) {
+        const vec_t w = *reinterpret_cast<const __attribute__((address_space(1))) vec_t*>(global(at(base, mn[i] + (ko[S][0] & ~3u))));
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[S][i][u] = w[u];
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[S][i][u] = *global(at(base, mn[i] + (ko[S][u] & ~3u)));
+      }
+    }
+  }
+};
+
+template <typename T, int MB, int NB, bool XV, bool YV, int NW>
+__global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a, int wk, int64_t xplane,
+                                                           int64_t yplane) {
+  using MF = Mfma16<T>;
+  constexpr int U = 16 / (int)sizeof(T), KS = 4 * U, BM = 16 * MB, BN = 16 * NB;
+  constexpr int D = 3;
+  __shared__ T part[NW * BM * BN];
+  const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int g = lane / 16, r = lane % 16;
+  const int ntiles = a.tiles_m * a.tiles_n;
+  // units: (batch index, K range, tile), tile fastest, M fastest within
+  const int64_t units = (int64_t)ntiles * a.splits * a.L;
+  const int64_t wg = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t unit = wk == 1 ? wg * NW + wave : wg;
+  if (unit >= units) return;  // wk == 1 only: whole waves, and no barrier follows
+  const int wki = wk == 1 ? 0 : wave;
+  const int t = (int)(unit % ntiles);
+  const int ls = (int)(unit / ntiles);
+  const int l = ls / a.splits, split = ls % a.splits;
+  const int m0 = (t % a.tiles_m) * BM, n0 = (t / a.tiles_m) * BN;
+  const T* X = static_cast<const T*>(a.x) + (xplane ? l * xplane : a.xl[l]);
+  const T* Y = static_cast<const T*>(a.y) + (yplane ? l * yplane : a.yl[l]);
+  const int kbeg = split * a.kchunk, kend = min(a.K, kbeg + a.kchunk);
+
+  DirectOperand<T, MB, XV, D> gx;
+  DirectOperand<T, NB, YV, D> gy;
+  gx.init(a.xmn, m0 + r);
+  gy.init(a.ymn, n0 + r);
+  typename MF::Acc acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = typename MF::Acc{};
+
+  const int ns = (kend - kbeg + KS - 1) / KS;                // K steps of the unit
+  const int n = ns > wki ? (ns - wki + wk - 1) / wk : 0;     // this wave's
+  const int klast = kbeg + (wki + (n - 1) * wk) * KS;
+  // first k of this lane's run in step `it` (clamped: loads past the last
+  // step repeat it and are not used)
+  auto kof = [&](int it) {
+    const int k = kbeg + (wki + it * wk) * KS;
+    return (k < klast ? k : klast) + g * U;
+  };
+  uint32_t skip[D];  // entries of this lane's run that repeat earlier ones (alike in X and Y)
+  if (n > 0) {
+    auto load = [&](auto sc) {
+      constexpr int S = decltype(sc)::value;
+      gx.template load<S>(X);
+      gy.template load<S>(Y);
+      skip[S] = gx.ko[S][0] & 3u;
+    };
+    auto start = [&](auto sc) {
+      constexpr int S = decltype(sc)::value;
+      gx.template fetch<S>(a.xk, kof(S));
+      gy.template fetch<S>(a.yk, kof(S));
+      load(sc);
+    };
+    auto ahead = [&](auto sc) {
+      constexpr int S = decltype(sc)::value;
+      gx.template fetch<S>(a.xk, kof(S + D));
+      gy.template fetch<S>(a.yk, kof(S + D));
+    };
+    start(std::integral_constant<int, 0>{});
+    start(std::integral_constant<int, 1>{});
+    start(std::integral_constant<int, 2>{});
+    ahead(std::integral_constant<int, 0>{});
+    ahead(std::integral_constant<int, 1>{});
+    ahead(std::integral_constant<int, 2>{});
+    auto step = [&](auto sc, int it) {
+      constexpr int S = decltype(sc)::value;
+      if ((it == n - 1 && klast + KS > kend) || __builtin_amdgcn_ballot_w64(skip[S] != 0)) {
+        // entries past the end of K and repeated ones: zero in both operands
+        // (an Inf or NaN there must not reach the sum)
+        const int k0 = it == n - 1 ? klast + g * U : kbeg;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const bool in = k0 + u < kend && u >= (int)skip[S];
+#pragma unroll
+          for (int i = 0; i < MB; ++i) gx.v[S][i][u] = in ? gx.v[S][i][u] : T(0);
+#pragma unroll
+          for (int j = 0; j < NB; ++j) gy.v[S][j][u] = in ? gy.v[S][j][u] : T(0);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j) acc[i][j] = MF::mma(gx.v[S][i][u], gy.v[S][j][u], acc[i][j]);
+      load(sc);
+      gx.template fetch<S>(a.xk, kof(it + 2 * D));
+      gy.template fetch<S>(a.yk, kof(it + 2 * D));
+    };
+    for (int it = 0; it < n; it += D) {
+      step(std::integral_constant<int, 0>{}, it);
+      if (it + 1 < n) step(std::integral_constant<int, 1>{}, it + 1);
+      if (it + 2 < n) step(std::integral_constant<int, 2>{}, it + 2);
+    }
+  }
+
+  T* __restrict__ C = static_cast<T*>(a.c) + a.cl[l];
+  const T al = static_cast<T>(a.alpha), be = static_cast<T>(a.beta);
+  T* __restrict__ W = a.splits > 1 ? static_cast<T*>(a.work) + ((size_t)split * ntiles + t) * (size_t)(BM * BN) : nullptr;
+  if (wk == 1) {
+    // reads (indexing vectors, C) before the first write
+    uint32_t cmv[MB][4], cnv[NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) cmv[i][e] = a.cm[m0 + 16 * i + MF::row(lane, e)];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) cnv[j] = a.cn[n0 + 16 * j + r];
+    T cv[MB][NB][4];
+    if (be != T(0)) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) cv[i][j][e] = *global(at(C, cmv[i][e] + cnv[j]));
+    }
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int m = m0 + 16 * i + MF::row(lane, e), nn = n0 + 16 * j + r;
+          if (m < a.M && nn < a.N) {
+            T v = al * acc[i][j][e];
+            if (be != T(0)) v += be * cv[i][j][e];
+            *global(at(C, cmv[i][e] + cnv[j])) = v;
+          }
+        }
+    return;
+  }
+  // partial tiles of the waves, summed in wave order
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        part[wave * (BM * BN) + (16 * i + MF::row(lane, e)) * BN + 16 * j + r] = acc[i][j][e];
+  __syncthreads();
+  constexpr int PER = (BM * BN + 64 * NW - 1) / (64 * NW);
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int e = tid + q * 64 * NW;
+    if ((BM * BN) % (64 * NW) != 0 && e >= BM * BN) break;
+    const int mi = e / BN, ni = e % BN, m = m0 + mi, nn = n0 + ni;
+    T s = part[e];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += part[w * (BM * BN) + e];
+    if (W) {
+      *global(W + e) = s;
+    } else if (m < a.M && nn < a.N) {
+      auto* cp = global(at(C, a.cm[m] + a.cn[nn]));
+      T v = al * s;
+      if (be != T(0)) v += be * *cp;
+      *cp = v;
+    }
+  }
+}
+
+template <typename T, int MB, int NB, bool XV, bool YV>
+static hipError_t launch_nw(const PlainArgs<uint32_t>& a, const DirectCfg& d, int64_t xplane, int64_t yplane,
+                            hipStream_t s) {
+  const int64_t units = (int64_t)a.tiles_m * a.tiles_n * a.splits * a.L;
+  const int grid = (int)(d.wk == 1 ? (units + 3) / 4 : units);
+  hipLaunchKernelGGL((direct_contract<T, MB, NB, XV, YV, 4>), dim3(grid), dim3(256), 0, s, a, d.wk, xplane, yplane);
+  return hipGetLastError();
+}
+
+template <typename T, int MB, int NB>
+static hipError_t launch_modes(const PlainArgs<uint32_t>& a, const DirectCfg& d, bool xv, bool yv, int64_t xplane,
+                               int64_t yplane, hipStream_t s) {
+  if (xv && yv) return launch_nw<T, MB, NB, true, true>(a, d, xplane, yplane, s);
+  if (xv) return launch_nw<T, MB, NB, true, false>(a, d, xplane, yplane, s);
+  if (yv) return launch_nw<T, MB, NB, false, true>(a, d, xplane, yplane, s);
+  return launch_nw<T, MB, NB, false, false>(a, d, xplane, yplane, s);
+}
+
+template <typename T>
+static hipError_t launch_direct_t(const PlainArgs<uint32_t>& a, const DirectCfg& d, bool xv, bool yv, int64_t xplane,
+                                  int64_t yplane, hipStream_t s) {
+  if (d.bm == 16 && d.bn == 16) return launch_modes<T, 1, 1>(a, d, xv, yv, xplane, yplane, s);
+  if (d.bm == 32 && d.bn == 32) return launch_modes<T, 2, 2>(a, d, xv, yv, xplane, yplane, s);
+  if (d.bm == 16 && d.bn == 64) return launch_modes<T, 1, 4>(a, d, xv, yv, xplane, yplane, s);
+  if (d.bm == 64 && d.bn == 16) return launch_modes<T, 4, 1>(a, d, xv, yv, xplane, yplane, s);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_direct(int dtype, const PlainArgs<uint32_t>& a, const DirectCfg& d, bool xv, bool yv,
+                         int64_t xplane, int64_t yplane, hipStream_t s) {
+  return dtype == FAMLIES_F64 ? launch_direct_t<double>(a, d, xv, yv, xplane, yplane, s)
+                              : launch_direct_t<float>(a, d, xv, yv, xplane, yplane, s);
+}
+
+}  // namespace famlies

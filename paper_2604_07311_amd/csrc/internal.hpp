@@ -66,6 +66,26 @@ int analyze(int dtype, int compute, const famlies_tensor* A, const famlies_tenso
 void offsets(const std::vector<Mode>& modes, int which, int64_t n, int64_t n_pad,
              std::vector<int64_t>& out);
 
+// Contracted order in whole runs of `u` elements (16 bytes): every run of the
+// first contracted mode is padded to a multiple of u by letting its last
+// chunk of u start early (at ext - u), so every chunk is u distinct,
+// existing elements and a unit-stride operand reads it with one load.  The
+// chunk's first entries then repeat elements of the chunk before: `skip`
+// holds, per entry, how many entries from this one on (to the end of the
+// repeated ones) do not count, 0 for an entry that counts.  `index` is the
+// entry's place in the plain (column-major odometer) order.
+struct KRuns {
+  std::vector<int64_t> index;
+  std::vector<uint8_t> skip;
+};
+// Length of that order, or 0 where it does not pay: no operand has unit
+// stride along the first contracted mode, the mode is shorter than a chunk,
+// or the padding would add more than a quarter to K.  Equal to K when no run
+// needs padding.
+int64_t padded_k_length(const Analysis& an, int u);
+// The padded order (length padded_k_length(an, u), which must not be 0).
+void padded_k_runs(const Analysis& an, int u, KRuns* out);
+
 // Tile configuration of the plain kernels.
 // TileCfg::index_bits value that asks for int32 element offsets.
 constexpr int kForceElem32 = 33;
@@ -79,6 +99,13 @@ struct TileCfg {
   // split > 1: how many tiles, the last ones in tile order, run as `split`
   // K slices each; the others run whole K first (0: every tile is split)
   int tail = 0;
+};
+
+// Configuration of the direct kernel (small and narrow problems): tile
+// bm x bn per wave, wk waves of a workgroup sharing a tile along K, K ranges
+// over workgroups.  bm == 0: the plan runs the LDS-tiled kernel.
+struct DirectCfg {
+  int bm = 0, bn = 0, wk = 4, split = 1, kchunk = 0;
 };
 
 // Host-side bounds check of indexing vectors: every address an operand's

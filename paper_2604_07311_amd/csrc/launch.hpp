@@ -5,6 +5,7 @@
 
 #include "args.hpp"
 #include "famlies.h"
+#include "internal.hpp"
 
 namespace famlies {
 
@@ -17,6 +18,10 @@ struct PlainLaunch {
 hipError_t launch_plain(int dtype, const PlainArgs<uint32_t>& a, const PlainLaunch& L, hipStream_t s);
 hipError_t launch_plain(int dtype, const PlainArgs<int32_t>& a, const PlainLaunch& L, hipStream_t s);
 hipError_t launch_plain(int dtype, const PlainArgs<int64_t>& a, const PlainLaunch& L, hipStream_t s);
+hipError_t launch_direct(int dtype, const PlainArgs<uint32_t>& a, const DirectCfg& d, bool xv, bool yv,
+                         int64_t xplane, int64_t yplane, hipStream_t s);
+// C = alpha * sum over K ranges of W + beta * C for the split tiles (bm x bn blocks of partial sums).
+hipError_t launch_splitk_reduce(int dtype, const PlainArgs<uint32_t>& a, int bm, int bn, hipStream_t s);
 bool plain_tile_supported(int dtype, int bm, int bn, int bk);
 
 }  // namespace famlies

@@ -204,6 +204,16 @@ hipError_t launch_plain(int dtype, const PlainArgs<int64_t>& a, const PlainLaunc
                               : launch_plain_t<float, int64_t>(a, L, s);
 }
 
+hipError_t launch_splitk_reduce(int dtype, const PlainArgs<uint32_t>& a, int bm, int bn, hipStream_t s) {
+  const int64_t red = ((int64_t)a.tiles_m * a.tiles_n - a.head) * bm * bn;
+  const dim3 grid((int)((red + kThreads - 1) / kThreads));
+  if (dtype == FAMLIES_F64)
+    hipLaunchKernelGGL((splitk_reduce<double, uint32_t>), grid, dim3(kThreads), 0, s, a, bm, bn);
+  else
+    hipLaunchKernelGGL((splitk_reduce<float, uint32_t>), grid, dim3(kThreads), 0, s, a, bm, bn);
+  return hipGetLastError();
+}
+
 bool plain_tile_supported(int dtype, int bm, int bn, int bk) {
   const int BK = dtype == FAMLIES_F64 ? 8 : 32;
   return bk == BK && ((bm == 128 && bn == 128) || (bm == 64 && bn == 64));

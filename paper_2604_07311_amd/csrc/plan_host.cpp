@@ -98,6 +98,83 @@ TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_t
   return pick;
 }
 
+// The direct kernel reads every operand element once per tile of the other
+// side, so it is bound by L2 (about 9 TB/s measured over its shapes: 32 x 32
+// tiles 107 to 2147 MB in 17.8 to 241 us) where there are many tiles, and by
+// the latency of one wave's K steps where there are few; the LDS-tiled kernel
+// pays a barrier and a memory round trip per K slice and, with split-K, a
+// second launch.  Both are estimated in microseconds from constants measured
+// on MI355X and the smaller wins.  Examples, tiled -> direct: FP64 256^3
+// 11.0 -> 5.8 us, FP64 144 x 1444 x 1444 34 -> 26, FP32 900^3 (runs of 30)
+// 42 -> 31, FP64 16 x 675840 x 64 142 -> 108; the other way FP32 256 x 4096 x
+// 4096 takes 78 tiled and 125 direct, so direct is not considered above 4
+// GFLOP except for narrow problems.
+DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const TileCfg& t) {
+  DirectCfg none;
+  if (an.M == 0 || an.N == 0 || an.K == 0) return none;
+  const double flops = 2.0 * (double)an.M * (double)an.N * (double)an.K * (double)an.L;
+  const bool narrow = std::min(an.M, an.N) <= 32;
+  if (flops > 4e9 && !narrow) return none;
+  const double es = an.esize, cus = h ? h->num_cus : 256;
+  const int u = 16 / an.esize, ks = 4 * u;
+  const int64_t kr = padded_k_length(an, u), K = kr ? kr : an.K;
+  // an operand gathered along K but not in 16-byte runs touches a cache line
+  // per element
+  const bool xrun = kr && an.P[0].sx == 1, yrun = kr && an.P[0].sy == 1;
+  const double xw = an.x_kfast && !xrun ? 2.5 : 1.0, yw = an.y_kfast && !yrun ? 2.5 : 1.0;
+  const double unique = ((double)an.M * an.K + (double)an.N * an.K + (double)an.M * an.N) * (double)an.L * es;
+  const double hbm_us = unique / 4.3e6;
+
+  // the tiled kernel
+  const int64_t tiles = ceil_div(an.M, t.bm) * ceil_div(an.N, t.bn) * an.L;
+  const int64_t split_tiles = t.split > 1 ? (t.tail ? t.tail : tiles) : 0;
+  const double units = (double)(tiles - split_tiles) + (double)split_tiles * t.split;
+  const double slices = (double)ceil_div(ceil_div(an.K, split_tiles == tiles ? t.split : 1), an.esize == 8 ? 8 : 32);
+  const bool full = units > cus;  // two workgroups share a CU
+  const double slice_us = t.bm == 64 ? (an.esize == 8 ? (full ? 0.72 : 0.45) : (full ? 1.5 : 0.92))
+                                     : (an.esize == 8 ? 1.9 : xw + yw > 2.0 ? 5.0 : 3.8);
+  double tiled = 3.5 + std::max(std::max(1.0, units / (2.0 * cus)) * slices * slice_us, hbm_us);
+  if (t.split > 1) tiled += 4.0 + (double)(t.split + 1) * (double)split_tiles * t.bm * t.bn * es / 4.0e6;
+
+  DirectCfg best = none;
+  double best_us = 0.95 * tiled;
+  const int shapes[4][2] = {{16, 16}, {32, 32}, {16, 64}, {64, 16}};
+  for (const auto& sh : shapes)
+    for (int wk : {1, 4})
+      for (int split : {1, 4, 16, 64}) {
+        if (split > 1 && (an.L > 1 || wk == 1 || K / split < 16 * ks)) continue;
+        const double n = (double)ceil_div(an.M, sh[0]) * (double)ceil_div(an.N, sh[1]) * (double)an.L * split;
+        if (n * wk > 1e9) continue;
+        const double steps = (double)ceil_div(ceil_div(K, split), ks);
+        const double rows = xw * (double)std::min<int64_t>(an.M, sh[0]) + yw * (double)std::min<int64_t>(an.N, sh[1]);
+        const double l2_us = n * rows * steps * ks * es / 9.0e6;
+        const double step_us = sh[0] * sh[1] == 256 ? (an.esize == 8 ? 0.20 : 0.27) : 0.43;
+        const double mfma_us = n * sh[0] * sh[1] * steps * ks * 2.0 / (an.esize == 8 ? 6.0e7 : 1.2e8);
+        // narrow tiles touch memory in short segments: FP64 16 x 675840 x 64
+        // takes 130 us in 16 x 16 tiles, 120 in 32 x 32, 108 in 16 x 64
+        const double mem_us = hbm_us * (sh[0] * sh[1] == 256 ? 1.25 : sh[0] == sh[1] ? 1.1 : 1.0);
+        double us = 4.0 + std::max(std::max(std::ceil(steps / wk) * step_us, mfma_us), std::max(l2_us, mem_us));
+        if (wk > 1) us += 0.0012 * n;  // the waves' partial tiles through LDS
+        if (split > 1) us += 4.0 + (double)(split + 1) * (double)an.M * (double)an.N * es / 4.0e6;
+        if (us < best_us) {
+          best_us = us;
+          best.bm = sh[0];
+          best.bn = sh[1];
+          best.wk = wk;
+          best.split = split;
+        }
+      }
+  return best;
+}
+
+bool contiguous_k_runs(const std::vector<int64_t>& ks, int64_t K, int u) {
+  if (K < 1 || K % u) return false;
+  for (int64_t b = 0; b < K; b += u)
+    for (int j = 1; j < u; ++j)
+      if (ks[(size_t)(b + j)] != ks[(size_t)b] + j) return false;
+  return true;
+}
+
 // Settle split-K: K slices of whole BK-blocks, and the number of tiles
 // computed whole first (*head; every tile when there is no split).
 void finalize_split(TileCfg* t, int64_t K, int64_t ntiles, int* kchunk, int* head) {
@@ -246,8 +323,8 @@ bool log_enabled() {
 // One line on stderr: what the planner decided (orientation, loaders, tile,
 // split, index form -- index_bits 32: uint32 bytes, -32: int32 elements, 64:
 // int64 elements -- and workspace).
-void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, int index_bits, bool x_vec,
-                  bool y_vec, size_t work_bytes, bool table_hit) {
+void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d, int index_bits,
+                  bool x_vec, bool y_vec, size_t work_bytes, bool table_hit) {
   static const char* loader[4] = {"rows", "k-gather", "packed", "k-affine"};
   const int xm = an.x_kfast ? (x_vec ? 3 : 1) : 0, ym = an.y_kfast ? (y_vec ? 3 : 1) : 0;
   static const char* int8_names[8] = {"", "", "", "int8x3", "int8x4", "int8x5", "int8x6", "int8x7"};
@@ -255,16 +332,18 @@ void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, int 
                      : an.compute == FAMLIES_BF16X6 ? "bf16x6"
                      : int8_slices(an.compute)      ? int8_names[int8_slices(an.compute)]
                                                     : "native";
+  char direct[64] = "";
+  if (d.bm) std::snprintf(direct, sizeof direct, " direct=%dx%d/%d waves/split %d", d.bm, d.bn, d.wk, d.split);
   std::fprintf(stderr,
                "[famlies] %s %s/%s M=%lld N=%lld K=%lld L=%lld swapped=%d groups=%zu/%zu/%zu/%zu "
                "trace=%d diag=%d X=%s Y=%s tile=%dx%dx%d split=%d split_tiles=%d index=%s "
-               "workspace=%zu B%s\n",
+               "workspace=%zu B%s%s\n",
                what, an.dtype == FAMLIES_F64 ? "f64" : "f32", comp, (long long)an.M, (long long)an.N,
                (long long)an.K, (long long)an.L, an.swapped ? 1 : 0, an.I.size(), an.J.size(), an.P.size(),
                an.Lm.size(), an.n_trace, an.n_diag, loader[xm], loader[ym], cfg.bm, cfg.bn, cfg.bk, cfg.split,
                cfg.split > 1 ? (cfg.tail ? cfg.tail : -1) : 0,
                index_bits == 32 ? "u32-bytes" : index_bits == -32 ? "i32-elements" : "i64-elements", work_bytes,
-               table_hit ? " (tile table)" : "");
+               table_hit ? " (tile table)" : "", direct);
 }
 
 }  // namespace famlies
@@ -304,7 +383,9 @@ static famlies_status analyze_impl(int dtype, int compute, const famlies_tensor*
   }
   fill_info(an, t, ib, kernel_code(an, xv, yv), info);
   info->index_elements = ib == 64 || e32;
-  if (log_enabled()) log_decision("analyze", an, t, e32 ? -32 : ib, xv, yv, 0, false);
+  const bool native = !split_parts(an.compute) && !int8_slices(an.compute);
+  const DirectCfg d = native && ib == 32 && !e32 ? choose_direct(nullptr, an, t) : DirectCfg();
+  if (log_enabled()) log_decision("analyze", an, t, d, e32 ? -32 : ib, xv, yv, 0, false);
   if (offs) {
     const int64_t need = 2 * an.M + 2 * an.K + 2 * an.N + 3 * an.L;
     if (offs_len < need) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_analyze: offsets buffer too short");

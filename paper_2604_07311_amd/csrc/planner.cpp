@@ -385,6 +385,29 @@ void offsets(const std::vector<Mode>& modes, int which, int64_t n, int64_t n_pad
   }
 }
 
+int64_t padded_k_length(const Analysis& an, int u) {
+  if (an.P.empty() || an.K == 0 || an.P[0].blk > 0) return 0;
+  const Mode& m = an.P[0];
+  if ((m.sx != 1 && m.sy != 1) || m.ext < u) return 0;
+  const int64_t run = (m.ext + u - 1) / u * u;
+  if (4 * run > 5 * m.ext) return 0;
+  return an.K / m.ext * run;
+}
+
+void padded_k_runs(const Analysis& an, int u, KRuns* out) {
+  const int64_t e = an.P[0].ext, runs = an.K / e;
+  out->index.clear();
+  out->skip.clear();
+  for (int64_t r = 0; r < runs; ++r)
+    for (int64_t c = 0; c < e; c += u) {
+      const int64_t start = std::min(c, e - u);
+      for (int64_t j = 0; j < u; ++j) {
+        out->index.push_back(r * e + start + j);
+        out->skip.push_back((uint8_t)std::max<int64_t>(0, c - start - j));
+      }
+    }
+}
+
 bool offsets_in_span(const std::vector<int64_t>& a, int64_t na, const std::vector<int64_t>& b, int64_t nb,
                      const std::vector<int64_t>& l, int64_t nl, int64_t lo, int64_t hi) {
   if (na <= 0 || nb <= 0 || nl <= 0) return true;  // no element is addressed

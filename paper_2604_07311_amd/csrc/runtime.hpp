@@ -65,6 +65,13 @@ struct famlies_plan_s {
   // X / Y are K-gathered from affine unit-stride K blocks with 16-byte
   // aligned run starts (given a 16-byte aligned base pointer)
   bool x_vec = false, y_vec = false;
+  famlies::DirectCfg direct;                // bm > 0: native kMain launches run the direct kernel
+  bool dx_vec = false, dy_vec = false;      // direct kernel: X / Y read 16 bytes along K per load
+  int64_t direct_k = 0;                     // direct kernel: K of its contracted order (KRuns where they pay)
+  size_t dk_pos[2] = {0, 0};                // direct kernel: contracted offsets of X, Y
+  bool pk_vec[2] = {false, false};          // the same for a pre-packed X / Y
+  bool pk_fits[2] = {false, false};         // direct kernel: 32-bit offsets reach all of the pre-packed X / Y
+  size_t pk_pos[4] = {0, 0, 0, 0};          // direct kernel, pre-packed operands: X rows, X k, Y rows, Y k
   bool table_hit = false;  // the tile came from the handle's tile table
   void* d_work = nullptr;  // split-K partial sums
   size_t work_bytes = 0;
@@ -122,8 +129,8 @@ inline famlies_plan_s* plan_of(const void* tok) {
 // FAMLIES_LOG is set to a non-empty value other than "0".
 bool log_enabled();
 void log_plan(const famlies_plan_s* p);
-void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, int index_bits, bool x_vec,
-                  bool y_vec, size_t work_bytes, bool table_hit);
+void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d, int index_bits,
+                  bool x_vec, bool y_vec, size_t work_bytes, bool table_hit);
 
 // Internal forms of the ABI calls, on resolved objects.
 famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, const void* B, double beta,
@@ -135,6 +142,11 @@ void destroy_plan(famlies_plan_s* p);
 TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_table = nullptr);
 
 // Host planning helpers (plan_host.cpp).
+// The direct kernel's configuration where it beats the LDS-tiled kernel with
+// configuration t, else bm = 0.
+DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const TileCfg& t);
+// Whether every aligned run of u contracted indices is contiguous.
+bool contiguous_k_runs(const std::vector<int64_t>& ks, int64_t K, int u);
 int64_t ceil_div(int64_t a, int64_t b);
 // Settle split-K: K slices of whole BK-blocks, and the number of tiles
 // computed whole first (*head; every tile when there is no split).
