@@ -66,47 +66,14 @@ DeviceGuard::~DeviceGuard() {
   if (prev >= 0) (void)hipSetDevice(prev);
 }
 
-// The direct kernel's own vectors (byte offsets, skip counts in the low two
-// bits): contracted offsets of X and Y in its order, then for each operand
-// the rows and contracted offsets of its pre-packed form -- block (tile, kb)
-// of BR x bk elements, [row][k] -- so that the same kernel reads either and
-// sums in the same order.  v: the plan's indexing vectors in elements.
-static void direct_vectors(famlies_plan_s* p, const std::vector<int64_t>* v, std::vector<uint32_t>* out) {
-  const Analysis& an = p->an;
-  const int u = 16 / an.esize;
-  const int64_t es = an.esize, ks = 4 * u;
-  KRuns kr;
-  const bool padded = padded_k_length(an, u) > 0;
-  if (padded) padded_k_runs(an, u, &kr);
-  const int64_t n = padded ? (int64_t)kr.index.size() : an.K;
-  const int64_t np = ceil_div(n, ks) * ks;  // == p->direct_k rounded up to whole steps
-  const int bk = p->cfg.bk;
-  const int64_t nkb = ceil_div(an.K, bk);
-  std::vector<int64_t> elem[2];
-  for (int op = 0; op < 2; ++op) {
-    const std::vector<int64_t>& k = v[1 + op];
-    elem[op].resize((size_t)n);
-    for (int64_t i = 0; i < n; ++i) elem[op][(size_t)i] = k[(size_t)(padded ? kr.index[(size_t)i] : i)];
-    (op ? p->dy_vec : p->dx_vec) = contiguous_k_runs(elem[op], n, u);
-    out[op].assign((size_t)np, 0);
-    const int br = op ? p->cfg.bn : p->cfg.bm;
-    std::vector<uint32_t>& pr = out[2 + 2 * op];
-    std::vector<uint32_t>& pk = out[3 + 2 * op];
-    const int64_t rows = (int64_t)v[3 * op].size();
-    pr.resize((size_t)rows);
-    for (int64_t r = 0; r < rows; ++r) pr[(size_t)r] = (uint32_t)((r / br * nkb * br * bk + r % br * bk) * es);
-    pk.assign((size_t)np, 0);
-    std::vector<int64_t> packed((size_t)n);
-    for (int64_t i = 0; i < n; ++i) {
-      const uint32_t skip = padded ? kr.skip[(size_t)i] : 0;
-      const int64_t k1 = padded ? kr.index[(size_t)i] : i;
-      out[op][(size_t)i] = (uint32_t)(uint64_t)(elem[op][(size_t)i] * es) | skip;
-      packed[(size_t)i] = k1 / bk * br * bk + k1 % bk;
-      pk[(size_t)i] = (uint32_t)(packed[(size_t)i] * es) | skip;
-    }
-    p->pk_vec[op] = contiguous_k_runs(packed, n, u);
-    p->pk_fits[op] = rows * nkb * bk * es < ((int64_t)1 << 32);
-  }
+// Rows and contracted offsets of an operand's pre-packed form -- block
+// (tile, kb) of br x bk elements, [row][k] -- for the direct kernel, which
+// then reads a packed operand like any other and sums in the same order.
+static void packed_vectors(int64_t rows, int64_t kd, int64_t kp, int br, int bk, int64_t es, uint32_t* pr,
+                           uint32_t* pk) {
+  const int64_t nkb = ceil_div(kd, bk);
+  for (int64_t r = 0; r < rows; ++r) pr[r] = (uint32_t)((r / br * nkb * br * bk + r % br * bk) * es);
+  for (int64_t k = 0; k < kp; ++k) pk[k] = k < nkb * bk ? (uint32_t)((k / bk * br * bk + k % bk) * es) : 0u;
 }
 
 template <typename OffT>
@@ -114,8 +81,8 @@ static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int
   const Analysis& an = p->an;
   std::vector<int64_t> v[9];
   offsets(an.I, 0, an.M, mp, v[0]);
-  offsets(an.P, 0, an.K, kp, v[1]);
-  offsets(an.P, 1, an.K, kp, v[2]);
+  offsets(an.P, 0, an.K, std::max(an.K, kp), v[1]);
+  offsets(an.P, 1, an.K, std::max(an.K, kp), v[2]);
   offsets(an.J, 1, an.N, np, v[3]);
   offsets(an.I, 2, an.M, mp, v[4]);
   offsets(an.J, 2, an.N, np, v[5]);
@@ -127,12 +94,54 @@ static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int
   const bool rebase = sizeof(OffT) == 4, bytes = std::is_same<OffT, uint32_t>::value;
   const int64_t es = an.esize;
   vec_flags(an, p->cfg.bk, sizeof(OffT) == 4 ? 32 : 64, v, &p->x_vec, &p->y_vec);
+  // host-side bounds check of the vectors against the descriptors' spans
+  const int64_t x_lo = an.swapped ? an.b_lo : an.a_lo, x_hi = an.swapped ? an.b_hi : an.a_hi;
+  const int64_t y_lo = an.swapped ? an.a_lo : an.b_lo, y_hi = an.swapped ? an.a_hi : an.b_hi;
+  if ((an.K > 0 && (!offsets_in_span(v[0], an.M, v[1], an.K, v[6], an.L, x_lo, x_hi) ||
+                    !offsets_in_span(v[3], an.N, v[2], an.K, v[7], an.L, y_lo, y_hi))) ||
+      !offsets_in_span(v[4], an.M, v[5], an.N, v[8], an.L, an.c_lo, an.c_hi))
+    return fail(FAMLIES_ERR_BOUNDS, "planner: an indexing vector addresses outside its tensor's span");
+  p->xmode = an.x_kfast ? (p->x_vec ? 3 : 1) : 0;
+  p->ymode = an.y_kfast ? (p->y_vec ? 3 : 1) : 0;
+  // the kernels' contracted order (the plain one, or padded to 16-byte runs)
+  // and its void mask; byte offsets of the plain and bf16 kernels only
+  std::vector<uint32_t> kvoid;
+  const int u = 16 / an.esize;
+  if (bytes && !int8_slices(an.compute)) {
+    kvoid.assign((size_t)(ceil_div(kp, 32) + 1), 0);
+    KRuns kr;
+    const bool padded = p->kd != an.K;
+    if (padded) {
+      padded_k_runs(an, u, &kr);
+      for (int i = 1; i <= 2; ++i) {
+        std::vector<int64_t> w((size_t)kp, 0);
+        for (int64_t k = 0; k < p->kd; ++k) w[(size_t)k] = v[i][(size_t)kr.index[(size_t)k]];
+        v[i].swap(w);
+      }
+    }
+    for (int64_t k = 0; k < (int64_t)kvoid.size() * 32; ++k)
+      if (k >= p->kd || (padded && kr.skip[(size_t)k])) kvoid[(size_t)(k >> 5)] |= 1u << (k & 31);
+    p->dx_vec = contiguous_k_runs(v[1], p->kd, u);
+    p->dy_vec = contiguous_k_runs(v[2], p->kd, u);
+    const int run = padded || p->kd % p->cfg.bk ? 4 : 3;
+    if (an.x_kfast) p->xmode = p->dx_vec ? run : 1;
+    if (an.y_kfast) p->ymode = p->dy_vec ? run : 1;
+  }
+  for (int i = 1; i <= 2; ++i) v[i].resize((size_t)kp);
+  std::vector<uint32_t> packed[4];  // direct kernel: rows and k's of a packed X, then of a packed Y
+  if (p->direct.bm && bytes)
+    for (int op = 0; op < 2; ++op) {
+      const int64_t rows = op ? np : mp;
+      const int br = op ? p->cfg.bn : p->cfg.bm;
+      packed[2 * op].resize((size_t)rows);
+      packed[2 * op + 1].resize((size_t)kp);
+      packed_vectors(rows, p->kd, kp, br, p->cfg.bk, es, packed[2 * op].data(), packed[2 * op + 1].data());
+      p->pk_fits[op] = rows * ceil_div(p->kd, p->cfg.bk) * p->cfg.bk * es < ((int64_t)1 << 32);
+    }
   const int64_t shift[6] = {an.x_lo, 0, 0, an.y_lo, an.c_lo_mn, 0};
-  size_t n6 = 0;
+  size_t n6 = kvoid.size();
   for (int i = 0; i < 6; ++i) n6 += v[i].size();
-  std::vector<uint32_t> extra[6];
-  if (p->direct.bm) direct_vectors(p, v, extra);
-  for (const auto& x : extra) n6 += x.size();
+  for (const auto& x : packed) n6 += x.size();
   const size_t b6 = (n6 * sizeof(OffT) + 7) & ~(size_t)7;
   const size_t total = b6 + 3 * (size_t)an.L * sizeof(int64_t);
   std::vector<char>& host = *image;
@@ -150,23 +159,18 @@ static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int
         o[pos++] = (OffT)x;
     }
   }
-  for (int i = 0; i < 6; ++i) {
-    (i < 2 ? p->dk_pos[i] : p->pk_pos[i - 2]) = pos;
-    for (uint32_t x : extra[i]) o[pos++] = (OffT)x;
+  for (int i = 0; i < 4; ++i) {
+    p->pk_pos[i] = pos;
+    for (uint32_t x : packed[i]) o[pos++] = (OffT)x;
   }
+  p->kvoid_pos = pos;
+  for (uint32_t x : kvoid) o[pos++] = (OffT)x;
   int64_t* lb = reinterpret_cast<int64_t*>(host.data() + b6);
   for (int i = 0; i < 3; ++i) {
     p->off_pos[6 + i] = (size_t)i * (size_t)an.L;
     for (int64_t l = 0; l < an.L; ++l) lb[i * an.L + l] = v[6 + i][(size_t)l];
   }
   p->batch_off_bytes = b6;
-  // host-side bounds check of the vectors against the descriptors' spans
-  const int64_t x_lo = an.swapped ? an.b_lo : an.a_lo, x_hi = an.swapped ? an.b_hi : an.a_hi;
-  const int64_t y_lo = an.swapped ? an.a_lo : an.b_lo, y_hi = an.swapped ? an.a_hi : an.b_hi;
-  if ((an.K > 0 && (!offsets_in_span(v[0], an.M, v[1], an.K, v[6], an.L, x_lo, x_hi) ||
-                    !offsets_in_span(v[3], an.N, v[2], an.K, v[7], an.L, y_lo, y_hi))) ||
-      !offsets_in_span(v[4], an.M, v[5], an.N, v[8], an.L, an.c_lo, an.c_hi))
-    return fail(FAMLIES_ERR_BOUNDS, "planner: an indexing vector addresses outside its tensor's span");
   return FAMLIES_OK;
 }
 
@@ -193,7 +197,8 @@ static PlainArgs<OffT> make_args(const famlies_plan_s* p, const void* x, const v
   a.cl = lb + p->off_pos[8];
   a.M = (int32_t)p->an.M;
   a.N = (int32_t)p->an.N;
-  a.K = (int32_t)p->an.K;
+  a.kvoid = reinterpret_cast<const uint32_t*>(o + p->kvoid_pos);
+  a.K = (int32_t)p->kd;
   a.L = (int32_t)p->an.L;
   a.x_nkb = 0;
   a.y_nkb = 0;
@@ -214,7 +219,7 @@ static PlainArgs<OffT> make_args(const famlies_plan_s* p, const void* x, const v
 // *image is left empty when C has no elements.
 static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int dtype, int compute,
                                    const famlies_tensor* A, const famlies_tensor* B, const famlies_tensor* C,
-                                   const TileCfg* force, std::vector<char>* image, bool allow_direct = true) {
+                                   const TileCfg* force, std::vector<char>* image, bool lean = false) {
   Analysis an;
   std::string err;
   int st = analyze(dtype, compute, A, B, C, &an, &err);
@@ -229,6 +234,10 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   if (i8 && force) p->cfg.index_bits = force->index_bits;
   index_form(an, p->cfg.index_bits, &p->index_bits, &p->elem32);
   const int ns = split_parts(compute);
+  // contracted order of the kernels: padded to 16-byte runs where that pays
+  const int64_t runs =
+      lean || i8 || p->index_bits != 32 || p->elem32 ? 0 : padded_k_length(an, 16 / an.esize);
+  p->kd = runs && runs <= lim ? runs : an.K;
   if (i8) {
     // fixed tile (int8_tile): no split-K, no tile table
   } else if (ns) {
@@ -251,6 +260,8 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
       bool xv = false, yv = false;
       all_offsets(an, v);
       vec_flags(an, 32, index_bits_for(an), v, &xv, &yv);
+      xv = xv || (runs && an.P[0].sx == 1);
+      yv = yv || (runs && an.P[0].sy == 1);
       if (!xv && !yv) {
         p->cfg.bm = 256;
         p->cfg.bn = 128;
@@ -263,19 +274,17 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   }
   if (an.L > 1) p->cfg.split = 1;  // batch modes already multiply the tile count
   const int64_t ntiles = ceil_div(an.M, p->cfg.bm) * ceil_div(an.N, p->cfg.bn);
-  finalize_split(&p->cfg, an.K, ntiles, &p->kchunk, &p->head);
+  finalize_split(&p->cfg, p->kd, ntiles, &p->kchunk, &p->head);
   if (ntiles * p->cfg.split * an.L >= ((int64_t)1 << 31))
     return fail(FAMLIES_ERR_UNSUPPORTED, "the tile grid exceeds 2^31 workgroups");
-  if (allow_direct && !force && !p->table_hit && !i8 && !ns && p->index_bits == 32 && !p->elem32) {
+  if (!lean && !force && !p->table_hit && !i8 && !ns && p->index_bits == 32 && !p->elem32) {
     p->direct = choose_direct(h, an, p->cfg);
     if (p->direct.bm) {
-      const int u = 16 / an.esize, ks = 4 * u;
+      const int ks = 64 / an.esize;
       DirectCfg& d = p->direct;
-      const int64_t kr = padded_k_length(an, u);
-      p->direct_k = kr ? kr : an.K;
       if (an.L > 1) d.split = 1;
-      d.kchunk = (int)(ceil_div(ceil_div(p->direct_k, d.split), ks) * ks);
-      d.split = (int)ceil_div(p->direct_k, d.kchunk);
+      d.kchunk = (int)(ceil_div(ceil_div(p->kd, d.split), ks) * ks);
+      d.split = (int)ceil_div(p->kd, d.kchunk);
     }
   }
   image->clear();
@@ -283,7 +292,7 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   if (an.M == 0 || an.N == 0) return FAMLIES_OK;
   const int64_t mp = ceil_div(std::max<int64_t>(an.M, 1), p->cfg.bm) * p->cfg.bm;
   const int64_t np = ceil_div(std::max<int64_t>(an.N, 1), p->cfg.bn) * p->cfg.bn;
-  const int64_t kp = ceil_div(std::max<int64_t>(an.K, 1), p->cfg.bk) * p->cfg.bk + p->cfg.bk;
+  const int64_t kp = ceil_div(std::max<int64_t>(p->kd, 1), p->cfg.bk) * p->cfg.bk + p->cfg.bk;
   st = p->index_bits == 64 ? index_image<int64_t>(p, mp, np, kp, image)
        : p->elem32          ? index_image<int32_t>(p, mp, np, kp, image)
                             : index_image<uint32_t>(p, mp, np, kp, image);
@@ -500,9 +509,8 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
   L.bm = p->cfg.bm;
   L.bn = p->cfg.bn;
   L.bk = p->cfg.bk;
-  // affine-block 16-byte loads need a 16-byte aligned base pointer
-  L.xm = xp ? 2 : (an.x_kfast ? (p->x_vec && !((uintptr_t)x & 15) ? 3 : 1) : 0);
-  L.ym = yp ? 2 : (an.y_kfast ? (p->y_vec && !((uintptr_t)y & 15) ? 3 : 1) : 0);
+  L.xm = xp ? 2 : p->xmode;
+  L.ym = yp ? 2 : p->ymode;
   L.kind = (an.K == 0 || alpha == 0.0) ? PlainLaunch::kScale : PlainLaunch::kMain;
   hipError_t e;
   const int ns = split_parts(an.compute);
@@ -522,11 +530,11 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
       PlainArgs<uint32_t> a = make_args<uint32_t>(p, x, y, C, alpha, beta);
       if (xp) {  // the packed buffer is addressed from its start, not through offsets
         a.x = x;
-        a.x_nkb = (int32_t)((an.K + L.bk - 1) / L.bk);
+        a.x_nkb = (int32_t)((p->kd + L.bk - 1) / L.bk);
       }
       if (yp) {
         a.y = y;
-        a.y_nkb = (int32_t)((an.K + L.bk - 1) / L.bk);
+        a.y_nkb = (int32_t)((p->kd + L.bk - 1) / L.bk);
       }
       e = launch_split(a, L, ns, s);
     } else {
@@ -538,28 +546,25 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
     PlainArgs<uint32_t> a = make_args<uint32_t>(p, x, y, C, alpha, beta);
     if (xp) {
       a.x = x;
-      a.x_nkb = (int32_t)((an.K + L.bk - 1) / L.bk);
+      a.x_nkb = (int32_t)((p->kd + L.bk - 1) / L.bk);
     }
     if (yp) {
       a.y = y;
-      a.y_nkb = (int32_t)((an.K + L.bk - 1) / L.bk);
+      a.y_nkb = (int32_t)((p->kd + L.bk - 1) / L.bk);
     }
     if (p->direct.bm && L.kind == PlainLaunch::kMain && (!xp || p->pk_fits[0]) && (!yp || p->pk_fits[1])) {
       const DirectCfg& d = p->direct;
       const uint32_t* o = static_cast<const uint32_t*>(p->d_off);
-      a.xk = o + (xp ? p->pk_pos[1] : p->dk_pos[0]);
-      a.yk = o + (yp ? p->pk_pos[3] : p->dk_pos[1]);
-      if (xp) a.xmn = o + p->pk_pos[0];
-      if (yp) a.ymn = o + p->pk_pos[2];
+      if (xp) a.xmn = o + p->pk_pos[0], a.xk = o + p->pk_pos[1];
+      if (yp) a.ymn = o + p->pk_pos[2], a.yk = o + p->pk_pos[3];
       const int64_t xplane = xp ? (int64_t)a.tiles_m * a.x_nkb * L.bm * L.bk : 0;
       const int64_t yplane = yp ? (int64_t)a.tiles_n * a.y_nkb * L.bn * L.bk : 0;
-      a.K = (int32_t)p->direct_k;
       a.tiles_m = (int32_t)ceil_div(an.M, d.bm);
       a.tiles_n = (int32_t)ceil_div(an.N, d.bn);
       a.splits = d.split;
       a.kchunk = d.kchunk;
       a.head = 0;
-      e = launch_direct(an.dtype, a, d, xp ? p->pk_vec[0] : p->dx_vec, yp ? p->pk_vec[1] : p->dy_vec, xplane, yplane, s);
+      e = launch_direct(an.dtype, a, d, xp || p->dx_vec, yp || p->dy_vec, xplane, yplane, s);
       if (e == hipSuccess && d.split > 1) e = launch_splitk_reduce(an.dtype, a, d.bm, d.bn, s);
     } else {
       e = launch_plain(an.dtype, a, L, s);
@@ -605,11 +610,11 @@ static famlies_status contract_noalloc_impl(famlies_handle htok, int dtype, int 
   famlies_status st = prepare_plan(h, &p, dtype, compute, A, B, C, nullptr, &image);
   if (st != FAMLIES_OK) return st;
   size_t off_bytes = (image.size() + 255) & ~(size_t)255;
-  if (p.direct.bm && off_bytes + p.work_bytes > kNoAllocScratchBytes) {
-    // the direct kernel's extra vectors do not fit: plan without it
+  if (off_bytes + p.work_bytes > kNoAllocScratchBytes) {
+    // without the direct kernel's extra vectors and the padded contracted order
     p = famlies_plan_s();
     p.owns_device = false;
-    st = prepare_plan(h, &p, dtype, compute, A, B, C, nullptr, &image, false);
+    st = prepare_plan(h, &p, dtype, compute, A, B, C, nullptr, &image, true);
     if (st != FAMLIES_OK) return st;
     off_bytes = (image.size() + 255) & ~(size_t)255;
   }

@@ -22,6 +22,7 @@ struct PlainArgs {
   const int64_t* xl;  // batch offsets of X, Y, C in elements (L entries each)
   const int64_t* yl;
   const int64_t* cl;
+  const uint32_t* kvoid;  // bit k % 32 of word k / 32: entry k of the contracted order does not count
   int32_t M, N, K, L;
   int32_t x_nkb, y_nkb;  // k-blocks per tile row of a pre-packed X / Y (0: not packed)
   int32_t tiles_m, tiles_n, splits, kchunk;

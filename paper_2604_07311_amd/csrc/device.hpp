@@ -231,6 +231,18 @@ struct TileGather {
     else
       store_impl<true, S>(lds, k0, kend);
   }
+  // The same with the slice's void mask (bit k: index k of the slice does not
+  // count and is stored as 0).
+  template <int S = 0>
+  __device__ __forceinline__ void store_masked(T* __restrict__ lds, uint32_t voids) {
+    if (voids) clear<S>(voids);
+    store_impl<false, S>(lds, 0, 0);
+  }
+  template <int S = 0>
+  __device__ __forceinline__ void clear(uint32_t voids) {
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[S][j] = (voids >> krel(j)) & 1u ? T(0) : v[S][j];
+  }
 };
 
 // Loader for a pre-packed operand (the packing step hoisted out of repeated
@@ -273,18 +285,31 @@ struct PackedGather {
       *reinterpret_cast<vec_t*>(lds + (e / BK) * LDK + e % BK) = v[S][q];
     }
   }
+  template <int S = 0>
+  __device__ __forceinline__ void store_masked(T* __restrict__ lds, uint32_t /*voids: packed as 0*/) const {
+    store<S>(lds, 0, 0);
+  }
 };
 
-// Loader for a K-gathered operand stored in affine blocks (the block-scatter
-// layout's block strides, Approach, "Supporting tensor computations"): in
-// every BK-slice of K the indexing vector is a progression of step one
-// element, and every run start is 16-byte aligned, so a row's slice is a
-// contiguous run in memory.  Each thread reads VK consecutive k's of a row
-// with one 16-byte load instead of VK gathered loads and takes one offset per
-// slice.  Every slice is whole (the planner takes this loader only when BK
-// divides K, and split-K chunks are whole slices): a load with a fallback
-// for a partial slice made the compiler copy the other operand's freshly
-// loaded registers at the join, waiting for those loads on every step.
+// Loader for a K-gathered operand whose every aligned run of 16 bytes along
+// K is contiguous in memory (the block-scatter layout's block strides,
+// Approach, "Supporting tensor computations"): each thread reads VK
+// consecutive k's of a row with one 16-byte load (at element alignment:
+// gfx950 global loads need no more) instead of VK gathered loads, and takes
+// one offset per slice.  Runs of any length of at least VK elements get that
+// form from the plan's padded contracted order (KRuns): element loads are
+// bound by the cache lines they touch per instruction (FP32 ladder v=93 o=27,
+// runs of 93 on both sides: 1095 us with element loads, 1002 with runs; bf16x6
+// ring o=31 v=115 722 -> 668 us).
+//
+// With whole slices and nothing to leave out (mode kVecK) a slice is stored
+// as it was loaded.  Otherwise (mode kRunK) the plan's void mask -- one bit
+// per entry of the contracted order, set for repeated entries and past the
+// end of K -- says which entries to store as 0, in both operands; a slice
+// without such entries takes the plain store.  The mask is applied to the
+// loaded registers just before the LDS store: a load with a fallback for a
+// partial slice made the compiler copy the other operand's freshly loaded
+// registers at the join, waiting for those loads on every step.
 template <typename T, typename OffT, int BR, int BK, int NSLOT = 1>
 struct VecKGather {
   static constexpr int VK = 16 / (int)sizeof(T);
@@ -296,6 +321,7 @@ struct VecKGather {
   static constexpr int NR = BR / RSTEP;        // runs per thread
   static_assert(BK % VK == 0 && kThreads % KT == 0 && BR % RSTEP == 0, "tile shape does not divide the workgroup");
   typedef T vec_t __attribute__((ext_vector_type(16 / sizeof(T))));
+  typedef T gvec_t __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
   OffT mn[NR];
   OffT ko[NSLOT];
   vec_t v[NSLOT][NR];
@@ -314,28 +340,52 @@ struct VecKGather {
   template <int S = 0>
   __device__ __forceinline__ void load(const T* __restrict__ base) {
 #pragma unroll
-    for (int i = 0; i < NR; ++i) v[S][i] = *global(reinterpret_cast<const vec_t*>(at(base, (OffT)(mn[i] + ko[S]))));
+    for (int i = 0; i < NR; ++i) v[S][i] = *global(reinterpret_cast<const gvec_t*>(at(base, (OffT)(mn[i] + ko[S]))));
   }
   template <int S = 0>
   __device__ __forceinline__ void store(T* __restrict__ lds, int /*k0*/, int /*kend*/) const {
 #pragma unroll
     for (int i = 0; i < NR; ++i) *reinterpret_cast<vec_t*>(lds + (r0 + i * RSTEP) * LDK + kk0) = v[S][i];
   }
+  template <int S = 0>
+  __device__ __forceinline__ void store_masked(T* __restrict__ lds, uint32_t voids) {
+    if (voids) clear<S>(voids);
+    store<S>(lds, 0, 0);
+  }
+  template <int S = 0>
+  __device__ __forceinline__ void clear(uint32_t voids) {
+#pragma unroll
+    for (int u = 0; u < VK; ++u) {
+      const bool out = (voids >> (kk0 + u)) & 1u;
+#pragma unroll
+      for (int i = 0; i < NR; ++i) v[S][i][u] = out ? T(0) : v[S][i][u];
+    }
+  }
 };
 
+// Void mask of the BK contracted entries from k0 (a multiple of BK), as a
+// wave-uniform value: bit k set where entry k0 + k does not count.
+template <int BK>
+__device__ __forceinline__ uint32_t void_bits(uint32_t word, int k0) {
+  static_assert(32 % BK == 0, "a slice lies in one word of the void mask");
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)word);
+  return BK == 32 ? w : (w >> (k0 & 31)) & ((1u << (BK % 32)) - 1u);
+}
+
 // Operand loaders by mode: 0 row-gathered, 1 K-gathered, 2 pre-packed,
-// 3 K-gathered from affine unit-stride blocks.
-enum { kRowGather = 0, kKGather = 1, kPacked = 2, kVecK = 3 };
+// 3 K-gathered in 16-byte runs, every slice whole, 4 the same under the
+// plan's void mask (its partner is then stored under the mask too).
+enum { kRowGather = 0, kKGather = 1, kPacked = 2, kVecK = 3, kRunK = 4 };
 template <int MODE>
 constexpr bool known_mode() {
-  static_assert(MODE >= kRowGather && MODE <= kVecK, "unknown loader mode");
+  static_assert(MODE >= kRowGather && MODE <= kRunK, "unknown loader mode");
   return true;
 }
 template <typename T, typename OffT, int BR, int BK, int MODE, int KV = 1, int NSLOT = 1,
           bool = known_mode<MODE>()>
 using Loader = typename std::conditional<
     MODE == kPacked, PackedGather<T, BR, BK, NSLOT>,
-    typename std::conditional<MODE == kVecK, VecKGather<T, OffT, BR, BK, NSLOT>,
+    typename std::conditional<MODE == kVecK || MODE == kRunK, VecKGather<T, OffT, BR, BK, NSLOT>,
                               TileGather<T, OffT, BR, BK, MODE == kKGather, KV, NSLOT>>::type>::type;
 
 }  // namespace famlies

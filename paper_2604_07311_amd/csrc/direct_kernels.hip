@@ -57,7 +57,7 @@ struct DirectOperand {
   typedef T vec_t __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
   typedef uint32_t off_t __attribute__((ext_vector_type(NK)));
   uint32_t mn[NBK];
-  off_t ko[D];  // byte offsets, each with its entry's skip count in the low two bits
+  off_t ko[D];
   T v[D][NBK][U];
 
   __device__ __forceinline__ void init(const uint32_t* __restrict__ rows, int row0) {
@@ -74,12 +74,12 @@ struct DirectOperand {
 #pragma unroll
     for (int i = 0; i < NBK; ++i) {
       if constexpr (VEC) {
-        const vec_t w = *reinterpret_cast<const __attribute__((address_space(1))) vec_t*>(global(at(base, mn[i] + (ko[S][0] & ~3u))));
+        const vec_t w = *reinterpret_cast<const __attribute__((address_space(1))) vec_t*>(global(at(base, mn[i] + ko[S][0])));
 #pragma unroll
         for (int u = 0; u < U; ++u) v[S][i][u] = w[u];
       } else {
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[S][i][u] = *global(at(base, mn[i] + (ko[S][u] & ~3u)));
+        for (int u = 0; u < U; ++u) v[S][i][u] = *global(at(base, mn[i] + ko[S][u]));
       }
     }
   }
@@ -128,19 +128,19 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
     const int k = kbeg + (wki + it * wk) * KS;
     return (k < klast ? k : klast) + g * U;
   };
-  uint32_t skip[D];  // entries of this lane's run that repeat earlier ones (alike in X and Y)
+  uint32_t vw[D];  // word of the void mask of this lane's run; its bits are picked at the step (not while loading)
   if (n > 0) {
-    auto load = [&](auto sc) {
+    auto load = [&](auto sc, int it) {
       constexpr int S = decltype(sc)::value;
+      vw[S] = *global(a.kvoid + (kof(it) >> 5));
       gx.template load<S>(X);
       gy.template load<S>(Y);
-      skip[S] = gx.ko[S][0] & 3u;
     };
     auto start = [&](auto sc) {
       constexpr int S = decltype(sc)::value;
       gx.template fetch<S>(a.xk, kof(S));
       gy.template fetch<S>(a.yk, kof(S));
-      load(sc);
+      load(sc, S);
     };
     auto ahead = [&](auto sc) {
       constexpr int S = decltype(sc)::value;
@@ -155,13 +155,13 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
     ahead(std::integral_constant<int, 2>{});
     auto step = [&](auto sc, int it) {
       constexpr int S = decltype(sc)::value;
-      if ((it == n - 1 && klast + KS > kend) || __builtin_amdgcn_ballot_w64(skip[S] != 0)) {
-        // entries past the end of K and repeated ones: zero in both operands
-        // (an Inf or NaN there must not reach the sum)
-        const int k0 = it == n - 1 ? klast + g * U : kbeg;
+      const uint32_t voids = (vw[S] >> (kof(it) & 31)) & ((1u << U) - 1u);
+      if (__builtin_amdgcn_ballot_w64(voids != 0)) {
+        // entries that do not count: zero in both operands (an Inf or NaN
+        // there must not reach the sum)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const bool in = k0 + u < kend && u >= (int)skip[S];
+          const bool in = !((voids >> u) & 1u);
 #pragma unroll
           for (int i = 0; i < MB; ++i) gx.v[S][i][u] = in ? gx.v[S][i][u] : T(0);
 #pragma unroll
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
         for (int i = 0; i < MB; ++i)
 #pragma unroll
           for (int j = 0; j < NB; ++j) acc[i][j] = MF::mma(gx.v[S][i][u], gy.v[S][j][u], acc[i][j]);
-      load(sc);
+      load(sc, it + D);
       gx.template fetch<S>(a.xk, kof(it + 2 * D));
       gy.template fetch<S>(a.yk, kof(it + 2 * D));
     };

@@ -70,18 +70,18 @@ void offsets(const std::vector<Mode>& modes, int which, int64_t n, int64_t n_pad
 // first contracted mode is padded to a multiple of u by letting its last
 // chunk of u start early (at ext - u), so every chunk is u distinct,
 // existing elements and a unit-stride operand reads it with one load.  The
-// chunk's first entries then repeat elements of the chunk before: `skip`
-// holds, per entry, how many entries from this one on (to the end of the
-// repeated ones) do not count, 0 for an entry that counts.  `index` is the
-// entry's place in the plain (column-major odometer) order.
+// chunk's first entries then repeat elements of the chunk before: `skip` is 1
+// for those entries, which do not count, and 0 for the others.  `index` is
+// the entry's place in the plain (column-major odometer) order.
 struct KRuns {
   std::vector<int64_t> index;
   std::vector<uint8_t> skip;
 };
-// Length of that order, or 0 where it does not pay: no operand has unit
-// stride along the first contracted mode, the mode is shorter than a chunk,
-// or the padding would add more than a quarter to K.  Equal to K when no run
-// needs padding.
+// Length of that order, or 0 where it does not pay: no operand gathered along
+// K has unit stride along the first contracted mode, the mode is shorter
+// than a chunk, or the padding would add more than a quarter to K (a kernel
+// with element loads on both sides runs at about 0.7 of the rate of one with
+// 16-byte runs).  Equal to K when no run needs padding.
 int64_t padded_k_length(const Analysis& an, int u);
 // The padded order (length padded_k_length(an, u), which must not be 0).
 void padded_k_runs(const Analysis& an, int u, KRuns* out);

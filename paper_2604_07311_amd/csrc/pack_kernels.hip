@@ -18,6 +18,7 @@ struct PackArgs {
   const OffT* mn;        // row offsets (padded to the tile grid)
   const OffT* ko;        // contracted offsets (padded)
   const int64_t* bl;     // batch offsets (elements)
+  const uint32_t* kvoid; // entries of the contracted order that do not count (packed as 0)
   void* dst;
   int32_t R, K, L, tiles, nkb;
 };
@@ -37,7 +38,7 @@ __global__ __launch_bounds__(kThreads) void pack_plain(PackArgs<OffT> p) {
     const int l = (int)(t / p.tiles);
     const int m = tile * BR + r, k = kb * BK + kin;
     T v = T(0);
-    if (m < p.R && k < p.K) v = *at(static_cast<const T*>(p.src) + p.bl[l], (OffT)(p.mn[m] + p.ko[k]));
+    if (m < p.R && !((p.kvoid[k >> 5] >> (k & 31)) & 1u)) v = *at(static_cast<const T*>(p.src) + p.bl[l], (OffT)(p.mn[m] + p.ko[k]));
     dst[e] = v;
   }
 }
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(kThreads) void pack_split(PackArgs<OffT> p) {
     const int l = (int)(blk / p.nkb / p.tiles);
     const int m = tile * BR + r, k = kb * BK + kin;
     float x = 0.f;
-    if (m < p.R && k < p.K) x = *at(static_cast<const float*>(p.src) + p.bl[l], (OffT)(p.mn[m] + p.ko[k]));
+    if (m < p.R && !((p.kvoid[k >> 5] >> (k & 31)) & 1u)) x = *at(static_cast<const float*>(p.src) + p.bl[l], (OffT)(p.mn[m] + p.ko[k]));
     __bf16* out = dst + blk * (int64_t)(NS * BR * BK) + r * BK + kin;
 #pragma unroll
     for (int q = 0; q < NS; ++q) {  // the same RNE split as the kernels' staging
@@ -136,7 +137,7 @@ famlies_status pack_geom(famlies_plan_s* p, int operand, PackGeom* g) {
   if (an.M == 0 || an.N == 0 || an.K == 0) return fail(FAMLIES_ERR_UNSUPPORTED, "pack: empty problem");
   g->rows = g->x ? an.M : an.N;
   g->tiles = (g->rows + g->br - 1) / g->br;
-  g->nkb = (an.K + g->bk - 1) / g->bk;
+  g->nkb = (p->kd + g->bk - 1) / g->bk;
   const size_t es = ns ? 2 * (size_t)ns : (size_t)an.esize;
   g->bytes = (size_t)an.L * (size_t)g->tiles * (size_t)g->nkb * (size_t)g->br * (size_t)g->bk * es;
   return FAMLIES_OK;
@@ -174,9 +175,10 @@ famlies_status pack_impl(famlies_plan_s* p, int operand, const void* src, void* 
   a.mn = o + p->off_pos[g.x ? 0 : 3];
   a.ko = o + p->off_pos[g.x ? 1 : 2];
   a.bl = lb + p->off_pos[g.x ? 6 : 7];
+  a.kvoid = o + p->kvoid_pos;
   a.dst = dst;
   a.R = (int32_t)g.rows;
-  a.K = (int32_t)an.K;
+  a.K = (int32_t)p->kd;
   a.L = (int32_t)an.L;
   a.tiles = (int32_t)g.tiles;
   a.nkb = (int32_t)g.nkb;

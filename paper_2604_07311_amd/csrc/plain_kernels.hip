@@ -33,11 +33,11 @@ __global__ __launch_bounds__(kThreads, FAMLIES_PLAIN_WAVES_PER_EU) void plain_co
   // with a row-gathered operand keep two slices in flight too (ring o=48
   // v=192 83.1 -> 85.5 %; ladder 87.0 -> 87.7 %).  With both operands
   // element-gathered along K the deeper pipeline was no faster.
-  static constexpr int kDepth =
-      ((sizeof(OffT) == 4 && (XM == kRowGather || YM == kRowGather)) ||
-       ((sizeof(OffT) == 4 || sizeof(T) == 4) && XM == kVecK && YM == kVecK))
-          ? 2
-          : 1;
+  static constexpr bool kBothRuns = (XM == kVecK || XM == kRunK) && (YM == kVecK || YM == kRunK);
+  static constexpr int kDepth = ((sizeof(OffT) == 4 && (XM == kRowGather || YM == kRowGather)) ||
+                                 ((sizeof(OffT) == 4 || sizeof(T) == 4) && kBothRuns))
+                                    ? 2
+                                    : 1;
   using Tile = PlainTile<T, BM, BN, BK, XM, YM, kDepth>;
   __shared__ T smem[Tile::SMEM];
   // Work units in launch order: without split-K, every tile of every batch
@@ -74,6 +74,7 @@ __global__ __launch_bounds__(kThreads, FAMLIES_PLAIN_WAVES_PER_EU) void plain_co
   j.ymn = a.ymn;
   j.cm = a.cm;
   j.cn = a.cn;
+  j.kvoid = a.kvoid;
   j.M = a.M;
   j.N = a.N;
   j.m0 = pm * BM;
@@ -134,35 +135,27 @@ static void launch_one(const PlainArgs<OffT>& a, int grid, hipStream_t s) {
   hipLaunchKernelGGL((plain_contract<T, OffT, BM, BN, BK, XM, YM>), dim3(grid), dim3(kThreads), 0, s, a);
 }
 
-// Gathered and affine-block operands (modes 0, 1, 3) with every offset form;
-// pre-packed operands (mode 2) with byte offsets only.
+// Gathered operands and whole 16-byte runs (modes 0, 1, 3) with every offset
+// form; pre-packed operands and masked runs (modes 2, 4) with byte offsets.
 template <typename T, typename OffT, int BM, int BN, int BK>
 static hipError_t launch_tile(const PlainArgs<OffT>& a, int xm, int ym, int grid, hipStream_t s) {
-  const int code = xm * 4 + ym;
-  switch (code) {
-    case 0: launch_one<T, OffT, BM, BN, BK, 0, 0>(a, grid, s); return hipGetLastError();
-    case 1: launch_one<T, OffT, BM, BN, BK, 0, 1>(a, grid, s); return hipGetLastError();
-    case 3: launch_one<T, OffT, BM, BN, BK, 0, 3>(a, grid, s); return hipGetLastError();
-    case 4: launch_one<T, OffT, BM, BN, BK, 1, 0>(a, grid, s); return hipGetLastError();
-    case 5: launch_one<T, OffT, BM, BN, BK, 1, 1>(a, grid, s); return hipGetLastError();
-    case 7: launch_one<T, OffT, BM, BN, BK, 1, 3>(a, grid, s); return hipGetLastError();
-    case 12: launch_one<T, OffT, BM, BN, BK, 3, 0>(a, grid, s); return hipGetLastError();
-    case 13: launch_one<T, OffT, BM, BN, BK, 3, 1>(a, grid, s); return hipGetLastError();
-    case 15: launch_one<T, OffT, BM, BN, BK, 3, 3>(a, grid, s); return hipGetLastError();
+#define FAMLIES_MODES(X, Y) \
+  case X * 8 + Y: launch_one<T, OffT, BM, BN, BK, X, Y>(a, grid, s); return hipGetLastError();
+  switch (xm * 8 + ym) {
+    FAMLIES_MODES(0, 0) FAMLIES_MODES(0, 1) FAMLIES_MODES(0, 3)
+    FAMLIES_MODES(1, 0) FAMLIES_MODES(1, 1) FAMLIES_MODES(1, 3)
+    FAMLIES_MODES(3, 0) FAMLIES_MODES(3, 1) FAMLIES_MODES(3, 3)
     default: break;
   }
   if constexpr (kByteOffsets<OffT>) {
-    switch (code) {
-      case 2: launch_one<T, OffT, BM, BN, BK, 0, 2>(a, grid, s); return hipGetLastError();
-      case 6: launch_one<T, OffT, BM, BN, BK, 1, 2>(a, grid, s); return hipGetLastError();
-      case 8: launch_one<T, OffT, BM, BN, BK, 2, 0>(a, grid, s); return hipGetLastError();
-      case 9: launch_one<T, OffT, BM, BN, BK, 2, 1>(a, grid, s); return hipGetLastError();
-      case 10: launch_one<T, OffT, BM, BN, BK, 2, 2>(a, grid, s); return hipGetLastError();
-      case 11: launch_one<T, OffT, BM, BN, BK, 2, 3>(a, grid, s); return hipGetLastError();
-      case 14: launch_one<T, OffT, BM, BN, BK, 3, 2>(a, grid, s); return hipGetLastError();
+    switch (xm * 8 + ym) {
+      FAMLIES_MODES(0, 2) FAMLIES_MODES(1, 2) FAMLIES_MODES(3, 2) FAMLIES_MODES(4, 2)
+      FAMLIES_MODES(2, 0) FAMLIES_MODES(2, 1) FAMLIES_MODES(2, 3) FAMLIES_MODES(2, 4) FAMLIES_MODES(2, 2)
+      FAMLIES_MODES(4, 0) FAMLIES_MODES(4, 1) FAMLIES_MODES(4, 4) FAMLIES_MODES(0, 4) FAMLIES_MODES(1, 4)
       default: break;
     }
   }
+#undef FAMLIES_MODES
   return hipErrorInvalidValue;
 }
 

@@ -137,7 +137,7 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
   if (t.split > 1) tiled += 4.0 + (double)(t.split + 1) * (double)split_tiles * t.bm * t.bn * es / 4.0e6;
 
   DirectCfg best = none;
-  double best_us = 0.95 * tiled;
+  double best_us = 0.88 * tiled;  // the estimates are good to about a tenth
   const int shapes[4][2] = {{16, 16}, {32, 32}, {16, 64}, {64, 16}};
   for (const auto& sh : shapes)
     for (int wk : {1, 4})
@@ -371,10 +371,13 @@ static famlies_status analyze_impl(int dtype, int compute, const famlies_tensor*
   }
   if (split_parts(an.compute)) t.bk = split_slice_k(split_parts(an.compute));
   int kchunk = 0, head = 0;
-  finalize_split(&t, an.K, ceil_div(an.M, t.bm) * ceil_div(an.N, t.bn), &kchunk, &head);
   int ib = 64;
   bool e32 = false;
   index_form(an, 0, &ib, &e32);
+  const int64_t runs =  // as in make_plan: the padded contracted order
+      int8_slices(an.compute) || ib != 32 || e32 ? 0 : padded_k_length(an, 16 / an.esize);
+  finalize_split(&t, runs && runs <= kMaxGemmDim ? runs : an.K, ceil_div(an.M, t.bm) * ceil_div(an.N, t.bn), &kchunk,
+                 &head);
   std::vector<int64_t> v[9];
   bool xv = false, yv = false;
   if (an.M > 0 && an.N > 0) {

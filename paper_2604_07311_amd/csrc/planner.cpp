@@ -388,7 +388,8 @@ void offsets(const std::vector<Mode>& modes, int which, int64_t n, int64_t n_pad
 int64_t padded_k_length(const Analysis& an, int u) {
   if (an.P.empty() || an.K == 0 || an.P[0].blk > 0) return 0;
   const Mode& m = an.P[0];
-  if ((m.sx != 1 && m.sy != 1) || m.ext < u) return 0;
+  if (!(an.x_kfast && m.sx == 1) && !(an.y_kfast && m.sy == 1)) return 0;
+  if (m.ext < u) return 0;
   const int64_t run = (m.ext + u - 1) / u * u;
   if (4 * run > 5 * m.ext) return 0;
   return an.K / m.ext * run;
@@ -403,7 +404,7 @@ void padded_k_runs(const Analysis& an, int u, KRuns* out) {
       const int64_t start = std::min(c, e - u);
       for (int64_t j = 0; j < u; ++j) {
         out->index.push_back(r * e + start + j);
-        out->skip.push_back((uint8_t)std::max<int64_t>(0, c - start - j));
+        out->skip.push_back((uint8_t)(start + j < c));
       }
     }
 }

@@ -65,11 +65,11 @@ struct famlies_plan_s {
   // X / Y are K-gathered from affine unit-stride K blocks with 16-byte
   // aligned run starts (given a 16-byte aligned base pointer)
   bool x_vec = false, y_vec = false;
+  int64_t kd = 0;          // K of the kernels' contracted order (padded to 16-byte runs, or the plain one)
+  int xmode = 0, ymode = 0;  // loader modes of X and Y when they are not pre-packed
+  size_t kvoid_pos = 0;    // void mask of the contracted order (byte-offset plans of the plain and bf16 kernels)
   famlies::DirectCfg direct;                // bm > 0: native kMain launches run the direct kernel
-  bool dx_vec = false, dy_vec = false;      // direct kernel: X / Y read 16 bytes along K per load
-  int64_t direct_k = 0;                     // direct kernel: K of its contracted order (KRuns where they pay)
-  size_t dk_pos[2] = {0, 0};                // direct kernel: contracted offsets of X, Y
-  bool pk_vec[2] = {false, false};          // the same for a pre-packed X / Y
+  bool dx_vec = false, dy_vec = false;      // every run of 16 bytes of X / Y along K is contiguous
   bool pk_fits[2] = {false, false};         // direct kernel: 32-bit offsets reach all of the pre-packed X / Y
   size_t pk_pos[4] = {0, 0, 0, 0};          // direct kernel, pre-packed operands: X rows, X k, Y rows, Y k
   bool table_hit = false;  // the tile came from the handle's tile table

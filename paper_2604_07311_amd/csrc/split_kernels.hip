@@ -124,6 +124,11 @@ struct SplitLoader {
   template <int S = 0>
   __device__ __forceinline__ void load(const void* base) { g.template load<S>(static_cast<const float*>(base)); }
   template <int S = 0>
+  __device__ __forceinline__ void store_masked(__bf16* tiles, int tile_elems, uint32_t voids) {
+    if (voids) g.template clear<S>(voids);
+    store_split<NS, G, KF, false, S>(g, tiles, tile_elems, 0, 0);
+  }
+  template <int S = 0>
   __device__ __forceinline__ void store(__bf16* tiles, int tile_elems, int k0, int kend) const {
     if (k0 + kSplitBK<NS> <= kend)
       store_split<NS, G, KF, false, S>(g, tiles, tile_elems, k0, kend);
@@ -148,8 +153,8 @@ __device__ __forceinline__ void store_split4(float x0, float x1, float x2, float
   }
 }
 
-// K-gathered from affine unit-stride K blocks: 16-byte loads of four k's
-// (every slice whole: the planner takes this loader only when BK divides K).
+// K-gathered in 16-byte runs: loads of four k's (kVecK: every slice whole;
+// kRunK: stored under the void mask).
 template <typename OffT, int BR, int NS, int NSLOT>
 struct SplitLoader<OffT, BR, NS, kVecK, NSLOT> {
   using G = VecKGather<float, OffT, BR, kSplitBK<NS>, NSLOT>;
@@ -168,7 +173,14 @@ struct SplitLoader<OffT, BR, NS, kVecK, NSLOT> {
       store_split4<NS>(v[0], v[1], v[2], v[3], tiles, tile_elems, (g.r0 + i * G::RSTEP) * kSplitLD<NS> + g.kk0);
     }
   }
+  template <int S = 0>
+  __device__ __forceinline__ void store_masked(__bf16* tiles, int tile_elems, uint32_t voids) {
+    if (voids) g.template clear<S>(voids);
+    store<S>(tiles, tile_elems, 0, 0);
+  }
 };
+template <typename OffT, int BR, int NS, int NSLOT>
+struct SplitLoader<OffT, BR, NS, kRunK, NSLOT> : SplitLoader<OffT, BR, NS, kVecK, NSLOT> {};
 
 template <typename OffT, int BR, int NS, int NSLOT>
 struct SplitLoader<OffT, BR, NS, kPacked, NSLOT> {
@@ -204,6 +216,10 @@ struct SplitLoader<OffT, BR, NS, kPacked, NSLOT> {
         const int e = (tid + q * kThreads) * 8;
         *reinterpret_cast<u32x4*>(tiles + t * tile_elems + (e / BK) * kSplitLD<NS> + e % BK) = v[S][t][q];
       }
+  }
+  template <int S = 0>
+  __device__ __forceinline__ void store_masked(__bf16* tiles, int tile_elems, uint32_t /*voids: packed as 0*/) const {
+    store<S>(tiles, tile_elems, 0, 0);
   }
 };
 
@@ -294,11 +310,25 @@ __global__ __launch_bounds__(kThreads, (kSplitWgPerCu<OffT, BM, NS, XM, YM>)) vo
       for (int j = 0; j < NB; ++j) acc[o][i][j] = f32x16{};
 
   const int g = lane / 32, r = lane % 32;
+  constexpr bool kMasked = XM == kRunK || YM == kRunK;
+  uint32_t vw[DEPTH] = {};  // word of the void mask of the slice in each register slot
+  auto stage_load = [&](auto sc, int k0) {
+    constexpr int S = decltype(sc)::value;
+    if constexpr (kMasked) vw[S] = *global(a.kvoid + (k0 >> 5));
+    gx.template load<S>(X);
+    gy.template load<S>(Y);
+  };
   auto stage_store = [&](auto sc, int buf, int k0) {
     constexpr int S = decltype(sc)::value;
     __bf16* base = smem + buf * STAGE;
-    gx.template store<S>(base, XS, k0, kend);
-    gy.template store<S>(base + NS * XS, YS, k0, kend);
+    if constexpr (kMasked) {
+      const uint32_t voids = void_bits<BK>(vw[S], k0);
+      gx.template store_masked<S>(base, XS, voids);
+      gy.template store_masked<S>(base + NS * XS, YS, voids);
+    } else {
+      gx.template store<S>(base, XS, k0, kend);
+      gy.template store<S>(base + NS * XS, YS, k0, kend);
+    }
   };
   auto multiply = [&](int cur) {
     const __bf16* xs = smem + cur * STAGE;
@@ -332,8 +362,7 @@ __global__ __launch_bounds__(kThreads, (kSplitWgPerCu<OffT, BM, NS, XM, YM>)) vo
     if constexpr (DEPTH == 1) {
       gx.fetch_k(a.xk, kbeg);
       gy.fetch_k(a.yk, kbeg);
-      gx.load(X);
-      gy.load(Y);
+      stage_load(slot0, kbeg);
       if (nk > 1) {
         gx.fetch_k(a.xk, kbeg + BK);
         gy.fetch_k(a.yk, kbeg + BK);
@@ -344,8 +373,7 @@ __global__ __launch_bounds__(kThreads, (kSplitWgPerCu<OffT, BM, NS, XM, YM>)) vo
         const int cur = it & 1;
         const bool more = it + 1 < nk;
         if (more) {
-          gx.load(X);
-          gy.load(Y);
+          stage_load(slot0, kbeg + (it + 1) * BK);
           if (it + 2 < nk) {
             gx.fetch_k(a.xk, kbeg + (it + 2) * BK);
             gy.fetch_k(a.yk, kbeg + (it + 2) * BK);
@@ -364,20 +392,17 @@ __global__ __launch_bounds__(kThreads, (kSplitWgPerCu<OffT, BM, NS, XM, YM>)) vo
       auto kc = [&](int k0) { return k0 < klast ? k0 : klast; };
       gx.template fetch_k<0>(a.xk, kbeg);
       gy.template fetch_k<0>(a.yk, kbeg);
-      gx.template load<0>(X);
-      gy.template load<0>(Y);
+      stage_load(slot0, kbeg);
       gx.template fetch_k<1>(a.xk, kc(kbeg + BK));
       gy.template fetch_k<1>(a.yk, kc(kbeg + BK));
-      gx.template load<1>(X);
-      gy.template load<1>(Y);
+      stage_load(std::integral_constant<int, 1>{}, kc(kbeg + BK));
       gx.template fetch_k<0>(a.xk, kc(kbeg + 2 * BK));
       gy.template fetch_k<0>(a.yk, kc(kbeg + 2 * BK));
       stage_store(slot0, 0, kbeg);
       __syncthreads();
       auto step = [&](auto sc, int it) {
         constexpr int S = decltype(sc)::value;
-        gx.template load<S>(X);
-        gy.template load<S>(Y);
+        stage_load(sc, kc(kbeg + (it + 2) * BK));
         gx.template fetch_k<S ^ 1>(a.xk, kc(kbeg + (it + 3) * BK));
         gy.template fetch_k<S ^ 1>(a.yk, kc(kbeg + (it + 3) * BK));
         multiply(S);
@@ -474,35 +499,27 @@ static void launch_split_one(const PlainArgs<OffT>& a, int grid, hipStream_t s) 
   hipLaunchKernelGGL((split_contract<OffT, BM, BN, XM, YM, NS>), dim3(grid), dim3(kThreads), 0, s, a);
 }
 
-// Gathered and affine-block operands with every offset form; pre-packed
-// operands with byte offsets only.
+// Gathered operands and whole 16-byte runs with every offset form;
+// pre-packed operands and masked runs with byte offsets only.
 template <typename OffT, int BM, int BN, int NS>
 static hipError_t launch_split_tile(const PlainArgs<OffT>& a, int xm, int ym, int grid, hipStream_t s) {
-  const int code = xm * 4 + ym;
-  switch (code) {
-    case 0: launch_split_one<OffT, BM, BN, NS, 0, 0>(a, grid, s); return hipGetLastError();
-    case 1: launch_split_one<OffT, BM, BN, NS, 0, 1>(a, grid, s); return hipGetLastError();
-    case 3: launch_split_one<OffT, BM, BN, NS, 0, 3>(a, grid, s); return hipGetLastError();
-    case 4: launch_split_one<OffT, BM, BN, NS, 1, 0>(a, grid, s); return hipGetLastError();
-    case 5: launch_split_one<OffT, BM, BN, NS, 1, 1>(a, grid, s); return hipGetLastError();
-    case 7: launch_split_one<OffT, BM, BN, NS, 1, 3>(a, grid, s); return hipGetLastError();
-    case 12: launch_split_one<OffT, BM, BN, NS, 3, 0>(a, grid, s); return hipGetLastError();
-    case 13: launch_split_one<OffT, BM, BN, NS, 3, 1>(a, grid, s); return hipGetLastError();
-    case 15: launch_split_one<OffT, BM, BN, NS, 3, 3>(a, grid, s); return hipGetLastError();
+#define FAMLIES_MODES(X, Y) \
+  case X * 8 + Y: launch_split_one<OffT, BM, BN, NS, X, Y>(a, grid, s); return hipGetLastError();
+  switch (xm * 8 + ym) {
+    FAMLIES_MODES(0, 0) FAMLIES_MODES(0, 1) FAMLIES_MODES(0, 3)
+    FAMLIES_MODES(1, 0) FAMLIES_MODES(1, 1) FAMLIES_MODES(1, 3)
+    FAMLIES_MODES(3, 0) FAMLIES_MODES(3, 1) FAMLIES_MODES(3, 3)
     default: break;
   }
   if constexpr (kByteOffsets<OffT>) {
-    switch (code) {
-      case 2: launch_split_one<OffT, BM, BN, NS, 0, 2>(a, grid, s); return hipGetLastError();
-      case 6: launch_split_one<OffT, BM, BN, NS, 1, 2>(a, grid, s); return hipGetLastError();
-      case 8: launch_split_one<OffT, BM, BN, NS, 2, 0>(a, grid, s); return hipGetLastError();
-      case 9: launch_split_one<OffT, BM, BN, NS, 2, 1>(a, grid, s); return hipGetLastError();
-      case 10: launch_split_one<OffT, BM, BN, NS, 2, 2>(a, grid, s); return hipGetLastError();
-      case 11: launch_split_one<OffT, BM, BN, NS, 2, 3>(a, grid, s); return hipGetLastError();
-      case 14: launch_split_one<OffT, BM, BN, NS, 3, 2>(a, grid, s); return hipGetLastError();
+    switch (xm * 8 + ym) {
+      FAMLIES_MODES(0, 2) FAMLIES_MODES(1, 2) FAMLIES_MODES(3, 2) FAMLIES_MODES(4, 2)
+      FAMLIES_MODES(2, 0) FAMLIES_MODES(2, 1) FAMLIES_MODES(2, 3) FAMLIES_MODES(2, 4) FAMLIES_MODES(2, 2)
+      FAMLIES_MODES(4, 0) FAMLIES_MODES(4, 1) FAMLIES_MODES(4, 4) FAMLIES_MODES(0, 4) FAMLIES_MODES(1, 4)
       default: break;
     }
   }
+#undef FAMLIES_MODES
   return hipErrorInvalidValue;
 }
 

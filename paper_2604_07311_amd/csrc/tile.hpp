@@ -23,6 +23,7 @@ struct TileJob {
   const OffT* ymn;
   const OffT* cm;
   const OffT* cn;
+  const uint32_t* kvoid;  // void mask of the contracted order (loader mode kRunK)
   int M, N;
   int m0, n0, kbeg, kend;
   double alpha, beta;
@@ -31,7 +32,7 @@ struct TileJob {
   int x_nkb, y_nkb;  // k-blocks per tile row of a pre-packed X / Y
 };
 
-// XM, YM: operand loader modes (kRowGather, kKGather, kPacked, kVecK).  DEPTH: K
+// XM, YM: operand loader modes (kRowGather, kKGather, kPacked, kVecK, kRunK).  DEPTH: K
 // slices whose data loads are in flight while a slice is multiplied (1: the
 // next slice; 2: the next two, for latency-bound gathers when registers
 // allow).
@@ -49,6 +50,7 @@ struct PlainTile {
   static constexpr int WTM = BM / 2, WTN = BN / 2;
   static constexpr int MB = WTM / MF::BS, NB = WTN / MF::BS;
   static constexpr int KPG = BK / MF::KG;
+  static constexpr bool kMasked = XM == kRunK || YM == kRunK;
   static_assert(MB >= 1 && NB >= 1 && BK % MF::KG == 0, "bad tile");
   static_assert(DEPTH == 1 || DEPTH == 2, "pipeline depth 1 or 2");
 
@@ -93,26 +95,43 @@ struct PlainTile {
       for (int jj = 0; jj < NB; ++jj) acc[i][jj] = typename MF::Acc{};
 
     const int g = lane / MF::BS, r = lane % MF::BS;
+    // word of the void mask of the slice in each register slot
+    uint32_t vw[DEPTH] = {};
+    auto load = [&](auto sc, int k0) {
+      constexpr int S = decltype(sc)::value;
+      if constexpr (kMasked) vw[S] = *global(j.kvoid + (k0 >> 5));
+      gx.template load<S>(X);
+      gy.template load<S>(Y);
+    };
+    auto store = [&](auto sc, T* buf, int k0) {
+      constexpr int S = decltype(sc)::value;
+      if constexpr (kMasked) {
+        const uint32_t voids = void_bits<BK>(vw[S], k0);
+        gx.template store_masked<S>(buf, voids);
+        gy.template store_masked<S>(buf + XS, voids);
+      } else {
+        gx.template store<S>(buf, k0, j.kend);
+        gy.template store<S>(buf + XS, k0, j.kend);
+      }
+    };
+    constexpr auto slot0 = std::integral_constant<int, 0>{};
     if constexpr (DEPTH == 1) {
       if (nk > 0) {
         // pipeline: offsets two slices ahead, data one slice ahead, LDS double buffer
         gx.fetch_k(j.xk, j.kbeg);
         gy.fetch_k(j.yk, j.kbeg);
-        gx.load(X);
-        gy.load(Y);
+        load(slot0, j.kbeg);
         if (nk > 1) {
           gx.fetch_k(j.xk, j.kbeg + BK);
           gy.fetch_k(j.yk, j.kbeg + BK);
         }
-        gx.store(smem, j.kbeg, j.kend);
-        gy.store(smem + XS, j.kbeg, j.kend);
+        store(slot0, smem, j.kbeg);
         __syncthreads();
         for (int it = 0; it < nk; ++it) {
           const int cur = it & 1;
           const bool more = it + 1 < nk;
           if (more) {
-            gx.load(X);
-            gy.load(Y);
+            load(slot0, j.kbeg + (it + 1) * BK);
             if (it + 2 < nk) {
               gx.fetch_k(j.xk, j.kbeg + (it + 2) * BK);
               gy.fetch_k(j.yk, j.kbeg + (it + 2) * BK);
@@ -120,10 +139,7 @@ struct PlainTile {
           }
           multiply(smem + cur * (XS + YS), wm, wn, g, r, acc);
           if (more) {
-            T* nx = smem + (cur ^ 1) * (XS + YS);
-            const int kn = j.kbeg + (it + 1) * BK;
-            gx.store(nx, kn, j.kend);
-            gy.store(nx + XS, kn, j.kend);
+            store(slot0, smem + (cur ^ 1) * (XS + YS), j.kbeg + (it + 1) * BK);
           }
           __syncthreads();
         }
@@ -139,31 +155,24 @@ struct PlainTile {
       auto kc = [&](int k0) { return k0 < klast ? k0 : klast; };
       gx.template fetch_k<0>(j.xk, j.kbeg);
       gy.template fetch_k<0>(j.yk, j.kbeg);
-      gx.template load<0>(X);
-      gy.template load<0>(Y);
+      load(slot0, j.kbeg);
       gx.template fetch_k<1>(j.xk, kc(j.kbeg + BK));
       gy.template fetch_k<1>(j.yk, kc(j.kbeg + BK));
-      gx.template load<1>(X);
-      gy.template load<1>(Y);
+      load(std::integral_constant<int, 1>{}, kc(j.kbeg + BK));
       gx.template fetch_k<0>(j.xk, kc(j.kbeg + 2 * BK));
       gy.template fetch_k<0>(j.yk, kc(j.kbeg + 2 * BK));
-      gx.template store<0>(smem, j.kbeg, j.kend);
-      gy.template store<0>(smem + XS, j.kbeg, j.kend);
+      store(slot0, smem, j.kbeg);
       __syncthreads();
       // Step for slice `it` held in LDS buffer S (it % 2 == S): slot S is free
       // and holds the offsets of slice it + 2; slot S^1 holds slice it + 1.
       auto step = [&](auto sc, int it) {
         constexpr int S = decltype(sc)::value;
-        gx.template load<S>(X);
-        gy.template load<S>(Y);
+        load(sc, kc(j.kbeg + (it + 2) * BK));
         gx.template fetch_k<S ^ 1>(j.xk, kc(j.kbeg + (it + 3) * BK));
         gy.template fetch_k<S ^ 1>(j.yk, kc(j.kbeg + (it + 3) * BK));
         multiply(smem + S * (XS + YS), wm, wn, g, r, acc);
         if (it + 1 < nk) {
-          T* nx = smem + (S ^ 1) * (XS + YS);
-          const int kn = j.kbeg + (it + 1) * BK;
-          gx.template store<S ^ 1>(nx, kn, j.kend);
-          gy.template store<S ^ 1>(nx + XS, kn, j.kend);
+          store(std::integral_constant<int, S ^ 1>{}, smem + (S ^ 1) * (XS + YS), j.kbeg + (it + 1) * BK);
         }
         __syncthreads();
       };
