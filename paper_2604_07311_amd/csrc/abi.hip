@@ -138,7 +138,9 @@ static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int
       packed_vectors(rows, p->kd, kp, br, p->cfg.bk, es, packed[2 * op].data(), packed[2 * op + 1].data());
       p->pk_fits[op] = rows * ceil_div(p->kd, p->cfg.bk) * p->cfg.bk * es < ((int64_t)1 << 32);
     }
-  const int64_t shift[6] = {an.x_lo, 0, 0, an.y_lo, an.c_lo_mn, 0};
+  // rows and contracted offsets are rebased each by its own lowest, so every
+  // entry of the byte form counts up from the operand's lowest element
+  const int64_t shift[6] = {an.x_lo - an.xk_lo, an.xk_lo, an.yk_lo, an.y_lo - an.yk_lo, an.c_lo_mn, 0};
   size_t n6 = kvoid.size();
   for (int i = 0; i < 6; ++i) n6 += v[i].size();
   for (const auto& x : packed) n6 += x.size();
@@ -207,6 +209,14 @@ static PlainArgs<OffT> make_args(const famlies_plan_s* p, const void* x, const v
   a.splits = p->cfg.split;
   a.kchunk = p->kchunk;
   a.head = p->head;
+  a.rem = p->level.rem;
+  if (a.rem) {
+    a.splits = 1;
+    a.head = p->level.head;
+    a.lev_q = p->level.q;
+    a.lev_part = p->level.part;
+    a.lev_parts = p->level.parts;
+  }
   a.alpha = alpha;
   a.beta = beta;
   a.work = p->d_work;
@@ -277,9 +287,20 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   finalize_split(&p->cfg, p->kd, ntiles, &p->kchunk, &p->head);
   if (ntiles * p->cfg.split * an.L >= ((int64_t)1 << 31))
     return fail(FAMLIES_ERR_UNSUPPORTED, "the tile grid exceeds 2^31 workgroups");
+  double level_us = 1e30;
+  if (!lean && !force && !p->table_hit && !i8) {
+    bool unsplit = false;
+    p->level = choose_level(h, an, p->cfg, p->kd, &unsplit, &level_us);
+    if (unsplit) {
+      p->cfg.split = 1;
+      p->cfg.tail = 0;
+      finalize_split(&p->cfg, p->kd, ntiles, &p->kchunk, &p->head);
+    }
+  }
   if (!lean && !force && !p->table_hit && !i8 && !ns && p->index_bits == 32 && !p->elem32) {
-    p->direct = choose_direct(h, an, p->cfg);
+    p->direct = choose_direct(h, an, p->cfg, level_us);
     if (p->direct.bm) {
+      p->level = LevelCfg();
       const int ks = 64 / an.esize;
       DirectCfg& d = p->direct;
       if (an.L > 1) d.split = 1;
@@ -300,12 +321,13 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   if (i8 && an.K > 0) {
     p->work_bytes = int8_work_bytes(i8, an.M, an.N, an.K, an.L);  // digit planes and exponents
   } else if (p->cfg.split > 1 && an.K > 0) {
-    // plain kernels: one BM x BN block per split tile and K slice; bf16
-    // kernels: one padded M x N plane of FP64 sums per K slice
+    // one BM x BN block per split tile and K slice (of FP64 sums in the bf16 kernels)
     p->work_bytes = ns ? (size_t)p->cfg.split * (size_t)mp * (size_t)np * 8
                        : (size_t)p->cfg.split * (size_t)(ntiles - p->head) * (size_t)p->cfg.bm *
                              (size_t)p->cfg.bn * (size_t)an.esize;
   }
+  if (p->level.rem)
+    p->work_bytes = std::max(p->work_bytes, (size_t)p->level.blocks() * 128 * 128 * (ns ? 8 : (size_t)an.esize));
   if (p->direct.bm && p->direct.split > 1)
     p->work_bytes = std::max(p->work_bytes, (size_t)p->direct.split * (size_t)ceil_div(an.M, p->direct.bm) *
                                                 (size_t)ceil_div(an.N, p->direct.bn) *
@@ -349,7 +371,7 @@ famlies_status make_plan(famlies_handle h, famlies_plan* out, int dtype, int com
 }
 
 void log_plan(const famlies_plan_s* p) {
-  log_decision("plan", p->an, p->cfg, p->direct, p->elem32 ? -32 : p->index_bits, p->x_vec, p->y_vec, p->work_bytes,
+  log_decision("plan", p->an, p->cfg, p->direct, p->level, p->elem32 ? -32 : p->index_bits, p->x_vec, p->y_vec, p->work_bytes,
                p->table_hit);
 }
 
@@ -565,7 +587,7 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
       a.kchunk = d.kchunk;
       a.head = 0;
       e = launch_direct(an.dtype, a, d, xp || p->dx_vec, yp || p->dy_vec, xplane, yplane, s);
-      if (e == hipSuccess && d.split > 1) e = launch_splitk_reduce(an.dtype, a, d.bm, d.bn, s);
+      if (e == hipSuccess && d.split > 1) e = launch_splitk_reduce(an.dtype, false, a, d.bm, d.bn, s);
     } else {
       e = launch_plain(an.dtype, a, L, s);
     }

@@ -29,9 +29,13 @@ struct PlainArgs {
   // splits > 1: tiles [0, head) run whole first; tiles [head, tiles_m*tiles_n)
   // run as `splits` K slices each, writing partial sums to `work`
   int32_t head;
+  // rem > 0: levelled last round (LevelCfg): tiles [0, head) of all batch
+  // planes run whole, the other rem their first lev_q slices in one
+  // workgroup each and the rest in lev_parts workgroups of lev_part slices
+  int32_t rem, lev_q, lev_part, lev_parts;
   double alpha, beta;
-  void* work;       // split-K partials [splits][tile - head][BM*BN] (plain kernels; the bf16
-                    // kernels use [splits][tiles_m*BM][tiles_n*BN] with head = 0)
+  void* work;       // split-K partials [splits][tile - head][BM*BN] (FP64 in the bf16 kernels, whose
+                    // head is 0), or a levelled round's blocks
 };
 
 }  // namespace famlies

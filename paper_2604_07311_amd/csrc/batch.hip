@@ -288,7 +288,7 @@ famlies_status batch_plan_make(famlies_handle_s* h, famlies_plan_s** out, int dt
     const int which[6] = {0, 0, 1, 1, 2, 2};
     const int64_t len[6] = {an.M, an.K, an.K, an.N, an.M, an.N};
     const int64_t padded[6] = {mp, kp, kp, np, mp, np};
-    const int64_t shift[6] = {an.x_lo, 0, 0, an.y_lo, an.c_lo_mn, 0};
+    const int64_t shift[6] = {an.x_lo - an.xk_lo, an.xk_lo, an.yk_lo, an.y_lo - an.yk_lo, an.c_lo_mn, 0};
     std::vector<int64_t> vecs[6];
     for (int v = 0; v < 6; ++v) {
       d.pos[v] = (int32_t)(pool.size() - d.off);

@@ -33,6 +33,39 @@ __device__ __forceinline__ int xcd_remap(int bid, int total) {
   return xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
 }
 
+// A wave-uniform value in a scalar register (integer division leaves its
+// result in a vector register).
+__device__ __forceinline__ int scalar(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// What workgroup b of a levelled launch runs (args.hpp): the tile (over all
+// batch planes), its slices [s0, s1) of nk and the block of partial sums they
+// go to (-1: a whole tile, written to C).  Runs of one number are
+// neighbours, so the tiles of a moment read the same K range.
+struct LevelWork {
+  int tile, s0, s1, block;
+  template <typename Args>
+  __device__ __forceinline__ LevelWork(const Args& a, int b, int nk) {
+    if (b < a.head) {
+      tile = xcd_remap(b, a.head);
+      s0 = 0;
+      s1 = nk;
+      block = -1;
+    } else if (b < a.head + a.rem) {
+      block = xcd_remap(b - a.head, a.rem);
+      tile = a.head + block;
+      s0 = 0;
+      s1 = a.lev_q;
+    } else {
+      const int v = xcd_remap(b - a.head - a.rem, a.rem * a.lev_parts);
+      const int run = v / a.rem, i = v % a.rem;
+      tile = a.head + i;
+      s0 = a.lev_q + run * a.lev_part;
+      s1 = min(nk, s0 + a.lev_part);
+      block = a.rem + i * a.lev_parts + run;
+    }
+  }
+};
+
 // Element at `off` from `base`: uint32_t offsets count bytes (an SGPR base
 // plus a 32-bit VGPR offset per load); int32_t and int64_t offsets count
 // elements (int32_t for operands past 4 GiB but under 2^31 elements: 32-bit
@@ -123,7 +156,7 @@ struct Mfma<float> {  // v_mfma_f32_32x32x2_f32
 // (row j / KV, k j % KV) in the KFAST case and (row 0, k j) otherwise.
 // NSLOT > 1 keeps that many slices in flight: each phase takes the slot it
 // works on as a template argument.
-template <typename T, typename OffT, int BR, int BK, bool KFAST, int KV = 1, int NSLOT = 1>
+template <typename T, typename OffT, int BR, int BK, bool KFAST, int KV = 1, int NSLOT = 1, bool SCALARK = false>
 struct TileGather {
   static constexpr int E = BR * BK / kThreads;
   static constexpr int KVT = KV;                  // KFAST: consecutive k's per thread
@@ -137,8 +170,18 @@ struct TileGather {
                       : (kThreads % BR == 0 && BK % KPH == 0 && E % VK == 0),
                 "tile shape does not divide the workgroup");
 
+  // SCALARK, row-fast with byte offsets: the run's contracted offsets are the
+  // same for the whole wave.  They are fetched with one load, entry j in lane
+  // j, and read back into scalar registers, so each data load is a scalar
+  // address plus the row's 32-bit offset: one register per slot instead of E.
+  // Taken where registers are short: the bf16x3 kernel with one row-gathered
+  // operand no longer spills (7 and, under the void mask, 37 registers; ring
+  // o=48 v=192 5.51 -> 5.40 ms); in the FP32 kernels, which have them, the
+  // address work per load costs more (autograd step 2.33 against 2.42 ms).
+  static constexpr bool SK = SCALARK && !KFAST && kByteOffsets<OffT> && E <= 64;
+
   OffT mn[KFAST ? E / KV : 1];  // row offsets, fixed for the tile
-  OffT ko[NSLOT][KFAST ? KV : E];  // contracted-index offsets of a slice to load
+  OffT ko[NSLOT][KFAST ? KV : SK ? 1 : E];  // contracted-index offsets of a slice to load
   T v[NSLOT][E];
   int r0, kk0;  // first row; first k of the thread's run
 
@@ -154,7 +197,7 @@ struct TileGather {
       // with vector loads on purpose: scalar loads share the LDS wait
       // counter, and every wait for an MFMA operand read would then also wait
       // for the offsets of a slice two steps ahead.
-      kk0 = (tid / BR) * E;
+      kk0 = SK ? scalar((tid / BR) * E) : (tid / BR) * E;
       mn[0] = mnoff[tile_r0 + r0];
     }
   }
@@ -165,7 +208,9 @@ struct TileGather {
   static constexpr int OV = 16 / (int)sizeof(OffT);
   template <int S = 0>
   __device__ __forceinline__ void fetch_k(const OffT* __restrict__ koff, int k0) {
-    if constexpr (!KFAST && E % OV == 0) {
+    if constexpr (SK) {
+      ko[S][0] = koff[k0 + kk0 + threadIdx.x % E];
+    } else if constexpr (!KFAST && E % OV == 0) {
       typedef OffT ovec_t __attribute__((ext_vector_type(16 / sizeof(OffT))));
       const ovec_t* src = reinterpret_cast<const ovec_t*>(koff + k0 + kk0);
 #pragma unroll
@@ -182,9 +227,17 @@ struct TileGather {
 
   template <int S = 0>
   __device__ __forceinline__ void load(const T* __restrict__ base) {
+    if constexpr (SK) {
+#pragma unroll
+      for (int j = 0; j < E; ++j) {
+        const uint32_t so = (uint32_t)__builtin_amdgcn_readlane((int)ko[S][0], j);
+        v[S][j] = gload(at(base, so), mn[0]);
+      }
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < E; ++j)
-      v[S][j] = KFAST ? gload(base, (OffT)(mn[j / KV] + ko[S][j % KV])) : gload(base, (OffT)(mn[0] + ko[S][j]));
+      v[S][j] = KFAST ? gload(base, (OffT)(mn[j / KV] + ko[S][j % KV])) : gload(base, (OffT)(mn[0] + ko[S][SK ? 0 : j]));
   }
 
   __device__ __forceinline__ int krel(int j) const { return kk0 + (KFAST ? j % KV : j); }
@@ -235,13 +288,15 @@ struct TileGather {
   // count and is stored as 0).
   template <int S = 0>
   __device__ __forceinline__ void store_masked(T* __restrict__ lds, uint32_t voids) {
-    if (voids) clear<S>(voids);
     store_impl<false, S>(lds, 0, 0);
+    if (voids)
+      zero(voids, [&](int r, int k) { lds[r * LDK + k] = T(0); });
   }
-  template <int S = 0>
-  __device__ __forceinline__ void clear(uint32_t voids) {
-#pragma unroll
-    for (int j = 0; j < E; ++j) v[S][j] = (voids >> krel(j)) & 1u ? T(0) : v[S][j];
+  // f(row, k) for this thread's elements at the slice's void k's
+  template <typename F>
+  __device__ __forceinline__ void zero(uint32_t voids, F f) const {
+    for (int j = 0; j < E; ++j)
+      if ((voids >> krel(j)) & 1u) f(KFAST ? r0 + (j / KV) * RSTEP : r0, krel(j));
   }
 };
 
@@ -306,10 +361,12 @@ struct PackedGather {
 // as it was loaded.  Otherwise (mode kRunK) the plan's void mask -- one bit
 // per entry of the contracted order, set for repeated entries and past the
 // end of K -- says which entries to store as 0, in both operands; a slice
-// without such entries takes the plain store.  The mask is applied to the
-// loaded registers just before the LDS store: a load with a fallback for a
-// partial slice made the compiler copy the other operand's freshly loaded
-// registers at the join, waiting for those loads on every step.
+// without such entries takes the plain store only.  The zeros are written
+// over the stored slice, by the threads that stored the elements: branches
+// that change the loaded registers cost registers at their joins (bf16x3 with
+// a row-gathered partner: 29 spilled with masked registers), and a load with
+// a fallback for a partial slice made the compiler wait there for the other
+// operand's loads on every step.
 template <typename T, typename OffT, int BR, int BK, int NSLOT = 1>
 struct VecKGather {
   static constexpr int VK = 16 / (int)sizeof(T);
@@ -349,17 +406,15 @@ struct VecKGather {
   }
   template <int S = 0>
   __device__ __forceinline__ void store_masked(T* __restrict__ lds, uint32_t voids) {
-    if (voids) clear<S>(voids);
     store<S>(lds, 0, 0);
+    if (voids)
+      zero(voids, [&](int r, int k) { lds[r * LDK + k] = T(0); });
   }
-  template <int S = 0>
-  __device__ __forceinline__ void clear(uint32_t voids) {
-#pragma unroll
-    for (int u = 0; u < VK; ++u) {
-      const bool out = (voids >> (kk0 + u)) & 1u;
-#pragma unroll
-      for (int i = 0; i < NR; ++i) v[S][i][u] = out ? T(0) : v[S][i][u];
-    }
+  template <typename F>
+  __device__ __forceinline__ void zero(uint32_t voids, F f) const {
+    for (int u = 0; u < VK; ++u)
+      if ((voids >> (kk0 + u)) & 1u)
+        for (int i = 0; i < NR; ++i) f(r0 + i * RSTEP, kk0 + u);
   }
 };
 

@@ -51,7 +51,9 @@ struct Analysis {
   // Lowest element offset (<= 0) and reach (max - min offset) of each kernel
   // operand over its non-batch modes: X over I and P, Y over J and P, C over
   // I and J.  Offsets rebased by the lowest one are non-negative.
+  // xk_lo, yk_lo: the contracted modes' part of x_lo, y_lo.
   int64_t x_lo = 0, y_lo = 0, c_lo_mn = 0;
+  int64_t xk_lo = 0, yk_lo = 0;
   int64_t x_span = 0, y_span = 0, c_span = 0;
   int n_trace = 0, n_diag = 0;  // labels summed inside one input / repeated in an input
   int esize = 8;
@@ -106,6 +108,19 @@ struct TileCfg {
 // over workgroups.  bm == 0: the plan runs the LDS-tiled kernel.
 struct DirectCfg {
   int bm = 0, bn = 0, wk = 4, split = 1, kchunk = 0;
+};
+
+// Levelled last round of the 128 x 128 kernels: the `rem` tiles that do not
+// fill a round of two workgroups per CU (the last ones; `head` run whole
+// before them) keep one workgroup each for their first q slices, and the
+// rest of each goes in `parts` runs of `part` slices to further workgroups,
+// which fill the slots that the round leaves empty, one after another, while
+// the first ones run.  Each of these workgroups writes a block of partial
+// sums -- block i for tile i's first slices, rem + i * parts + j for its run
+// j -- and the blocks of a tile are summed in that order.  rem == 0: not used.
+struct LevelCfg {
+  int head = 0, rem = 0, q = 0, part = 0, parts = 0;
+  int64_t blocks() const { return (int64_t)rem * (1 + parts); }
 };
 
 // Host-side bounds check of indexing vectors: every address an operand's

@@ -21,7 +21,12 @@ hipError_t launch_plain(int dtype, const PlainArgs<int64_t>& a, const PlainLaunc
 hipError_t launch_direct(int dtype, const PlainArgs<uint32_t>& a, const DirectCfg& d, bool xv, bool yv,
                          int64_t xplane, int64_t yplane, hipStream_t s);
 // C = alpha * sum over K ranges of W + beta * C for the split tiles (bm x bn blocks of partial sums).
-hipError_t launch_splitk_reduce(int dtype, const PlainArgs<uint32_t>& a, int bm, int bn, hipStream_t s);
+// bf16: the partial sums are FP64 (split-bf16 kernels).
+template <typename OffT>
+hipError_t launch_splitk_reduce(int dtype, bool bf16, const PlainArgs<OffT>& a, int bm, int bn, hipStream_t s);
+// C from the blocks of partial sums of a levelled launch.
+template <typename OffT>
+hipError_t launch_level_reduce(int dtype, bool bf16, const PlainArgs<OffT>& a, hipStream_t s);
 bool plain_tile_supported(int dtype, int bm, int bn, int bk);
 
 }  // namespace famlies

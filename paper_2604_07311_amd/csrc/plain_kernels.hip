@@ -40,26 +40,42 @@ __global__ __launch_bounds__(kThreads, FAMLIES_PLAIN_WAVES_PER_EU) void plain_co
                                     : 1;
   using Tile = PlainTile<T, BM, BN, BK, XM, YM, kDepth>;
   __shared__ T smem[Tile::SMEM];
-  // Work units in launch order: without split-K, every tile of every batch
-  // plane; with split-K, first the tiles [0, head) over all of K, then each
+  // Work units in launch order: with a levelled last round, LevelWork's; without
+  // split-K, every tile of every batch plane; with split-K, first the tiles [0, head) over all of K, then each
   // remaining tile once per K slice.  Each range is spread over the XCDs in
   // contiguous blocks, so neighbouring tiles share an L2.
   const int ntiles = a.tiles_m * a.tiles_n;
-  int l = 0, split = -1, t;
-  if (a.splits == 1) {
-    const int lid = xcd_remap(blockIdx.x, gridDim.x);
-    l = lid / ntiles;  // batch index
-    t = lid % ntiles;
+  TileJob<OffT> j;
+  j.kbeg = 0;
+  j.kend = a.K;
+  int t;            // tile over all batch planes
+  int block = -1;   // its block of partial sums, -1: none
+  if (BM == 128 && BN == 128 && a.rem > 0) {
+    const LevelWork lw(a, (int)blockIdx.x, (a.K + BK - 1) / BK);
+    t = lw.tile;
+    block = lw.block;
+    j.kbeg = lw.s0 * BK;
+    j.kend = min(a.K, lw.s1 * BK);
+  } else if (a.splits == 1) {
+    t = xcd_remap(blockIdx.x, gridDim.x);
   } else if ((int)blockIdx.x < a.head) {
     t = xcd_remap(blockIdx.x, a.head);
   } else {
     const int ntail = ntiles - a.head;
     const int v = xcd_remap(blockIdx.x - a.head, gridDim.x - a.head);
-    split = v / ntail;
+    const int split = v / ntail;
     t = a.head + v % ntail;
+    block = v;
+    j.kbeg = split * a.kchunk;
+    j.kend = min(a.K, j.kbeg + a.kchunk);
   }
-  const int pm = t % a.tiles_m, pn = t / a.tiles_m;  // M fastest: neighbours share Y's panel
-  TileJob<OffT> j;
+  t = scalar(t);
+  block = scalar(block);
+  j.kbeg = scalar(j.kbeg);
+  j.kend = scalar(j.kend);
+  const int l = scalar(t / ntiles), tl = t - l * ntiles;  // batch index, tile of its plane
+  // M fastest: neighbours share Y's panel
+  const int pn = scalar(tl / a.tiles_m), pm = tl - pn * a.tiles_m;
   // a pre-packed operand holds its batch planes back to back
   j.x = static_cast<const T*>(a.x) +
         (XM == kPacked ? (int64_t)l * a.tiles_m * a.x_nkb * (int64_t)(BM * BK) : a.xl[l]);
@@ -79,23 +95,20 @@ __global__ __launch_bounds__(kThreads, FAMLIES_PLAIN_WAVES_PER_EU) void plain_co
   j.N = a.N;
   j.m0 = pm * BM;
   j.n0 = pn * BN;
-  j.kbeg = split < 0 ? 0 : split * a.kchunk;
-  j.kend = split < 0 ? a.K : min(a.K, j.kbeg + a.kchunk);
   j.alpha = a.alpha;
   j.beta = a.beta;
-  // partial sums of a split tile: its own dense BM x BN block
+  // partial sums: a dense BM x BN block of their own
   j.ldw = BN;
-  j.work = split < 0 ? nullptr
-                     : static_cast<void*>(static_cast<T*>(a.work) +
-                                          ((size_t)split * (size_t)(ntiles - a.head) + (size_t)(t - a.head)) *
-                                              (size_t)(BM * BN));
+  j.work = block < 0 ? nullptr
+                     : static_cast<void*>(static_cast<T*>(a.work) + (size_t)block * (size_t)(BM * BN));
   Tile::run(j, smem);
 }
 
 // For the split tiles: C = alpha * sum_s W[s] + beta * C, the K slices
 // summed in index order so the result does not depend on scheduling.  One
-// thread per element of a split tile (bm x bn blocks, row-major).
-template <typename T, typename OffT>
+// thread per element of a split tile (bm x bn blocks, row-major).  P: type of
+// the partial sums (T; double in the bf16 kernels).
+template <typename T, typename P, typename OffT>
 __global__ __launch_bounds__(kThreads) void splitk_reduce(PlainArgs<OffT> a, int bm, int bn) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   const int ntail = a.tiles_m * a.tiles_n - a.head;
@@ -105,15 +118,88 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce(PlainArgs<OffT> a, int
   const int t = a.head + tt;
   const int m = (t % a.tiles_m) * bm + r / bn, n = (t / a.tiles_m) * bn + r % bn;
   if (m >= a.M || n >= a.N) return;
-  const T* W = static_cast<const T*>(a.work);
-  T s = T(0);
+  const P* W = static_cast<const P*>(a.work);
+  P s = P(0);
   for (int k = 0; k < a.splits; ++k) s += W[((size_t)k * ntail + tt) * per + r];
   T* cp = at(static_cast<T*>(a.c), (OffT)(a.cm[m] + a.cn[n]));
-  const T al = static_cast<T>(a.alpha), be = static_cast<T>(a.beta);
-  T v = al * s;
-  if (be != T(0)) v += be * *cp;
-  *cp = v;
+  const P al = static_cast<P>(a.alpha), be = static_cast<P>(a.beta);
+  P v = al * s;
+  if (be != P(0)) v += be * (P)*cp;
+  *cp = (T)v;
 }
+
+// The levelled tiles: C = alpha * (their blocks of partial sums in order) +
+// beta * C.  P is the type of the partial sums (and of the update): T for the
+// plain kernels, double for the bf16 kernels.  A workgroup takes 16 rows of a
+// tile, its lanes consecutive columns, eight rows per thread in flight; bound
+// by HBM (partial sums read once, C read and written).
+template <typename T, typename P, typename OffT>
+__global__ __launch_bounds__(kThreads) void level_reduce(PlainArgs<OffT> a) {
+  constexpr int B = 128, RW = 16, RT = RW / 2;
+  const int i = blockIdx.x / (B / RW), row0 = (blockIdx.x % (B / RW)) * RW + threadIdx.x / B;
+  const int ntiles = a.tiles_m * a.tiles_n;
+  const int t = a.head + i, l = t / ntiles, tl = t % ntiles;
+  const int m0 = (tl % a.tiles_m) * B + row0, n = (tl / a.tiles_m) * B + threadIdx.x % B;
+  const P* W = static_cast<const P*>(a.work) + (size_t)row0 * B + threadIdx.x % B;
+  P s[RT];
+#pragma unroll
+  for (int q = 0; q < RT; ++q) s[q] = *global(W + (size_t)i * (B * B) + q * 2 * B);
+  for (int w = 0; w < a.lev_parts; ++w)
+#pragma unroll
+    for (int q = 0; q < RT; ++q)
+      s[q] += *global(W + ((size_t)a.rem + (size_t)i * a.lev_parts + w) * (B * B) + q * 2 * B);
+  if (n >= a.N) return;
+  T* C = static_cast<T*>(a.c) + a.cl[l];
+  const OffT cn = a.cn[n];
+  const P al = static_cast<P>(a.alpha), be = static_cast<P>(a.beta);
+  OffT co[RT];
+  P c[RT];
+#pragma unroll
+  for (int q = 0; q < RT; ++q) co[q] = (OffT)(a.cm[m0 + 2 * q < a.M ? m0 + 2 * q : 0] + cn);
+  if (be != P(0)) {
+#pragma unroll
+    for (int q = 0; q < RT; ++q) c[q] = (P)*global(at(C, co[q]));
+  }
+#pragma unroll
+  for (int q = 0; q < RT; ++q)
+    if (m0 + 2 * q < a.M) {
+      P v = al * s[q];
+      if (be != P(0)) v += be * c[q];
+      *global(at(C, co[q])) = (T)v;
+    }
+}
+
+// bf16: the partial sums are FP64.
+template <typename OffT>
+hipError_t launch_level_reduce(int dtype, bool bf16, const PlainArgs<OffT>& a, hipStream_t s) {
+  const dim3 grid(a.rem * 8);
+  if (dtype == FAMLIES_F64)
+    hipLaunchKernelGGL((level_reduce<double, double, OffT>), grid, dim3(kThreads), 0, s, a);
+  else if (bf16)
+    hipLaunchKernelGGL((level_reduce<float, double, OffT>), grid, dim3(kThreads), 0, s, a);
+  else
+    hipLaunchKernelGGL((level_reduce<float, float, OffT>), grid, dim3(kThreads), 0, s, a);
+  return hipGetLastError();
+}
+template hipError_t launch_level_reduce(int, bool, const PlainArgs<uint32_t>&, hipStream_t);
+template hipError_t launch_level_reduce(int, bool, const PlainArgs<int32_t>&, hipStream_t);
+template hipError_t launch_level_reduce(int, bool, const PlainArgs<int64_t>&, hipStream_t);
+
+template <typename OffT>
+hipError_t launch_splitk_reduce(int dtype, bool bf16, const PlainArgs<OffT>& a, int bm, int bn, hipStream_t s) {
+  const int64_t red = ((int64_t)a.tiles_m * a.tiles_n - a.head) * bm * bn;
+  const dim3 grid((int)((red + kThreads - 1) / kThreads));
+  if (dtype == FAMLIES_F64)
+    hipLaunchKernelGGL((splitk_reduce<double, double, OffT>), grid, dim3(kThreads), 0, s, a, bm, bn);
+  else if (bf16)
+    hipLaunchKernelGGL((splitk_reduce<float, double, OffT>), grid, dim3(kThreads), 0, s, a, bm, bn);
+  else
+    hipLaunchKernelGGL((splitk_reduce<float, float, OffT>), grid, dim3(kThreads), 0, s, a, bm, bn);
+  return hipGetLastError();
+}
+template hipError_t launch_splitk_reduce(int, bool, const PlainArgs<uint32_t>&, int, int, hipStream_t);
+template hipError_t launch_splitk_reduce(int, bool, const PlainArgs<int32_t>&, int, int, hipStream_t);
+template hipError_t launch_splitk_reduce(int, bool, const PlainArgs<int64_t>&, int, int, hipStream_t);
 
 // K == 0 or alpha == 0: C = beta * C (beta == 0 writes zeros without reading C).
 template <typename T, typename OffT>
@@ -168,18 +254,17 @@ static hipError_t launch_plain_t(const PlainArgs<OffT>& a, const PlainLaunch& L,
     return hipGetLastError();
   }
   const int64_t ntiles = (int64_t)a.tiles_m * a.tiles_n;
-  const int grid = (int)(a.splits == 1 ? ntiles * a.L : a.head + (ntiles - a.head) * a.splits);
+  const int grid = a.rem > 0 ? a.head + a.rem * (1 + a.lev_parts)
+                             : (int)(a.splits == 1 ? ntiles * a.L : a.head + (ntiles - a.head) * a.splits);
   constexpr int BK = sizeof(T) == 8 ? 8 : 32;
   hipError_t e = hipErrorInvalidValue;
   if (L.bm == 128 && L.bn == 128 && L.bk == BK)
     e = launch_tile<T, OffT, 128, 128, BK>(a, L.xm, L.ym, grid, s);
   else if (L.bm == 64 && L.bn == 64 && L.bk == BK)
     e = launch_tile<T, OffT, 64, 64, BK>(a, L.xm, L.ym, grid, s);
+  if (e == hipSuccess && a.rem > 0) return launch_level_reduce(sizeof(T) == 8 ? FAMLIES_F64 : FAMLIES_F32, false, a, s);
   if (e != hipSuccess || a.splits == 1) return e;
-  const int64_t red = (ntiles - a.head) * L.bm * L.bn;
-  hipLaunchKernelGGL((splitk_reduce<T, OffT>), dim3((int)((red + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                     a, L.bm, L.bn);
-  return hipGetLastError();
+  return launch_splitk_reduce(sizeof(T) == 8 ? FAMLIES_F64 : FAMLIES_F32, false, a, L.bm, L.bn, s);
 }
 
 hipError_t launch_plain(int dtype, const PlainArgs<uint32_t>& a, const PlainLaunch& L, hipStream_t s) {
@@ -195,16 +280,6 @@ hipError_t launch_plain(int dtype, const PlainArgs<int32_t>& a, const PlainLaunc
 hipError_t launch_plain(int dtype, const PlainArgs<int64_t>& a, const PlainLaunch& L, hipStream_t s) {
   return dtype == FAMLIES_F64 ? launch_plain_t<double, int64_t>(a, L, s)
                               : launch_plain_t<float, int64_t>(a, L, s);
-}
-
-hipError_t launch_splitk_reduce(int dtype, const PlainArgs<uint32_t>& a, int bm, int bn, hipStream_t s) {
-  const int64_t red = ((int64_t)a.tiles_m * a.tiles_n - a.head) * bm * bn;
-  const dim3 grid((int)((red + kThreads - 1) / kThreads));
-  if (dtype == FAMLIES_F64)
-    hipLaunchKernelGGL((splitk_reduce<double, uint32_t>), grid, dim3(kThreads), 0, s, a, bm, bn);
-  else
-    hipLaunchKernelGGL((splitk_reduce<float, uint32_t>), grid, dim3(kThreads), 0, s, a, bm, bn);
-  return hipGetLastError();
 }
 
 bool plain_tile_supported(int dtype, int bm, int bn, int bk) {

@@ -109,7 +109,7 @@ TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_t
 // 42 -> 31, FP64 16 x 675840 x 64 142 -> 108; the other way FP32 256 x 4096 x
 // 4096 takes 78 tiled and 125 direct, so direct is not considered above 4
 // GFLOP except for narrow problems.
-DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const TileCfg& t) {
+DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, double level_us) {
   DirectCfg none;
   if (an.M == 0 || an.N == 0 || an.K == 0) return none;
   const double flops = 2.0 * (double)an.M * (double)an.N * (double)an.K * (double)an.L;
@@ -136,6 +136,7 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
   double tiled = 3.5 + std::max(std::max(1.0, units / (2.0 * cus)) * slices * slice_us, hbm_us);
   if (t.split > 1) tiled += 4.0 + (double)(t.split + 1) * (double)split_tiles * t.bm * t.bn * es / 4.0e6;
 
+  tiled = std::min(tiled, level_us);
   DirectCfg best = none;
   double best_us = 0.88 * tiled;  // the estimates are good to about a tenth
   const int shapes[4][2] = {{16, 16}, {32, 32}, {16, 64}, {64, 16}};
@@ -165,6 +166,76 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
         }
       }
   return best;
+}
+
+// Times of the 128 x 128 kernels in microseconds, from constants measured on
+// MI355X: per K slice with two workgroups on every CU, per workgroup outside
+// its slices (first loads, C update or partial sums), per byte of partial sums
+// written and read.  A CU with a single workgroup runs it at about 0.65 of
+// the CU's rate.  Two ways to cut the last round's tiles are weighed: evenly
+// into 2 to 8 runs, or a long first part beside shorter runs on the slots
+// that are free; the second moves fewer bytes, but its workgroups are at
+// different places of K and share less in L2 (6 % charged).  Measured against
+// no split and the best even split with a plain reduction: FP32 ladder v=93
+// o=27 (408 tiles) 1104 and 960 -> 924 us in five even runs, 945 uneven; FP32
+// ring o=31 v=115 981 and 894 -> 808; bf16x6 ring o=31 v=115 638 and 727 ->
+// 585; bf16x3 ring o=48 v=192 5590 -> 5500.
+LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd, bool* unsplit,
+                      double* us) {
+  LevelCfg lv;
+  *unsplit = false;
+  if (t.bm != 128 || t.bn != 128 || an.M == 0 || an.N == 0 || an.K == 0) return lv;
+  const int ns = split_parts(an.compute);
+  const int64_t cus = h ? h->num_cus : 256, slots = 2 * cus;
+  const int64_t tiles = ceil_div(an.M, 128) * ceil_div(an.N, 128) * an.L;
+  const int64_t nk = ceil_div(kd, t.bk), rem = tiles % slots, full = tiles / slots;
+  if (tiles >= ((int64_t)1 << 30)) return lv;
+  const double slice = ns ? 1.45 : an.esize == 8 ? 1.95 : 3.8, unit = 9.0;
+  const double block = 128.0 * 128.0 * (ns ? 8.0 : (double)an.esize), pass = 7.0e6;
+  // rounds of n workgroups per tile-sized unit of s slices
+  auto rounds = [&](int64_t n, double s) {
+    const int64_t last = n % slots;
+    return (double)(n / slots) * (s * slice + unit) +
+           (last == 0 ? 0.0 : (last > cus ? 1.0 : 0.77) * s * slice + unit);
+  };
+  const double whole = rounds(tiles, (double)nk);
+  double now = whole;
+  if (t.split > 1) {
+    const int64_t cut = t.tail ? t.tail : tiles;
+    now = rounds(tiles - cut, (double)nk) + rounds(cut * t.split, (double)ceil_div(nk, t.split)) + 4.0 +
+          (double)(2 * t.split + 2) * (double)cut * block / 4.2e6;  // splitk_reduce, one element per thread
+    if (whole < now) {
+      *unsplit = true;
+      now = whole;
+    }
+  }
+  if (rem == 0) return lv;
+  double best = 0.95 * now;
+  auto consider = [&](double time, int64_t q, int64_t part, int64_t parts) {
+    time += (double)full * ((double)nk * slice + unit) + 4.0 + (double)(rem * (2 * (1 + parts) + 2)) * block / pass;
+    if (time >= best) return;
+    best = *us = time;
+    *unsplit = false;
+    lv.head = (int)(tiles - rem);
+    lv.rem = (int)rem;
+    lv.q = (int)q;
+    lv.part = (int)part;
+    lv.parts = (int)parts;
+  };
+  const int64_t free_slots = slots - rem;
+  for (int64_t parts = 1; parts <= 7; ++parts) {
+    if (nk / (parts + 1) < 4 || rem * (parts + 1) > (1 << 24)) break;
+    const int64_t even = ceil_div(nk, parts + 1);
+    if (nk - parts * even >= 1) consider(rounds(rem * (parts + 1), (double)even), nk - parts * even, even, parts);
+    // the runs take `turns` each on the free slots, the first part is as long
+    // as those together
+    const int64_t turns = ceil_div(rem * parts, free_slots);
+    const int64_t part = (int64_t)(((double)nk * slice - (double)(turns - 1) * unit) / (slice * (double)(turns + parts)));
+    const int64_t q = nk - parts * part;
+    if (part < 4 || q <= part) continue;
+    consider(1.06 * std::max((double)q * slice + unit, (double)turns * ((double)part * slice + unit)), q, part, parts);
+  }
+  return lv;
 }
 
 bool contiguous_k_runs(const std::vector<int64_t>& ks, int64_t K, int u) {
@@ -323,8 +394,8 @@ bool log_enabled() {
 // One line on stderr: what the planner decided (orientation, loaders, tile,
 // split, index form -- index_bits 32: uint32 bytes, -32: int32 elements, 64:
 // int64 elements -- and workspace).
-void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d, int index_bits,
-                  bool x_vec, bool y_vec, size_t work_bytes, bool table_hit) {
+void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d,
+                  const LevelCfg& lv, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit) {
   static const char* loader[4] = {"rows", "k-gather", "packed", "k-affine"};
   const int xm = an.x_kfast ? (x_vec ? 3 : 1) : 0, ym = an.y_kfast ? (y_vec ? 3 : 1) : 0;
   static const char* int8_names[8] = {"", "", "", "int8x3", "int8x4", "int8x5", "int8x6", "int8x7"};
@@ -332,8 +403,11 @@ void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, cons
                      : an.compute == FAMLIES_BF16X6 ? "bf16x6"
                      : int8_slices(an.compute)      ? int8_names[int8_slices(an.compute)]
                                                     : "native";
-  char direct[64] = "";
+  char direct[96] = "";
   if (d.bm) std::snprintf(direct, sizeof direct, " direct=%dx%d/%d waves/split %d", d.bm, d.bn, d.wk, d.split);
+  if (lv.rem)
+    std::snprintf(direct, sizeof direct, " level=%d whole, %d x %d + %d x %d slices", lv.head, lv.rem, lv.q, lv.parts,
+                  lv.part);
   std::fprintf(stderr,
                "[famlies] %s %s/%s M=%lld N=%lld K=%lld L=%lld swapped=%d groups=%zu/%zu/%zu/%zu "
                "trace=%d diag=%d X=%s Y=%s tile=%dx%dx%d split=%d split_tiles=%d index=%s "
@@ -386,9 +460,17 @@ static famlies_status analyze_impl(int dtype, int compute, const famlies_tensor*
   }
   fill_info(an, t, ib, kernel_code(an, xv, yv), info);
   info->index_elements = ib == 64 || e32;
-  const bool native = !split_parts(an.compute) && !int8_slices(an.compute);
-  const DirectCfg d = native && ib == 32 && !e32 ? choose_direct(nullptr, an, t) : DirectCfg();
-  if (log_enabled()) log_decision("analyze", an, t, d, e32 ? -32 : ib, xv, yv, 0, false);
+  // what a plan would run instead of the tile choice reported above
+  DirectCfg d;
+  LevelCfg lv;
+  if (!int8_slices(an.compute)) {
+    bool unsplit = false;
+    double level_us = 1e30;
+    lv = choose_level(nullptr, an, t, runs ? runs : an.K, &unsplit, &level_us);
+    if (!split_parts(an.compute) && ib == 32 && !e32) d = choose_direct(nullptr, an, t, level_us);
+    if (d.bm) lv = LevelCfg();
+  }
+  if (log_enabled()) log_decision("analyze", an, t, d, lv, e32 ? -32 : ib, xv, yv, 0, false);
   if (offs) {
     const int64_t need = 2 * an.M + 2 * an.K + 2 * an.N + 3 * an.L;
     if (offs_len < need) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_analyze: offsets buffer too short");

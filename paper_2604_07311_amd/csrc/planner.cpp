@@ -337,8 +337,10 @@ int analyze(int dtype, int compute, const famlies_tensor* A, const famlies_tenso
   an.max_abs_x = reach(an.I, 0) + reach(an.P, 0) + reach(an.Lm, 0);
   an.max_abs_y = reach(an.J, 1) + reach(an.P, 1) + reach(an.Lm, 1);
   an.max_abs_c = reach(an.I, 2) + reach(an.J, 2) + reach(an.Lm, 2);
-  an.x_lo = lowest(an.I, 0) + lowest(an.P, 0);
-  an.y_lo = lowest(an.J, 1) + lowest(an.P, 1);
+  an.xk_lo = lowest(an.P, 0);
+  an.yk_lo = lowest(an.P, 1);
+  an.x_lo = lowest(an.I, 0) + an.xk_lo;
+  an.y_lo = lowest(an.J, 1) + an.yk_lo;
   an.c_lo_mn = lowest(an.I, 2) + lowest(an.J, 2);
   an.x_span = reach(an.I, 0) + reach(an.P, 0);
   an.y_span = reach(an.J, 1) + reach(an.P, 1);

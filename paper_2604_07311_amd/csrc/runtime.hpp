@@ -67,6 +67,7 @@ struct famlies_plan_s {
   bool x_vec = false, y_vec = false;
   int64_t kd = 0;          // K of the kernels' contracted order (padded to 16-byte runs, or the plain one)
   int xmode = 0, ymode = 0;  // loader modes of X and Y when they are not pre-packed
+  famlies::LevelCfg level;  // rem > 0: the 128 x 128 kernel runs with a levelled last round instead of cfg's split
   size_t kvoid_pos = 0;    // void mask of the contracted order (byte-offset plans of the plain and bf16 kernels)
   famlies::DirectCfg direct;                // bm > 0: native kMain launches run the direct kernel
   bool dx_vec = false, dy_vec = false;      // every run of 16 bytes of X / Y along K is contiguous
@@ -129,8 +130,8 @@ inline famlies_plan_s* plan_of(const void* tok) {
 // FAMLIES_LOG is set to a non-empty value other than "0".
 bool log_enabled();
 void log_plan(const famlies_plan_s* p);
-void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d, int index_bits,
-                  bool x_vec, bool y_vec, size_t work_bytes, bool table_hit);
+void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d,
+                  const LevelCfg& lv, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit);
 
 // Internal forms of the ABI calls, on resolved objects.
 famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, const void* B, double beta,
@@ -143,8 +144,15 @@ TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_t
 
 // Host planning helpers (plan_host.cpp).
 // The direct kernel's configuration where it beats the LDS-tiled kernel with
-// configuration t, else bm = 0.
-DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const TileCfg& t);
+// configuration t (and level_us, the levelled tiled kernel's estimate), else
+// bm = 0.
+DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, double level_us);
+// A levelled last round for the 128 x 128 kernel of a plan with configuration
+// t (settled) and contracted order length kd, where it beats both t and no
+// split (*us: its estimated time, else untouched); *unsplit is set where no
+// split at all is the fastest.
+LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd, bool* unsplit,
+                      double* us);
 // Whether every aligned run of u contracted indices is contiguous.
 bool contiguous_k_runs(const std::vector<int64_t>& ks, int64_t K, int u);
 int64_t ceil_div(int64_t a, int64_t b);

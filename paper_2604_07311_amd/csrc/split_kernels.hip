@@ -106,6 +106,14 @@ __device__ __forceinline__ void store_split(const G& gg, __bf16* tiles, int tile
   }
 }
 
+// Zero this thread's elements at the slice's void k's in every part tile.
+template <int NS, typename G>
+__device__ __forceinline__ void zero_split(const G& gg, __bf16* tiles, int tile_elems, uint32_t voids) {
+  gg.zero(voids, [&](int r, int k) {
+    for (int t = 0; t < NS; ++t) tiles[t * tile_elems + r * kSplitLD<NS> + k] = (__bf16)0.0f;
+  });
+}
+
 // Operand loader of the split kernels: a gathered FP32 slice split at the
 // LDS store (modes kRowGather, kKGather), or pre-packed bf16 parts copied as
 // they are (kPacked: block (tile, kb) holds the NS part planes of BR x BK
@@ -115,7 +123,7 @@ template <typename OffT, int BR, int NS, int MODE, int NSLOT = 1>
 struct SplitLoader {
   static_assert(MODE == kRowGather || MODE == kKGather, "every other mode has its own loader");
   static constexpr bool KF = MODE == kKGather;
-  using G = TileGather<float, OffT, BR, kSplitBK<NS>, KF, KF ? 2 : 1, NSLOT>;
+  using G = TileGather<float, OffT, BR, kSplitBK<NS>, KF, KF ? 2 : 1, NSLOT, NS == 2>;
   G g;
   int nkb = 0;
   __device__ __forceinline__ void init(const OffT* mnoff, int tile_r0, int tid) { g.init(mnoff, tile_r0, tid); }
@@ -125,8 +133,8 @@ struct SplitLoader {
   __device__ __forceinline__ void load(const void* base) { g.template load<S>(static_cast<const float*>(base)); }
   template <int S = 0>
   __device__ __forceinline__ void store_masked(__bf16* tiles, int tile_elems, uint32_t voids) {
-    if (voids) g.template clear<S>(voids);
     store_split<NS, G, KF, false, S>(g, tiles, tile_elems, 0, 0);
+    if (voids) zero_split<NS>(g, tiles, tile_elems, voids);
   }
   template <int S = 0>
   __device__ __forceinline__ void store(__bf16* tiles, int tile_elems, int k0, int kend) const {
@@ -175,8 +183,8 @@ struct SplitLoader<OffT, BR, NS, kVecK, NSLOT> {
   }
   template <int S = 0>
   __device__ __forceinline__ void store_masked(__bf16* tiles, int tile_elems, uint32_t voids) {
-    if (voids) g.template clear<S>(voids);
     store<S>(tiles, tile_elems, 0, 0);
+    if (voids) zero_split<NS>(g, tiles, tile_elems, voids);
   }
 };
 template <typename OffT, int BR, int NS, int NSLOT>
@@ -269,17 +277,31 @@ __global__ __launch_bounds__(kThreads, (kSplitWgPerCu<OffT, BM, NS, XM, YM>)) vo
   const int tid = threadIdx.x;
   const int lane = tid % 64, wave = tid / 64;
   const int wm = wave / 2, wn = wave % 2;
-  const int lid0 = xcd_remap(blockIdx.x, gridDim.x);
   const int ntiles = a.tiles_m * a.tiles_n;
-  const int per_batch = ntiles * a.splits;
-  const int l = lid0 / per_batch;  // batch index
-  const int lid = lid0 % per_batch;
-  const int split = lid / ntiles;
-  const int t = lid % ntiles;
-  const int pm = t % a.tiles_m, pn = t / a.tiles_m;
+  int t, block = -1, kbeg, kend;  // t: tile over all batch planes
+  if (BM == 128 && BN == 128 && a.rem > 0) {
+    const LevelWork lw(a, (int)blockIdx.x, (a.K + BK - 1) / BK);
+    t = lw.tile;
+    block = lw.block;
+    kbeg = lw.s0 * BK;
+    kend = min(a.K, lw.s1 * BK);
+  } else {
+    const int per_batch = ntiles * a.splits;
+    const int lid0 = xcd_remap(blockIdx.x, gridDim.x);
+    const int lid = lid0 % per_batch;
+    const int split = lid / ntiles;
+    t = lid0 / per_batch * ntiles + lid % ntiles;
+    kbeg = split * a.kchunk;
+    kend = min(a.K, kbeg + a.kchunk);
+    if (a.splits > 1) block = lid;  // K range by K range, tile by tile (no batch planes then)
+  }
+  t = scalar(t);
+  block = scalar(block);
+  kbeg = scalar(kbeg);
+  kend = scalar(kend);
+  const int l = scalar(t / ntiles), tl = t - l * ntiles;  // batch index, tile of its plane
+  const int pn = scalar(tl / a.tiles_m), pm = tl - pn * a.tiles_m;
   const int m0 = pm * BM, n0 = pn * BN;
-  const int kbeg = split * a.kchunk;
-  const int kend = min(a.K, kbeg + a.kchunk);
   const int nk = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
   // a pre-packed operand holds its batch planes back to back
   const void* X = XM == kPacked ? static_cast<const void*>(static_cast<const __bf16*>(a.x) +
@@ -422,7 +444,7 @@ __global__ __launch_bounds__(kThreads, (kSplitWgPerCu<OffT, BM, NS, XM, YM>)) vo
     for (int o = NA - 1; o >= 0; --o) v += (double)acc[o][i][j][e];  // smallest order first
     return v;
   };
-  if (a.splits == 1) {
+  if (block < 0) {
     float* __restrict__ C = static_cast<float*>(a.c) + a.cl[l];
     // Every read (indexing vectors, then C for beta != 0) before the first
     // write, so that the reads are in flight together rather than one per
@@ -463,35 +485,20 @@ __global__ __launch_bounds__(kThreads, (kSplitWgPerCu<OffT, BM, NS, XM, YM>)) vo
         }
     }
   } else {
-    const int ldw = a.tiles_n * BN;
-    double* __restrict__ W = static_cast<double*>(a.work) + (size_t)split * (size_t)(a.tiles_m * BM) * ldw;
+    // FP64 partial sums: a BM x BN block of their own
+    double* __restrict__ W = static_cast<double*>(a.work) + (size_t)block * (size_t)(BM * BN);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const int n = n0 + wn * WTN + j * 32 + r;
+      const int n = wn * WTN + j * 32 + r;
 #pragma unroll
       for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int m = m0 + wm * WTM + i * 32 + Mfma<float>::row(lane, e);
-          W[(size_t)m * ldw + n] = total(i, j, e);
+          const int m = wm * WTM + i * 32 + Mfma<float>::row(lane, e);
+          *global(W + m * BN + n) = total(i, j, e);
         }
     }
   }
-}
-
-template <typename OffT>
-__global__ __launch_bounds__(kThreads) void split_reduce(PlainArgs<OffT> a, int ldw, int rows) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= (int64_t)a.M * a.N) return;
-  const int m = (int)(i / a.N), n = (int)(i % a.N);
-  const double* W = static_cast<const double*>(a.work);
-  const size_t plane = (size_t)rows * ldw;
-  double s = 0.0;
-  for (int k = 0; k < a.splits; ++k) s += W[(size_t)k * plane + (size_t)m * ldw + n];
-  float* cp = at(static_cast<float*>(a.c), (OffT)(a.cm[m] + a.cn[n]));
-  double v = a.alpha * s;
-  if (a.beta != 0.0) v += a.beta * (double)*cp;
-  *cp = (float)v;
 }
 
 template <typename OffT, int BM, int BN, int NS, int XM, int YM>
@@ -525,7 +532,7 @@ static hipError_t launch_split_tile(const PlainArgs<OffT>& a, int xm, int ym, in
 
 template <typename OffT>
 static hipError_t launch_split_t(const PlainArgs<OffT>& a, const PlainLaunch& L, int ns, hipStream_t s) {
-  const int grid = a.tiles_m * a.tiles_n * a.splits * a.L;
+  const int grid = a.rem > 0 ? a.head + a.rem * (1 + a.lev_parts) : a.tiles_m * a.tiles_n * a.splits * a.L;
   hipError_t e = hipErrorInvalidValue;
   if (ns == 2) {
     if (L.bm == 256 && L.bn == 128)
@@ -540,11 +547,9 @@ static hipError_t launch_split_t(const PlainArgs<OffT>& a, const PlainLaunch& L,
     else if (L.bm == 64 && L.bn == 64)
       e = launch_split_tile<OffT, 64, 64, 3>(a, L.xm, L.ym, grid, s);
   }
+  if (e == hipSuccess && a.rem > 0) return launch_level_reduce(FAMLIES_F32, true, a, s);
   if (e != hipSuccess || a.splits == 1) return e;
-  const int64_t mn = (int64_t)a.M * a.N;
-  hipLaunchKernelGGL((split_reduce<OffT>), dim3((int)((mn + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                     s, a, a.tiles_n * L.bn, a.tiles_m * L.bm);
-  return hipGetLastError();
+  return launch_splitk_reduce(FAMLIES_F32, true, a, L.bm, L.bn, s);
 }
 
 hipError_t launch_split(const PlainArgs<uint32_t>& a, const PlainLaunch& L, int ns, hipStream_t s) {
