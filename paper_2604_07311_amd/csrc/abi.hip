@@ -104,10 +104,10 @@ static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int
   p->xmode = an.x_kfast ? (p->x_vec ? 3 : 1) : 0;
   p->ymode = an.y_kfast ? (p->y_vec ? 3 : 1) : 0;
   // the kernels' contracted order (the plain one, or padded to 16-byte runs)
-  // and its void mask; byte offsets of the plain and bf16 kernels only
+  // and its void mask, with byte offsets
   std::vector<uint32_t> kvoid;
   const int u = 16 / an.esize;
-  if (bytes && !int8_slices(an.compute)) {
+  if (bytes) {
     kvoid.assign((size_t)(ceil_div(kp, 32) + 1), 0);
     KRuns kr;
     const bool padded = p->kd != an.K;
@@ -240,16 +240,17 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   p->h = h;
   p->an = an;
   const int i8 = int8_slices(compute);
-  p->cfg = i8 ? int8_tile() : force ? *force : choose_tiles(h, an, &p->table_hit);
+  p->cfg = i8 ? int8_tile(i8, an.N) : force ? *force : choose_tiles(h, an, &p->table_hit);
   if (i8 && force) p->cfg.index_bits = force->index_bits;
   index_form(an, p->cfg.index_bits, &p->index_bits, &p->elem32);
   const int ns = split_parts(compute);
   // contracted order of the kernels: padded to 16-byte runs where that pays
   const int64_t runs =
-      lean || i8 || p->index_bits != 32 || p->elem32 ? 0 : padded_k_length(an, 16 / an.esize);
+      lean || p->index_bits != 32 || p->elem32 ? 0 : padded_k_length(an, 16 / an.esize);
   p->kd = runs && runs <= lim ? runs : an.K;
   if (i8) {
-    // fixed tile (int8_tile): no split-K, no tile table
+    // int8_tile, no tile table; K ranges where tiles are few
+    if (!lean && an.L == 1 && p->kd <= int8_exact_k(i8)) p->cfg.split = int8_split(h, an, p->cfg, p->kd);
   } else if (ns) {
     // the bf16 kernels split every tile or none: a tail split becomes none
     if (p->cfg.tail) {
@@ -319,7 +320,7 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
                             : index_image<uint32_t>(p, mp, np, kp, image);
   if (st != FAMLIES_OK) return st;
   if (i8 && an.K > 0) {
-    p->work_bytes = int8_work_bytes(i8, an.M, an.N, an.K, an.L);  // digit planes and exponents
+    p->work_bytes = int8_work_bytes(i8, an.M, an.N, p->kd, an.L, p->cfg.bn, p->cfg.split);  // digit planes and exponents
   } else if (p->cfg.split > 1 && an.K > 0) {
     // one BM x BN block per split tile and K slice (of FP64 sums in the bf16 kernels)
     p->work_bytes = ns ? (size_t)p->cfg.split * (size_t)mp * (size_t)np * 8
@@ -539,12 +540,10 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
   const int i8 = int8_slices(an.compute);
   if (i8 && (pa || pb)) return fail(FAMLIES_ERR_UNSUPPORTED, "famlies_execute_packed: no packed operands for INT8 plans");
   if (i8 && L.kind == PlainLaunch::kMain) {
-    // slicer read modes: affine K blocks (the plan's block-stride flags, for
-    // slices of 64 and a 16-byte aligned base) with 16-byte loads
-    const int xmode = an.x_kfast ? (p->x_vec && !((uintptr_t)x & 15) ? 2 : 1) : 0;
-    const int ymode = an.y_kfast ? (p->y_vec && !((uintptr_t)y & 15) ? 2 : 1) : 0;
-    e = p->index_bits == 32 ? launch_int8(make_args<uint32_t>(p, x, y, C, alpha, beta), i8, xmode, ymode, s)
-                            : launch_int8(make_args<int64_t>(p, x, y, C, alpha, beta), i8, xmode, ymode, s);
+    const int xm = std::min(p->xmode, 2), ym = std::min(p->ymode, 2);  // 16-byte runs of any form: 2
+    e = p->index_bits == 32
+            ? launch_int8(make_args<uint32_t>(p, x, y, C, alpha, beta), i8, p->cfg.bn, xm, ym, s)
+            : launch_int8(make_args<int64_t>(p, x, y, C, alpha, beta), i8, p->cfg.bn, xm, ym, s);
   } else if (ns && L.kind == PlainLaunch::kMain) {
     if (p->elem32) {
       e = launch_split(make_args<int32_t>(p, x, y, C, alpha, beta), L, ns, s);

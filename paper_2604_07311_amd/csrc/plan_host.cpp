@@ -373,14 +373,36 @@ int kernel_code(const Analysis& an, bool xv, bool yv) {
   return 1 + split_parts(an.compute) + (xv ? 16 : 0) + (yv ? 32 : 0);
 }
 
-TileCfg int8_tile() {
+TileCfg int8_tile(int slices, int64_t n) {
   TileCfg t;
   t.bm = 128;
-  t.bn = 64;
+  t.bn = slices <= 6 && n > 64 ? 128 : 64;
   t.bk = 64;
   t.split = 1;
   t.tail = 0;
   return t;
+}
+
+// One workgroup per CU: K ranges even out the rounds of tiles.  A step of 32
+// contracted indices takes about 0.04 S (S + 1) us, a workgroup 8 us besides
+// (first loads, recombination), partial sums pass at 6 TB/s.  FP64 ladder v=38
+// o=12 at six slices (24 tiles): GEMM 70 us unsplit.
+int int8_split(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd) {
+  const int64_t cus = h ? h->num_cus : 256;
+  const int64_t tiles = ceil_div(an.M, t.bm) * ceil_div(an.N, t.bn), blocks = ceil_div(kd, t.bk);
+  const int S = int8_slices(an.compute);
+  const double block_us = 0.08 * S * (S + 1) * t.bn / 128.0;
+  double best = 1e300;
+  int pick = 1;
+  for (int s = 1; s <= 16 && s <= blocks; ++s) {
+    double us = (double)ceil_div(tiles * s, cus) * ((double)ceil_div(blocks, s) * block_us + 8.0);
+    if (s > 1) us += 4.0 + (double)(2 * s + 2) * (double)tiles * t.bm * t.bn * 8.0 / 6.0e6;
+    if (us < 0.95 * best) {
+      best = us;
+      pick = s;
+    }
+  }
+  return pick;
 }
 
 bool log_enabled() {
@@ -438,7 +460,7 @@ static famlies_status analyze_impl(int dtype, int compute, const famlies_tensor*
   if (st != FAMLIES_OK) return fail(st, err);
   if (an.M > kMaxGemmDim || an.N > kMaxGemmDim || an.K > kMaxGemmDim || an.L > kMaxGemmDim)
     return fail(FAMLIES_ERR_UNSUPPORTED, "a GEMM dimension exceeds 2^31 - 1024");
-  TileCfg t = int8_slices(an.compute) ? int8_tile() : choose_tiles(nullptr, an);
+  TileCfg t = int8_slices(an.compute) ? int8_tile(int8_slices(an.compute), an.N) : choose_tiles(nullptr, an);
   if (split_parts(an.compute) && t.tail) {  // as in make_plan: no split for the bf16 kernels
     t.split = 1;
     t.tail = 0;
@@ -449,7 +471,7 @@ static famlies_status analyze_impl(int dtype, int compute, const famlies_tensor*
   bool e32 = false;
   index_form(an, 0, &ib, &e32);
   const int64_t runs =  // as in make_plan: the padded contracted order
-      int8_slices(an.compute) || ib != 32 || e32 ? 0 : padded_k_length(an, 16 / an.esize);
+      ib != 32 || e32 ? 0 : padded_k_length(an, 16 / an.esize);
   finalize_split(&t, runs && runs <= kMaxGemmDim ? runs : an.K, ceil_div(an.M, t.bm) * ceil_div(an.N, t.bn), &kchunk,
                  &head);
   std::vector<int64_t> v[9];

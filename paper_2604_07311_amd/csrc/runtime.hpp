@@ -68,7 +68,7 @@ struct famlies_plan_s {
   int64_t kd = 0;          // K of the kernels' contracted order (padded to 16-byte runs, or the plain one)
   int xmode = 0, ymode = 0;  // loader modes of X and Y when they are not pre-packed
   famlies::LevelCfg level;  // rem > 0: the 128 x 128 kernel runs with a levelled last round instead of cfg's split
-  size_t kvoid_pos = 0;    // void mask of the contracted order (byte-offset plans of the plain and bf16 kernels)
+  size_t kvoid_pos = 0;    // void mask of the contracted order (byte-offset plans)
   famlies::DirectCfg direct;                // bm > 0: native kMain launches run the direct kernel
   bool dx_vec = false, dy_vec = false;      // every run of 16 bytes of X / Y along K is contiguous
   bool pk_fits[2] = {false, false};         // direct kernel: 32-bit offsets reach all of the pre-packed X / Y
@@ -162,8 +162,11 @@ void finalize_split(TileCfg* t, int64_t K, int64_t ntiles, int* kchunk, int* hea
 void fill_info(const Analysis& an, const TileCfg& t, int index_bits, int kernel, famlies_plan_info* info);
 // famlies_plan_info.kernel of a plan (xv, yv: affine-block loaders of X, Y).
 int kernel_code(const Analysis& an, bool xv, bool yv);
-// The fixed tile of the INT8 kernels: 128 x 64 outputs, K slices of 64.
-TileCfg int8_tile();
+// The tile of the INT8 kernels: 128 x 128 outputs up to six slices and beyond
+// 64 columns, else 128 x 64; K blocks of 64, no split.
+TileCfg int8_tile(int slices, int64_t n);
+// K ranges of an INT8 plan (contracted order of kd, one exact chunk).
+int int8_split(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd);
 // 32: uint32 byte offsets from each operand's lowest element (every operand
 // spans less than 4 GiB over its non-batch modes); 64: int64 element offsets.
 int index_bits_for(const Analysis& an);
@@ -211,11 +214,13 @@ constexpr int batch_slice_k() { return 16; }
 inline int int8_slices(int compute) {
   return compute >= FAMLIES_INT8X3 && compute <= FAMLIES_INT8X7 ? compute - FAMLIES_INT8X3 + 3 : 0;
 }
-// xmode / ymode: 0 row-gathered, 1 K-gathered, 2 K-gathered in affine blocks
-hipError_t launch_int8(const PlainArgs<uint32_t>& a, int slices, int xmode, int ymode, hipStream_t s);
-hipError_t launch_int8(const PlainArgs<int64_t>& a, int slices, int xmode, int ymode, hipStream_t s);
-// Workspace of an INT8 plan: the digit planes of X and Y and their row /
-// column exponents.
-size_t int8_work_bytes(int slices, int64_t M, int64_t N, int64_t K, int64_t L);
+// xmode / ymode: 0 row-gathered, 1 K-gathered, 2 K-gathered in 16-byte pairs
+hipError_t launch_int8(const PlainArgs<uint32_t>& a, int slices, int bn, int xmode, int ymode, hipStream_t s);
+hipError_t launch_int8(const PlainArgs<int64_t>& a, int slices, int bn, int xmode, int ymode, hipStream_t s);
+// Workspace of an INT8 plan with tiles of 128 x bn and `splits` K ranges: the
+// digit planes of X and Y, their exponents and row maxima, partial sums.
+size_t int8_work_bytes(int slices, int64_t M, int64_t N, int64_t K, int64_t L, int bn, int splits);
+// The longest K whose digit products one launch sums exactly in int32.
+int64_t int8_exact_k(int slices);
 
 }  // namespace famlies
