@@ -397,7 +397,9 @@ struct VecKGather {
   template <int S = 0>
   __device__ __forceinline__ void load(const T* __restrict__ base) {
 #pragma unroll
-    for (int i = 0; i < NR; ++i) v[S][i] = *global(reinterpret_cast<const gvec_t*>(at(base, (OffT)(mn[i] + ko[S]))));
+    for (int i = 0; i < NR; ++i) 
+      v[S][i] = *reinterpret_cast<const __attribute__((address_space(1))) gvec_t*>(
+          global(at(base, (OffT)(mn[i] + ko[S]))));
   }
   template <int S = 0>
   __device__ __forceinline__ void store(T* __restrict__ lds, int /*k0*/, int /*kend*/) const {

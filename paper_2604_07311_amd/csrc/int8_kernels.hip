@@ -143,7 +143,8 @@ struct SliceTile {
         typedef double f64x2 __attribute__((ext_vector_type(2), aligned(8)));
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const f64x2 w = *global(reinterpret_cast<const f64x2*>(at(base, (OffT)(ro + sk[k0 + 2 * h]))));
+          const f64x2 w = *reinterpret_cast<const __attribute__((address_space(1))) f64x2*>(
+            global(at(base, (OffT)(ro + sk[k0 + 2 * h]))));
           v[j][2 * h] = w[0];
           v[j][2 * h + 1] = w[1];
         }
