@@ -235,7 +235,8 @@ famlies_status famlies_batch_execute(famlies_plan p, double alpha, double beta,
  * 1 = B; src is its base pointer as for famlies_execute) into dst in the
  * plan's tile order -- blocks of tile rows x tile_k contracted indices,
  * [row][k], zero-filled past the edges, and for the split-bf16 modes already
- * split into bf16 parts -- so that famlies_execute_packed copies whole tiles
+ * split into bf16 parts (large split-bf16 plans: the part planes their kernel
+ * reads) -- so that famlies_execute_packed copies whole tiles
  * instead of gathering and splitting.  dst must hold famlies_pack_size bytes
  * and be 16-byte aligned; it is owned by the caller and valid for this plan
  * only.  UNSUPPORTED for plans whose offsets are not byte offsets (an

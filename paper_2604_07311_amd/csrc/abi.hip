@@ -298,6 +298,9 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
       finalize_split(&p->cfg, p->kd, ntiles, &p->kchunk, &p->head);
     }
   }
+  LevelCfg planes_level;
+  if (!lean && !force && !p->table_hit && ns && p->index_bits == 32 && !p->elem32)
+    p->planes = choose_planes(h, an, p->kd, level_us, &planes_level);
   if (!lean && !force && !p->table_hit && !i8 && !ns && p->index_bits == 32 && !p->elem32) {
     p->direct = choose_direct(h, an, p->cfg, level_us);
     if (p->direct.bm) {
@@ -314,7 +317,8 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   if (an.M == 0 || an.N == 0) return FAMLIES_OK;
   const int64_t mp = ceil_div(std::max<int64_t>(an.M, 1), p->cfg.bm) * p->cfg.bm;
   const int64_t np = ceil_div(std::max<int64_t>(an.N, 1), p->cfg.bn) * p->cfg.bn;
-  const int64_t kp = ceil_div(std::max<int64_t>(p->kd, 1), p->cfg.bk) * p->cfg.bk + p->cfg.bk;
+  int64_t kp = ceil_div(std::max<int64_t>(p->kd, 1), p->cfg.bk) * p->cfg.bk + p->cfg.bk;
+  if (p->planes) kp = std::max(kp, ceil_div(p->kd, 64) * 64);
   st = p->index_bits == 64 ? index_image<int64_t>(p, mp, np, kp, image)
        : p->elem32          ? index_image<int32_t>(p, mp, np, kp, image)
                             : index_image<uint32_t>(p, mp, np, kp, image);
@@ -327,6 +331,10 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
                        : (size_t)p->cfg.split * (size_t)(ntiles - p->head) * (size_t)p->cfg.bm *
                              (size_t)p->cfg.bn * (size_t)an.esize;
   }
+  if (p->planes) {
+    p->planes_level = planes_level;
+    p->work_bytes = std::max(p->work_bytes, planes_work_bytes(ns, an.M, an.N, p->kd, an.L, planes_level));
+  }
   if (p->level.rem)
     p->work_bytes = std::max(p->work_bytes, (size_t)p->level.blocks() * 128 * 128 * (ns ? 8 : (size_t)an.esize));
   if (p->direct.bm && p->direct.split > 1)
@@ -338,7 +346,7 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
 
 famlies_status make_plan(famlies_handle h, famlies_plan* out, int dtype, int compute,
                          const famlies_tensor* A, const famlies_tensor* B, const famlies_tensor* C,
-                         const TileCfg* force) {
+                         const TileCfg* force, bool lean) {
   if (!out) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_plan_contract: null output pointer");
   *out = nullptr;
   if (!h) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_plan_contract: invalid handle");
@@ -353,8 +361,18 @@ famlies_status make_plan(famlies_handle h, famlies_plan* out, int dtype, int com
     }
   } owner{&p};
   std::vector<char> image;
-  famlies_status st = prepare_plan(h, p, dtype, compute, A, B, C, force, &image);
+  famlies_status st = prepare_plan(h, p, dtype, compute, A, B, C, force, &image, lean);
   if (st != FAMLIES_OK) return st;
+  if (p->planes) {
+    const int64_t bytes = (int64_t)p->work_bytes;
+    if (h->planes_bytes.fetch_add(bytes) + bytes > kPlanesBytesMax) {
+      h->planes_bytes.fetch_sub(bytes);
+      delete p;
+      p = nullptr;
+      return make_plan(h, out, dtype, compute, A, B, C, force, true);
+    }
+    p->planes_held = bytes;
+  }
   if (!image.empty()) {
     hipError_t e = hipMalloc(&p->d_off, image.size());
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(indexing vectors)");
@@ -363,6 +381,14 @@ famlies_status make_plan(famlies_handle h, famlies_plan* out, int dtype, int com
   }
   if (p->work_bytes) {
     hipError_t e = hipMalloc(&p->d_work, p->work_bytes);
+    if (e == hipErrorOutOfMemory && p->planes) {
+      // no room for the part planes: the kernels that split while staging
+      // (their plan needs a workspace of at most the same size)
+      (void)hipGetLastError();
+      delete p;
+      p = nullptr;
+      return make_plan(h, out, dtype, compute, A, B, C, force, true);
+    }
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(split-K workspace)");
   }
   if (log_enabled()) log_plan(p);
@@ -372,7 +398,7 @@ famlies_status make_plan(famlies_handle h, famlies_plan* out, int dtype, int com
 }
 
 void log_plan(const famlies_plan_s* p) {
-  log_decision("plan", p->an, p->cfg, p->direct, p->level, p->elem32 ? -32 : p->index_bits, p->x_vec, p->y_vec, p->work_bytes,
+  log_decision("plan", p->an, p->cfg, p->direct, p->level, p->planes, p->elem32 ? -32 : p->index_bits, p->x_vec, p->y_vec, p->work_bytes,
                p->table_hit);
 }
 
@@ -387,6 +413,7 @@ void destroy_plan(famlies_plan_s* p) {
 famlies_plan_s::~famlies_plan_s() {
   if (owns_device && d_off) (void)hipFree(d_off);
   if (owns_device && d_work) (void)hipFree(d_work);
+  if (planes_held) h->planes_bytes.fetch_sub(planes_held);
   if (batch) famlies::destroy_batch(batch);
 }
 
@@ -557,7 +584,20 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
         a.y = y;
         a.y_nkb = (int32_t)((p->kd + L.bk - 1) / L.bk);
       }
-      e = launch_split(a, L, ns, s);
+      if (p->planes) {
+        const LevelCfg& lv = p->planes_level;
+        a.tiles_m = (int32_t)ceil_div(an.M, 256);
+        a.tiles_n = (int32_t)ceil_div(an.N, 128);
+        a.splits = 1;
+        a.head = lv.head;
+        a.rem = lv.rem;
+        a.lev_q = lv.q;
+        a.lev_part = lv.part;
+        a.lev_parts = lv.parts;
+        e = launch_planes(a, ns, xp ? 3 : std::min(p->xmode, 2), yp ? 3 : std::min(p->ymode, 2), s);
+      } else {
+        e = launch_split(a, L, ns, s);
+      }
     } else {
       e = launch_split(make_args<int64_t>(p, x, y, C, alpha, beta), L, ns, s);
     }

@@ -40,31 +40,20 @@ __device__ __forceinline__ int scalar(int v) { return __builtin_amdgcn_readfirst
 // What workgroup b of a levelled launch runs (args.hpp): the tile (over all
 // batch planes), its slices [s0, s1) of nk and the block of partial sums they
 // go to (-1: a whole tile, written to C).  Runs of one number are
-// neighbours, so the tiles of a moment read the same K range.
-struct LevelWork {
-  int tile, s0, s1, block;
-  template <typename Args>
-  __device__ __forceinline__ LevelWork(const Args& a, int b, int nk) {
-    if (b < a.head) {
-      tile = xcd_remap(b, a.head);
-      s0 = 0;
-      s1 = nk;
-      block = -1;
-    } else if (b < a.head + a.rem) {
-      block = xcd_remap(b - a.head, a.rem);
-      tile = a.head + block;
-      s0 = 0;
-      s1 = a.lev_q;
-    } else {
-      const int v = xcd_remap(b - a.head - a.rem, a.rem * a.lev_parts);
-      const int run = v / a.rem, i = v % a.rem;
-      tile = a.head + i;
-      s0 = a.lev_q + run * a.lev_part;
-      s1 = min(nk, s0 + a.lev_part);
-      block = a.rem + i * a.lev_parts + run;
-    }
-  }
-};
+// neighbours, so the tiles of a moment read the same K range.  Selects, no
+// branches: with branches the compiler kept these values in scratch memory.
+template <typename Args>
+__device__ __forceinline__ void level_work(const Args& a, int b, int nk, int& tile, int& s0, int& s1, int& block) {
+  const bool whole = b < a.head, first = !whole && b < a.head + a.rem;
+  const int from = whole ? 0 : first ? a.head : a.head + a.rem;
+  const int count = whole ? a.head : first ? a.rem : a.rem * a.lev_parts;
+  const int v = scalar(xcd_remap(b - from, count));
+  const int run = whole || first ? 0 : scalar(v / a.rem), i = v - run * a.rem;
+  tile = whole ? v : a.head + i;
+  s0 = whole || first ? 0 : a.lev_q + run * a.lev_part;
+  s1 = whole ? nk : first ? a.lev_q : min(nk, s0 + a.lev_part);
+  block = whole ? -1 : first ? i : a.rem + i * a.lev_parts + run;
+}
 
 // Element at `off` from `base`: uint32_t offsets count bytes (an SGPR base
 // plus a 32-bit VGPR offset per load); int32_t and int64_t offsets count

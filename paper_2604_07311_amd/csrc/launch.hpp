@@ -24,9 +24,9 @@ hipError_t launch_direct(int dtype, const PlainArgs<uint32_t>& a, const DirectCf
 // bf16: the partial sums are FP64 (split-bf16 kernels).
 template <typename OffT>
 hipError_t launch_splitk_reduce(int dtype, bool bf16, const PlainArgs<OffT>& a, int bm, int bn, hipStream_t s);
-// C from the blocks of partial sums of a levelled launch.
+// C from the blocks (bm x 128) of partial sums of a levelled launch.
 template <typename OffT>
-hipError_t launch_level_reduce(int dtype, bool bf16, const PlainArgs<OffT>& a, hipStream_t s);
+hipError_t launch_level_reduce(int dtype, bool bf16, const PlainArgs<OffT>& a, int bm, hipStream_t s);
 bool plain_tile_supported(int dtype, int bm, int bn, int bk);
 
 }  // namespace famlies

@@ -138,6 +138,10 @@ famlies_status pack_geom(famlies_plan_s* p, int operand, PackGeom* g) {
   g->rows = g->x ? an.M : an.N;
   g->tiles = (g->rows + g->br - 1) / g->br;
   g->nkb = (p->kd + g->bk - 1) / g->bk;
+  if (p->planes) {  // the part planes that the plan's kernel reads
+    g->bytes = planes_pack_bytes(ns, an.M, an.N, p->kd, an.L, g->x);
+    return FAMLIES_OK;
+  }
   const size_t es = ns ? 2 * (size_t)ns : (size_t)an.esize;
   g->bytes = (size_t)an.L * (size_t)g->tiles * (size_t)g->nkb * (size_t)g->br * (size_t)g->bk * es;
   return FAMLIES_OK;
@@ -169,8 +173,29 @@ famlies_status pack_impl(famlies_plan_s* p, int operand, const void* src, void* 
   if (!dg.ok) return fail(FAMLIES_ERR_DEVICE, "cannot select the plan's device");
   const uint32_t* o = static_cast<const uint32_t*>(p->d_off);
   const int64_t* lb = reinterpret_cast<const int64_t*>(static_cast<const char*>(p->d_off) + p->batch_off_bytes);
-  PackArgs<uint32_t> a;
   const int64_t es = an.esize;
+  if (p->planes) {
+    PlainArgs<uint32_t> q{};
+    const char* base = static_cast<const char*>(src) + (g.x ? an.x_lo : an.y_lo) * es;
+    (g.x ? q.x : q.y) = base;
+    q.xmn = o + p->off_pos[0];
+    q.xk = o + p->off_pos[1];
+    q.yk = o + p->off_pos[2];
+    q.ymn = o + p->off_pos[3];
+    q.xl = lb + p->off_pos[6];
+    q.yl = lb + p->off_pos[7];
+    q.kvoid = o + p->kvoid_pos;
+    q.M = (int32_t)an.M;
+    q.N = (int32_t)an.N;
+    q.K = (int32_t)p->kd;
+    q.L = (int32_t)an.L;
+    q.work = dst;
+    hipError_t e = launch_planes_pack(q, split_parts(an.compute), g.x, std::min(g.x ? p->xmode : p->ymode, 2),
+                                      static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return hip_fail(e, "pack kernel launch");
+    return FAMLIES_OK;
+  }
+  PackArgs<uint32_t> a;
   a.src = static_cast<const char*>(src) + (g.x ? an.x_lo : an.y_lo) * es;
   a.mn = o + p->off_pos[g.x ? 0 : 3];
   a.ko = o + p->off_pos[g.x ? 1 : 2];

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(kThreads, FAMLIES_PLAIN_WAVES_PER_EU) void plain_co
                                     : 1;
   using Tile = PlainTile<T, BM, BN, BK, XM, YM, kDepth>;
   __shared__ T smem[Tile::SMEM];
-  // Work units in launch order: with a levelled last round, LevelWork's; without
+  // Work units in launch order: with a levelled last round, level_work's; without
   // split-K, every tile of every batch plane; with split-K, first the tiles [0, head) over all of K, then each
   // remaining tile once per K slice.  Each range is spread over the XCDs in
   // contiguous blocks, so neighbouring tiles share an L2.
@@ -51,11 +51,10 @@ __global__ __launch_bounds__(kThreads, FAMLIES_PLAIN_WAVES_PER_EU) void plain_co
   int t;            // tile over all batch planes
   int block = -1;   // its block of partial sums, -1: none
   if (BM == 128 && BN == 128 && a.rem > 0) {
-    const LevelWork lw(a, (int)blockIdx.x, (a.K + BK - 1) / BK);
-    t = lw.tile;
-    block = lw.block;
-    j.kbeg = lw.s0 * BK;
-    j.kend = min(a.K, lw.s1 * BK);
+    int s0, s1;
+    level_work(a, (int)blockIdx.x, (a.K + BK - 1) / BK, t, s0, s1, block);
+    j.kbeg = s0 * BK;
+    j.kend = min(a.K, s1 * BK);
   } else if (a.splits == 1) {
     t = xcd_remap(blockIdx.x, gridDim.x);
   } else if ((int)blockIdx.x < a.head) {
@@ -134,20 +133,21 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce(PlainArgs<OffT> a, int
 // tile, its lanes consecutive columns, eight rows per thread in flight; bound
 // by HBM (partial sums read once, C read and written).
 template <typename T, typename P, typename OffT>
-__global__ __launch_bounds__(kThreads) void level_reduce(PlainArgs<OffT> a) {
-  constexpr int B = 128, RW = 16, RT = RW / 2;
-  const int i = blockIdx.x / (B / RW), row0 = (blockIdx.x % (B / RW)) * RW + threadIdx.x / B;
+__global__ __launch_bounds__(kThreads) void level_reduce(PlainArgs<OffT> a, int bm) {
+  constexpr int B = 128, RW = 16, RT = RW / 2;  // B: columns of a tile
+  const int i = blockIdx.x / (bm / RW), row0 = (blockIdx.x % (bm / RW)) * RW + threadIdx.x / B;
+  const size_t per = (size_t)bm * B;
   const int ntiles = a.tiles_m * a.tiles_n;
   const int t = a.head + i, l = t / ntiles, tl = t % ntiles;
-  const int m0 = (tl % a.tiles_m) * B + row0, n = (tl / a.tiles_m) * B + threadIdx.x % B;
+  const int m0 = (tl % a.tiles_m) * bm + row0, n = (tl / a.tiles_m) * B + threadIdx.x % B;
   const P* W = static_cast<const P*>(a.work) + (size_t)row0 * B + threadIdx.x % B;
   P s[RT];
 #pragma unroll
-  for (int q = 0; q < RT; ++q) s[q] = *global(W + (size_t)i * (B * B) + q * 2 * B);
+  for (int q = 0; q < RT; ++q) s[q] = *global(W + i * per + q * 2 * B);
   for (int w = 0; w < a.lev_parts; ++w)
 #pragma unroll
     for (int q = 0; q < RT; ++q)
-      s[q] += *global(W + ((size_t)a.rem + (size_t)i * a.lev_parts + w) * (B * B) + q * 2 * B);
+      s[q] += *global(W + ((size_t)a.rem + (size_t)i * a.lev_parts + w) * per + q * 2 * B);
   if (n >= a.N) return;
   T* C = static_cast<T*>(a.c) + a.cl[l];
   const OffT cn = a.cn[n];
@@ -171,19 +171,19 @@ __global__ __launch_bounds__(kThreads) void level_reduce(PlainArgs<OffT> a) {
 
 // bf16: the partial sums are FP64.
 template <typename OffT>
-hipError_t launch_level_reduce(int dtype, bool bf16, const PlainArgs<OffT>& a, hipStream_t s) {
-  const dim3 grid(a.rem * 8);
+hipError_t launch_level_reduce(int dtype, bool bf16, const PlainArgs<OffT>& a, int bm, hipStream_t s) {
+  const dim3 grid(a.rem * (bm / 16));
   if (dtype == FAMLIES_F64)
-    hipLaunchKernelGGL((level_reduce<double, double, OffT>), grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((level_reduce<double, double, OffT>), grid, dim3(kThreads), 0, s, a, bm);
   else if (bf16)
-    hipLaunchKernelGGL((level_reduce<float, double, OffT>), grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((level_reduce<float, double, OffT>), grid, dim3(kThreads), 0, s, a, bm);
   else
-    hipLaunchKernelGGL((level_reduce<float, float, OffT>), grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((level_reduce<float, float, OffT>), grid, dim3(kThreads), 0, s, a, bm);
   return hipGetLastError();
 }
-template hipError_t launch_level_reduce(int, bool, const PlainArgs<uint32_t>&, hipStream_t);
-template hipError_t launch_level_reduce(int, bool, const PlainArgs<int32_t>&, hipStream_t);
-template hipError_t launch_level_reduce(int, bool, const PlainArgs<int64_t>&, hipStream_t);
+template hipError_t launch_level_reduce(int, bool, const PlainArgs<uint32_t>&, int, hipStream_t);
+template hipError_t launch_level_reduce(int, bool, const PlainArgs<int32_t>&, int, hipStream_t);
+template hipError_t launch_level_reduce(int, bool, const PlainArgs<int64_t>&, int, hipStream_t);
 
 template <typename OffT>
 hipError_t launch_splitk_reduce(int dtype, bool bf16, const PlainArgs<OffT>& a, int bm, int bn, hipStream_t s) {
@@ -262,7 +262,7 @@ static hipError_t launch_plain_t(const PlainArgs<OffT>& a, const PlainLaunch& L,
     e = launch_tile<T, OffT, 128, 128, BK>(a, L.xm, L.ym, grid, s);
   else if (L.bm == 64 && L.bn == 64 && L.bk == BK)
     e = launch_tile<T, OffT, 64, 64, BK>(a, L.xm, L.ym, grid, s);
-  if (e == hipSuccess && a.rem > 0) return launch_level_reduce(sizeof(T) == 8 ? FAMLIES_F64 : FAMLIES_F32, false, a, s);
+  if (e == hipSuccess && a.rem > 0) return launch_level_reduce(sizeof(T) == 8 ? FAMLIES_F64 : FAMLIES_F32, false, a, L.bm, s);
   if (e != hipSuccess || a.splits == 1) return e;
   return launch_splitk_reduce(sizeof(T) == 8 ? FAMLIES_F64 : FAMLIES_F32, false, a, L.bm, L.bn, s);
 }

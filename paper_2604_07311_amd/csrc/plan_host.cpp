@@ -180,62 +180,110 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
 // o=27 (408 tiles) 1104 and 960 -> 924 us in five even runs, 945 uneven; FP32
 // ring o=31 v=115 981 and 894 -> 808; bf16x6 ring o=31 v=115 638 and 727 ->
 // 585; bf16x3 ring o=48 v=192 5590 -> 5500.
-LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd, bool* unsplit,
-                      double* us) {
-  LevelCfg lv;
-  *unsplit = false;
-  if (t.bm != 128 || t.bn != 128 || an.M == 0 || an.N == 0 || an.K == 0) return lv;
-  const int ns = split_parts(an.compute);
-  const int64_t cus = h ? h->num_cus : 256, slots = 2 * cus;
-  const int64_t tiles = ceil_div(an.M, 128) * ceil_div(an.N, 128) * an.L;
-  const int64_t nk = ceil_div(kd, t.bk), rem = tiles % slots, full = tiles / slots;
-  if (tiles >= ((int64_t)1 << 30)) return lv;
-  const double slice = ns ? 1.45 : an.esize == 8 ? 1.95 : 3.8, unit = 9.0;
-  const double block = 128.0 * 128.0 * (ns ? 8.0 : (double)an.esize), pass = 7.0e6;
-  // rounds of n workgroups per tile-sized unit of s slices
-  auto rounds = [&](int64_t n, double s) {
+namespace {
+struct RoundModel {
+  int bm, bn;
+  int64_t slots;               // workgroups in a round
+  double slice, unit, block;   // us per slice, us per workgroup besides, bytes of a block of partial sums
+  double lone;                 // time of a slice in a round of at most half the slots
+  // units of n workgroups of s slices each
+  double rounds(int64_t n, double s) const {
     const int64_t last = n % slots;
     return (double)(n / slots) * (s * slice + unit) +
-           (last == 0 ? 0.0 : (last > cus ? 1.0 : 0.77) * s * slice + unit);
-  };
-  const double whole = rounds(tiles, (double)nk);
-  double now = whole;
-  if (t.split > 1) {
-    const int64_t cut = t.tail ? t.tail : tiles;
-    now = rounds(tiles - cut, (double)nk) + rounds(cut * t.split, (double)ceil_div(nk, t.split)) + 4.0 +
-          (double)(2 * t.split + 2) * (double)cut * block / 4.2e6;  // splitk_reduce, one element per thread
-    if (whole < now) {
-      *unsplit = true;
-      now = whole;
-    }
+           (last == 0 ? 0.0 : (2 * last > slots ? 1.0 : lone) * s * slice + unit);
   }
-  if (rem == 0) return lv;
-  double best = 0.95 * now;
+};
+constexpr double kPassRate = 7.0e6;  // bytes of partial sums per us, written then read
+
+// The fastest levelled round for `tiles` tiles of nk slices below *best us
+// (which it lowers).
+LevelCfg level_round(const RoundModel& m, int64_t tiles, int64_t nk, double* best) {
+  LevelCfg lv;
+  const int64_t rem = tiles % m.slots, full = tiles / m.slots;
+  if (rem == 0 || tiles >= ((int64_t)1 << 30)) return lv;
   auto consider = [&](double time, int64_t q, int64_t part, int64_t parts) {
-    time += (double)full * ((double)nk * slice + unit) + 4.0 + (double)(rem * (2 * (1 + parts) + 2)) * block / pass;
-    if (time >= best) return;
-    best = *us = time;
-    *unsplit = false;
+    time += (double)full * ((double)nk * m.slice + m.unit) + 4.0 +
+            (double)(rem * (2 * (1 + parts) + 2)) * m.block / kPassRate;
+    if (time >= *best) return;
+    *best = time;
     lv.head = (int)(tiles - rem);
     lv.rem = (int)rem;
     lv.q = (int)q;
     lv.part = (int)part;
     lv.parts = (int)parts;
   };
-  const int64_t free_slots = slots - rem;
+  const int64_t free_slots = m.slots - rem;
   for (int64_t parts = 1; parts <= 7; ++parts) {
     if (nk / (parts + 1) < 4 || rem * (parts + 1) > (1 << 24)) break;
     const int64_t even = ceil_div(nk, parts + 1);
-    if (nk - parts * even >= 1) consider(rounds(rem * (parts + 1), (double)even), nk - parts * even, even, parts);
+    if (nk - parts * even >= 1) consider(m.rounds(rem * (parts + 1), (double)even), nk - parts * even, even, parts);
     // the runs take `turns` each on the free slots, the first part is as long
     // as those together
     const int64_t turns = ceil_div(rem * parts, free_slots);
-    const int64_t part = (int64_t)(((double)nk * slice - (double)(turns - 1) * unit) / (slice * (double)(turns + parts)));
+    const int64_t part =
+        (int64_t)(((double)nk * m.slice - (double)(turns - 1) * m.unit) / (m.slice * (double)(turns + parts)));
     const int64_t q = nk - parts * part;
     if (part < 4 || q <= part) continue;
-    consider(1.06 * std::max((double)q * slice + unit, (double)turns * ((double)part * slice + unit)), q, part, parts);
+    consider(1.06 * std::max((double)q * m.slice + m.unit, (double)turns * ((double)part * m.slice + m.unit)), q, part,
+             parts);
   }
   return lv;
+}
+}  // namespace
+
+LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd, bool* unsplit,
+                      double* us) {
+  *unsplit = false;
+  if (t.bm != 128 || t.bn != 128 || an.M == 0 || an.N == 0 || an.K == 0) return LevelCfg();
+  const int ns = split_parts(an.compute);
+  // a slice of the bf16 kernel: 16-deep in bf16x6; 32-deep in bf16x3, where
+  // gathered rows take their staging registers from the products
+  const double bf16 = ns == 3 ? 1.5 : an.x_kfast && an.y_kfast ? 1.55 : 1.85;
+  const RoundModel m{128, 128, 2 * (int64_t)(h ? h->num_cus : 256), ns ? bf16 : an.esize == 8 ? 1.95 : 3.8, 9.0,
+                     128.0 * 128.0 * (ns ? 8.0 : (double)an.esize), 0.77};
+  const int64_t tiles = ceil_div(an.M, 128) * ceil_div(an.N, 128) * an.L, nk = ceil_div(kd, t.bk);
+  const double whole = m.rounds(tiles, (double)nk);
+  double now = whole;
+  if (t.split > 1) {
+    const int64_t cut = t.tail ? t.tail : tiles;
+    now = m.rounds(tiles - cut, (double)nk) + m.rounds(cut * t.split, (double)ceil_div(nk, t.split)) + 4.0 +
+          (double)(2 * t.split + 2) * (double)cut * m.block / 4.2e6;  // splitk_reduce, one element per thread
+    if (whole < now) {
+      *unsplit = true;
+      now = whole;
+    }
+  }
+  double best = 0.95 * now;
+  const LevelCfg lv = level_round(m, tiles, nk, &best);
+  if (lv.rem) *unsplit = false;
+  *us = lv.rem ? best : now;
+  return lv;
+}
+
+// The pass over the operands at 5.5 TB/s and tiles of twice the size, one per
+// CU, against the estimate of the kernel that splits while staging.  Taken 7 %
+// or more below it; measured on either side of the line: bf16x3 ladder o=27
+// v=93 484 us split while staging (estimated 530 through planes), ladder o=36
+// v=110 1824 -> 1552, ring o=32 v=112 363 -> 323.
+bool choose_planes(const famlies_handle_s* h, const Analysis& an, int64_t kd, double split_us, LevelCfg* lv) {
+  if (split_us >= 1e30) return false;  // 64 x 64 tiles: operands that small are read too few times over
+  const int ns = split_parts(an.compute);
+  const int64_t tiles = ceil_div(an.M, 256) * ceil_div(an.N, 128) * an.L, nk = ceil_div(kd, 32);
+  const double pass = (double)(an.M + an.N) * (double)kd * (double)an.L * (4.0 + 2.0 * ns) / 5.5e6 + 8.0;
+  const RoundModel m{256, 128, h ? h->num_cus : 256, ns == 2 ? 1.4 : 2.3, 9.0, 256.0 * 128.0 * 8.0, 1.0};
+  double best = 0.93 * split_us - pass;
+  *lv = LevelCfg();
+  bool take = false;
+  if (m.rounds(tiles, (double)nk) < best) {
+    best = m.rounds(tiles, (double)nk);
+    take = true;
+  }
+  const LevelCfg c = level_round(m, tiles, nk, &best);
+  if (c.rem) {
+    *lv = c;
+    take = true;
+  }
+  return take;
 }
 
 bool contiguous_k_runs(const std::vector<int64_t>& ks, int64_t K, int u) {
@@ -417,7 +465,7 @@ bool log_enabled() {
 // split, index form -- index_bits 32: uint32 bytes, -32: int32 elements, 64:
 // int64 elements -- and workspace).
 void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d,
-                  const LevelCfg& lv, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit) {
+                  const LevelCfg& lv, bool planes, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit) {
   static const char* loader[4] = {"rows", "k-gather", "packed", "k-affine"};
   const int xm = an.x_kfast ? (x_vec ? 3 : 1) : 0, ym = an.y_kfast ? (y_vec ? 3 : 1) : 0;
   static const char* int8_names[8] = {"", "", "", "int8x3", "int8x4", "int8x5", "int8x6", "int8x7"};
@@ -433,13 +481,13 @@ void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, cons
   std::fprintf(stderr,
                "[famlies] %s %s/%s M=%lld N=%lld K=%lld L=%lld swapped=%d groups=%zu/%zu/%zu/%zu "
                "trace=%d diag=%d X=%s Y=%s tile=%dx%dx%d split=%d split_tiles=%d index=%s "
-               "workspace=%zu B%s%s\n",
+               "workspace=%zu B%s%s%s\n",
                what, an.dtype == FAMLIES_F64 ? "f64" : "f32", comp, (long long)an.M, (long long)an.N,
                (long long)an.K, (long long)an.L, an.swapped ? 1 : 0, an.I.size(), an.J.size(), an.P.size(),
                an.Lm.size(), an.n_trace, an.n_diag, loader[xm], loader[ym], cfg.bm, cfg.bn, cfg.bk, cfg.split,
                cfg.split > 1 ? (cfg.tail ? cfg.tail : -1) : 0,
                index_bits == 32 ? "u32-bytes" : index_bits == -32 ? "i32-elements" : "i64-elements", work_bytes,
-               table_hit ? " (tile table)" : "", direct);
+               table_hit ? " (tile table)" : "", planes ? " planes 256x128" : "", direct);
 }
 
 }  // namespace famlies
@@ -484,15 +532,18 @@ static famlies_status analyze_impl(int dtype, int compute, const famlies_tensor*
   info->index_elements = ib == 64 || e32;
   // what a plan would run instead of the tile choice reported above
   DirectCfg d;
-  LevelCfg lv;
+  LevelCfg lv, plv;
+  bool planes = false;
   if (!int8_slices(an.compute)) {
     bool unsplit = false;
     double level_us = 1e30;
     lv = choose_level(nullptr, an, t, runs ? runs : an.K, &unsplit, &level_us);
+    if (split_parts(an.compute) && ib == 32 && !e32) planes = choose_planes(nullptr, an, runs ? runs : an.K, level_us, &plv);
+    if (planes) lv = plv;
     if (!split_parts(an.compute) && ib == 32 && !e32) d = choose_direct(nullptr, an, t, level_us);
     if (d.bm) lv = LevelCfg();
   }
-  if (log_enabled()) log_decision("analyze", an, t, d, lv, e32 ? -32 : ib, xv, yv, 0, false);
+  if (log_enabled()) log_decision("analyze", an, t, d, lv, planes, e32 ? -32 : ib, xv, yv, 0, false);
   if (offs) {
     const int64_t need = 2 * an.M + 2 * an.K + 2 * an.N + 3 * an.L;
     if (offs_len < need) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_analyze: offsets buffer too short");

@@ -1,6 +1,7 @@
 // Handle, plan and tile-table objects behind the opaque C ABI pointers.
 #pragma once
 
+#include <atomic>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -49,6 +50,7 @@ struct famlies_handle_s {
   // device address of the library's static scratch array on this handle's
   // device (famlies_contract_noalloc), resolved once when the handle is made
   void* scratch = nullptr;
+  std::atomic<int64_t> planes_bytes{0};  // part planes held by the handle's plans (kPlanesBytesMax)
 };
 
 struct famlies_plan_s {
@@ -68,6 +70,9 @@ struct famlies_plan_s {
   int64_t kd = 0;          // K of the kernels' contracted order (padded to 16-byte runs, or the plain one)
   int xmode = 0, ymode = 0;  // loader modes of X and Y when they are not pre-packed
   famlies::LevelCfg level;  // rem > 0: the 128 x 128 kernel runs with a levelled last round instead of cfg's split
+  bool planes = false;     // bf16: through part planes (256 x 128 tiles)
+  famlies::LevelCfg planes_level;
+  int64_t planes_held = 0;  // bytes counted in the handle's planes_bytes
   size_t kvoid_pos = 0;    // void mask of the contracted order (byte-offset plans)
   famlies::DirectCfg direct;                // bm > 0: native kMain launches run the direct kernel
   bool dx_vec = false, dy_vec = false;      // every run of 16 bytes of X / Y along K is contiguous
@@ -107,6 +112,12 @@ famlies_status no_throw(const char* where, F&& f) {
   }
 }
 
+// Part planes are as large as the operands (1.5 times in bf16x6).  The plans
+// of a handle hold at most this much of them together, so that a long list of
+// live plans leaves the device's memory to the caller's tensors; a plan past
+// it splits while staging and needs none.
+constexpr int64_t kPlanesBytesMax = (int64_t)16 << 30;
+
 // GEMM dimensions the single-contraction kernels index with 32-bit ints.
 constexpr int64_t kMaxGemmDim = ((int64_t)1 << 31) - 1024;
 
@@ -131,7 +142,7 @@ inline famlies_plan_s* plan_of(const void* tok) {
 bool log_enabled();
 void log_plan(const famlies_plan_s* p);
 void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d,
-                  const LevelCfg& lv, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit);
+                  const LevelCfg& lv, bool planes, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit);
 
 // Internal forms of the ABI calls, on resolved objects.
 famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, const void* B, double beta,
@@ -149,10 +160,13 @@ TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_t
 DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, double level_us);
 // A levelled last round for the 128 x 128 kernel of a plan with configuration
 // t (settled) and contracted order length kd, where it beats both t and no
-// split (*us: its estimated time, else untouched); *unsplit is set where no
-// split at all is the fastest.
+// split; *unsplit is set where no split at all is the fastest.  *us: the
+// estimated time of the fastest (untouched where the model does not apply).
 LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd, bool* unsplit,
                       double* us);
+// Whether a bf16 plan whose split_contract launch is estimated at split_us
+// runs faster through part planes; *lv: its levelled round (rem == 0: none).
+bool choose_planes(const famlies_handle_s* h, const Analysis& an, int64_t kd, double split_us, LevelCfg* lv);
 // Whether every aligned run of u contracted indices is contiguous.
 bool contiguous_k_runs(const std::vector<int64_t>& ks, int64_t K, int u);
 int64_t ceil_div(int64_t a, int64_t b);
@@ -194,10 +208,12 @@ famlies_status batch_execute_impl(famlies_plan_s* p, double alpha, double beta, 
                                   const void* const* B_dev, void* const* C_dev, void* stream);
 // Tile class of the batched kernel with tile BM x BN (each 64 or 128).
 int batch_class_of(int bm, int bn);
-// Plan one contraction; `force` (may be null) overrides the tile choice.
+// Plan one contraction; `force` (may be null) overrides the tile choice;
+// lean: as the smallest scratch needs it (plain contracted order, no direct
+// kernel, levelled round or part planes).
 famlies_status make_plan(famlies_handle_s* h, famlies_plan_s** out, int dtype, int compute,
                          const famlies_tensor* A, const famlies_tensor* B, const famlies_tensor* C,
-                         const TileCfg* force);
+                         const TileCfg* force, bool lean = false);
 
 // Split-bf16 kernels: ns = 2 (bf16x3) or 3 (bf16x6) parts per operand.
 hipError_t launch_split(const PlainArgs<uint32_t>& a, const PlainLaunch& L, int ns, hipStream_t s);
@@ -205,6 +221,14 @@ hipError_t launch_split(const PlainArgs<int32_t>& a, const PlainLaunch& L, int n
 hipError_t launch_split(const PlainArgs<int64_t>& a, const PlainLaunch& L, int ns, hipStream_t s);
 bool split_tile_supported(int ns, int bm, int bn);
 inline int split_parts(int compute) { return compute == FAMLIES_BF16X6 ? 3 : compute == FAMLIES_BF16X3 ? 2 : 0; }
+// Split-bf16 through part planes (planes_kernels.hip; byte-offset plans), ns
+// parts; xmode / ymode: 0 row-gathered, 1 K-gathered, 2 in 16-byte runs, 3
+// planes written before (by launch_planes_pack: one operand, to a.work).
+hipError_t launch_planes_pack(const PlainArgs<uint32_t>& a, int ns, bool x, int mode, hipStream_t s);
+size_t planes_pack_bytes(int ns, int64_t M, int64_t N, int64_t K, int64_t L, bool x);
+hipError_t launch_planes(const PlainArgs<uint32_t>& a, int ns, int xmode, int ymode, hipStream_t s);
+// Its workspace: both operands' planes and the blocks of a levelled round.
+size_t planes_work_bytes(int ns, int64_t M, int64_t N, int64_t K, int64_t L, const LevelCfg& lv);
 // Contraction slice (BK) of the split-bf16 kernels with ns parts per operand:
 // 32 for bf16x3, 16 for bf16x6 (three part planes per operand in LDS).
 constexpr int split_slice_k(int ns) { return ns == 3 ? 16 : 32; }

@@ -280,11 +280,10 @@ __global__ __launch_bounds__(kThreads, (kSplitWgPerCu<OffT, BM, NS, XM, YM>)) vo
   const int ntiles = a.tiles_m * a.tiles_n;
   int t, block = -1, kbeg, kend;  // t: tile over all batch planes
   if (BM == 128 && BN == 128 && a.rem > 0) {
-    const LevelWork lw(a, (int)blockIdx.x, (a.K + BK - 1) / BK);
-    t = lw.tile;
-    block = lw.block;
-    kbeg = lw.s0 * BK;
-    kend = min(a.K, lw.s1 * BK);
+    int s0, s1;
+    level_work(a, (int)blockIdx.x, (a.K + BK - 1) / BK, t, s0, s1, block);
+    kbeg = s0 * BK;
+    kend = min(a.K, s1 * BK);
   } else {
     const int per_batch = ntiles * a.splits;
     const int lid0 = xcd_remap(blockIdx.x, gridDim.x);
@@ -547,7 +546,7 @@ static hipError_t launch_split_t(const PlainArgs<OffT>& a, const PlainLaunch& L,
     else if (L.bm == 64 && L.bn == 64)
       e = launch_split_tile<OffT, 64, 64, 3>(a, L.xm, L.ym, grid, s);
   }
-  if (e == hipSuccess && a.rem > 0) return launch_level_reduce(FAMLIES_F32, true, a, s);
+  if (e == hipSuccess && a.rem > 0) return launch_level_reduce(FAMLIES_F32, true, a, L.bm, s);
   if (e != hipSuccess || a.splits == 1) return e;
   return launch_splitk_reduce(FAMLIES_F32, true, a, L.bm, L.bn, s);
 }
