@@ -72,7 +72,7 @@ __host__ __device__ constexpr int batch_class_bn(int cls) { return (cls & 2) ? 1
 // batch_slice_k()).  The items are short in K (tens of slices) and their
 // operands mostly miss L2, so the loads' lead time decides: FP32 takes
 // 16-deep slices with two in flight (the lead of one 32-deep slice, in finer
-// steps).  On the 20,000-problem workload, against 32-deep slices with one
+// steps).  On the 20,000-problem workload, before the loads were spread, against 32-deep slices with one
 // in flight: 174.6 -> 166.7 ms; 16-deep with one in flight (half the lead)
 // 184.8 ms.  FP64 keeps one 16-deep slice in flight.
 __host__ __device__ constexpr int batch_depth(int esize) { return esize == 4 ? 2 : 1; }

@@ -148,6 +148,7 @@ struct Mfma<float> {  // v_mfma_f32_32x32x2_f32
 template <typename T, typename OffT, int BR, int BK, bool KFAST, int KV = 1, int NSLOT = 1, bool SCALARK = false>
 struct TileGather {
   static constexpr int E = BR * BK / kThreads;
+  static constexpr int kLoads = E;
   static constexpr int KVT = KV;                  // KFAST: consecutive k's per thread
   static constexpr int LDK = BK + 16 / (int)sizeof(T);
   static constexpr int VK = 16 / (int)sizeof(T);  // k's per 16-byte vector
@@ -179,7 +180,7 @@ struct TileGather {
       kk0 = (tid % KT) * KV;
       r0 = tid / KT;
 #pragma unroll
-      for (int i = 0; i < E / KV; ++i) mn[i] = mnoff[tile_r0 + r0 + i * RSTEP];
+      for (int i = 0; i < E / KV; ++i) mn[i] = *global(mnoff + tile_r0 + r0 + i * RSTEP);
     } else {
       r0 = tid % BR;
       // The k run is the same for a whole wave, but its offsets are fetched
@@ -187,7 +188,7 @@ struct TileGather {
       // counter, and every wait for an MFMA operand read would then also wait
       // for the offsets of a slice two steps ahead.
       kk0 = SK ? scalar((tid / BR) * E) : (tid / BR) * E;
-      mn[0] = mnoff[tile_r0 + r0];
+      mn[0] = *global(mnoff + tile_r0 + r0);
     }
   }
 
@@ -198,10 +199,10 @@ struct TileGather {
   template <int S = 0>
   __device__ __forceinline__ void fetch_k(const OffT* __restrict__ koff, int k0) {
     if constexpr (SK) {
-      ko[S][0] = koff[k0 + kk0 + threadIdx.x % E];
+      ko[S][0] = *global(koff + k0 + kk0 + threadIdx.x % E);
     } else if constexpr (!KFAST && E % OV == 0) {
       typedef OffT ovec_t __attribute__((ext_vector_type(16 / sizeof(OffT))));
-      const ovec_t* src = reinterpret_cast<const ovec_t*>(koff + k0 + kk0);
+      const auto* src = global(reinterpret_cast<const ovec_t*>(koff + k0 + kk0));
 #pragma unroll
       for (int q = 0; q < E / OV; ++q) {
         const ovec_t w = src[q];
@@ -210,7 +211,7 @@ struct TileGather {
       }
     } else {
 #pragma unroll
-      for (int u = 0; u < (KFAST ? KV : E); ++u) ko[S][u] = koff[k0 + kk0 + u];
+      for (int u = 0; u < (KFAST ? KV : E); ++u) ko[S][u] = *global(koff + k0 + kk0 + u);
     }
   }
 
@@ -301,6 +302,7 @@ struct PackedGather {
   static constexpr int LDK = BK + VK;
   static constexpr int NV = BR * BK / VK;  // vectors per block
   static constexpr int VPT = NV / kThreads;
+  static constexpr int kLoads = VPT;
   static_assert(NV % kThreads == 0 && BK % VK == 0, "packed block does not divide the workgroup");
   typedef T vec_t __attribute__((ext_vector_type(16 / sizeof(T))));
   vec_t v[NSLOT][VPT];
@@ -365,6 +367,7 @@ struct VecKGather {
   static constexpr int KT = BK / VK;           // threads along k
   static constexpr int RSTEP = kThreads / KT;  // rows between a thread's runs
   static constexpr int NR = BR / RSTEP;        // runs per thread
+  static constexpr int kLoads = NR;
   static_assert(BK % VK == 0 && kThreads % KT == 0 && BR % RSTEP == 0, "tile shape does not divide the workgroup");
   typedef T vec_t __attribute__((ext_vector_type(16 / sizeof(T))));
   typedef T gvec_t __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
@@ -377,11 +380,11 @@ struct VecKGather {
     kk0 = (tid % KT) * VK;
     r0 = tid / KT;
 #pragma unroll
-    for (int i = 0; i < NR; ++i) mn[i] = mnoff[tile_r0 + r0 + i * RSTEP];
+    for (int i = 0; i < NR; ++i) mn[i] = *global(mnoff + tile_r0 + r0 + i * RSTEP);
   }
   template <int S = 0>
   __device__ __forceinline__ void fetch_k(const OffT* __restrict__ koff, int k0) {
-    ko[S] = koff[k0 + kk0];
+    ko[S] = *global(koff + k0 + kk0);
   }
   template <int S = 0>
   __device__ __forceinline__ void load(const T* __restrict__ base) {

@@ -72,6 +72,29 @@ struct PlainTile {
     }
   }
 
+  // Order of a step's instructions: the loads of the next slice spread between
+  // the matrix products of this one.  In one burst, gathers of short runs (up
+  // to 64 lines of L1 per load) back up in the memory pipeline, and a wave
+  // that waits to issue a load issues no product either.  Over the whole step
+  // where the loads are many (FP32 with an operand gathered by elements), over
+  // its first half else: few loads queue little, and the late ones are waited
+  // for at the store (FP64 ladder o=32 v=128: 8.02 ms in one burst, 8.47 over
+  // the whole step, 7.78 over half of it; FP32 ring o=31 v=115 820, 787 and
+  // 797 us).  Also 2,000 uneven FP32 problems 17.35 -> 16.5 ms, FP64 ladder
+  // o=25 v=75 760 -> 717 us.
+  template <typename OffT>
+  __device__ __forceinline__ static void spread() {
+    constexpr int loads = GX<OffT>::kLoads + GY<OffT>::kLoads;
+    constexpr bool gathers = XM == kRowGather || XM == kKGather || YM == kRowGather || YM == kKGather;
+    constexpr int products = MB * NB * KPG / (sizeof(T) == 4 && gathers ? 1 : 2);
+    constexpr int per = products / loads > 0 ? products / loads : 1;
+#pragma unroll
+    for (int i = 0; i < loads; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);   // one global load
+      __builtin_amdgcn_sched_group_barrier(0x8, per, 0);  // its share of the products
+    }
+  }
+
   template <typename OffT>
   __device__ __forceinline__ static void run(const TileJob<OffT>& j, T* smem) {
     const int tid = threadIdx.x;
@@ -127,22 +150,20 @@ struct PlainTile {
         }
         store(slot0, smem, j.kbeg);
         __syncthreads();
-        for (int it = 0; it < nk; ++it) {
-          const int cur = it & 1;
-          const bool more = it + 1 < nk;
-          if (more) {
-            load(slot0, j.kbeg + (it + 1) * BK);
-            if (it + 2 < nk) {
-              gx.fetch_k(j.xk, j.kbeg + (it + 2) * BK);
-              gy.fetch_k(j.yk, j.kbeg + (it + 2) * BK);
-            }
-          }
+        // the last slice apart: one path through the loop, so that its loads
+        // and products can be interleaved
+        const int klast = j.kbeg + (nk - 1) * BK;
+        for (int it = 0; it + 1 < nk; ++it) {
+          const int cur = it & 1, k2 = j.kbeg + (it + 2) * BK;
+          load(slot0, j.kbeg + (it + 1) * BK);
+          gx.fetch_k(j.xk, k2 < klast ? k2 : klast);
+          gy.fetch_k(j.yk, k2 < klast ? k2 : klast);
           multiply(smem + cur * (XS + YS), wm, wn, g, r, acc);
-          if (more) {
-            store(slot0, smem + (cur ^ 1) * (XS + YS), j.kbeg + (it + 1) * BK);
-          }
+          spread<OffT>();
+          store(slot0, smem + (cur ^ 1) * (XS + YS), j.kbeg + (it + 1) * BK);
           __syncthreads();
         }
+        multiply(smem + ((nk - 1) & 1) * (XS + YS), wm, wn, g, r, acc);
       }
     } else if (nk > 0) {
       // DEPTH 2: slice s lives in register slot s % 2 and LDS buffer s % 2;
@@ -171,6 +192,7 @@ struct PlainTile {
         gx.template fetch_k<S ^ 1>(j.xk, kc(j.kbeg + (it + 3) * BK));
         gy.template fetch_k<S ^ 1>(j.yk, kc(j.kbeg + (it + 3) * BK));
         multiply(smem + S * (XS + YS), wm, wn, g, r, acc);
+        spread<OffT>();
         if (it + 1 < nk) {
           store(std::integral_constant<int, S ^ 1>{}, smem + (S ^ 1) * (XS + YS), j.kbeg + (it + 1) * BK);
         }
@@ -196,12 +218,12 @@ struct PlainTile {
 #pragma unroll
         for (int e = 0; e < MF::NACC; ++e) {
           const int m = j.m0 + wm * WTM + i * MF::BS + MF::row(lane, e);
-          cmv[i][e] = j.cm[m < j.M ? m : 0];
+          cmv[i][e] = *global(j.cm + (m < j.M ? m : 0));
         }
 #pragma unroll
       for (int jj = 0; jj < NB; ++jj) {
         const int n = j.n0 + wn * WTN + jj * MF::BS + r;
-        cnv[jj] = j.cn[n < j.N ? n : 0];
+        cnv[jj] = *global(j.cn + (n < j.N ? n : 0));
       }
 #pragma unroll
       for (int jj = 0; jj < NB; ++jj) {
