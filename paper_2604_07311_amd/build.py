@@ -14,8 +14,8 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libfamlies.so")
 OBJDIR = os.path.join(HERE, "_build")
 
-SOURCES = ["abi.hip", "planner.cpp", "table.cpp", "plain_kernels.hip", "direct_kernels.hip", "split_kernels.hip", "planes_kernels.hip",
-           "batch.hip", "tune.hip", "pack_kernels.hip", "network.cpp", "registry.cpp", "plan_host.cpp", "int8_kernels.hip"]
+SOURCES = ["abi.hip", "planner.cpp", "table.cpp", "plain_kernels.hip", "direct_kernels.hip", "split_kernels.hip",
+           "planes_kernels.hip", "batch.hip", "tune.hip", "pack_kernels.hip", "network.cpp", "registry.cpp", "plan_host.cpp", "int8_kernels.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CXX = os.environ.get("FAMLIES_CXX", "/opt/rocm/lib/llvm/bin/clang++")

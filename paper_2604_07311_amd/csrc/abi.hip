@@ -240,7 +240,7 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   p->h = h;
   p->an = an;
   const int i8 = int8_slices(compute);
-  p->cfg = i8 ? int8_tile(i8, an.N) : force ? *force : choose_tiles(h, an, &p->table_hit);
+  p->cfg = i8 ? int8_tile(i8, lean ? 64 : an.N) : force ? *force : choose_tiles(h, an, &p->table_hit);
   if (i8 && force) p->cfg.index_bits = force->index_bits;
   index_form(an, p->cfg.index_bits, &p->index_bits, &p->elem32);
   const int ns = split_parts(compute);
@@ -249,7 +249,8 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
       lean || p->index_bits != 32 || p->elem32 ? 0 : padded_k_length(an, 16 / an.esize);
   p->kd = runs && runs <= lim ? runs : an.K;
   if (i8) {
-    // int8_tile, no tile table; K ranges where tiles are few
+    // int8_tile (the narrow one in a lean plan: it pads N least), no tile table;
+    // K ranges where tiles are few
     if (!lean && an.L == 1 && p->kd <= int8_exact_k(i8)) p->cfg.split = int8_split(h, an, p->cfg, p->kd);
   } else if (ns) {
     // the bf16 kernels split every tile or none: a tail split becomes none
