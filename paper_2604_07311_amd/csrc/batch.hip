@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kThreads, 2) void batch_contract(BatchArgs a) {
     const int flags = uniform(P.flags);
     const bool swapped = flags & 1;
     const int cls = flags >> 8;
-    const uint32_t* o = uniform(a.pool + P.off);
+    const uint32_t* o = a.pool + uniform(P.off);  // from the kernel's argument: read with global, not flat, loads
     TileJob<uint32_t> j;
     j.x = uniform(static_cast<const T*>(swapped ? a.B[prob] : a.A[prob]) + P.xlo);
     j.y = uniform(static_cast<const T*>(swapped ? a.A[prob] : a.B[prob]) + P.ylo);

@@ -75,18 +75,21 @@ struct PlainTile {
   // Order of a step's instructions: the loads of the next slice spread between
   // the matrix products of this one.  In one burst, gathers of short runs (up
   // to 64 lines of L1 per load) back up in the memory pipeline, and a wave
-  // that waits to issue a load issues no product either.  Over the whole step
-  // where the loads are many (FP32 with an operand gathered by elements), over
-  // its first half else: few loads queue little, and the late ones are waited
-  // for at the store (FP64 ladder o=32 v=128: 8.02 ms in one burst, 8.47 over
-  // the whole step, 7.78 over half of it; FP32 ring o=31 v=115 820, 787 and
-  // 797 us).  Also 2,000 uneven FP32 problems 17.35 -> 16.5 ms, FP64 ladder
-  // o=25 v=75 760 -> 717 us.
+  // that waits to issue a load issues no product either.  FP32 with an operand
+  // gathered by elements or pre-packed: over the whole step; FP64, with half
+  // the loads per product: over its first half, since the late ones are waited
+  // for at the store (ladder o=32 v=128 8.02 ms in one burst, 8.47 over the
+  // whole step, 7.6 to 7.8 over half of it).  FP32 with both operands in
+  // 16-byte runs is left to the compiler, which puts its few loads late (ladder
+  // o=24 v=96 847 us against 860 spread).  Measured: FP32 ring o=31 v=115 825
+  // -> 782 us, FP64 ladder o=25 v=75 760 -> 717, 2,000 uneven FP32 problems
+  // 17.4 -> 16.9 ms with the compiler's order of the rest unchanged.
   template <typename OffT>
   __device__ __forceinline__ static void spread() {
     constexpr int loads = GX<OffT>::kLoads + GY<OffT>::kLoads;
-    constexpr bool gathers = XM == kRowGather || XM == kKGather || YM == kRowGather || YM == kKGather;
-    constexpr int products = MB * NB * KPG / (sizeof(T) == 4 && gathers ? 1 : 2);
+    constexpr bool runs = (XM == kVecK || XM == kRunK) && (YM == kVecK || YM == kRunK);
+    if constexpr (sizeof(T) == 4 && runs) return;
+    constexpr int products = MB * NB * KPG / (sizeof(T) == 4 ? 1 : 2);
     constexpr int per = products / loads > 0 ? products / loads : 1;
 #pragma unroll
     for (int i = 0; i < loads; ++i) {
@@ -218,12 +221,12 @@ struct PlainTile {
 #pragma unroll
         for (int e = 0; e < MF::NACC; ++e) {
           const int m = j.m0 + wm * WTM + i * MF::BS + MF::row(lane, e);
-          cmv[i][e] = *global(j.cm + (m < j.M ? m : 0));
+          cmv[i][e] = j.cm[m < j.M ? m : 0];
         }
 #pragma unroll
       for (int jj = 0; jj < NB; ++jj) {
         const int n = j.n0 + wn * WTN + jj * MF::BS + r;
-        cnv[jj] = *global(j.cn + (n < j.N ? n : 0));
+        cnv[jj] = j.cn[n < j.N ? n : 0];
       }
 #pragma unroll
       for (int jj = 0; jj < NB; ++jj) {
