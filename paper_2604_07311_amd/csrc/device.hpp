@@ -428,8 +428,17 @@ __device__ __forceinline__ uint32_t void_bits(uint32_t word, int k0) {
 
 // Operand loaders by mode: 0 row-gathered, 1 K-gathered, 2 pre-packed,
 // 3 K-gathered in 16-byte runs, every slice whole, 4 the same under the
-// plan's void mask (its partner is then stored under the mask too).
+// plan's void mask.
 enum { kRowGather = 0, kKGather = 1, kPacked = 2, kVecK = 3, kRunK = 4 };
+// Whether both operands of a slice are stored under the void mask: with an
+// operand in masked runs, and for an operand gathered by elements beside a
+// pre-packed one, whose plan may have the padded contracted order -- the
+// packed side holds 0 at a void entry, and the partner's real value there
+// must not meet it (0 * Inf).
+constexpr bool masked_modes(int xm, int ym) {
+  return xm == kRunK || ym == kRunK || (xm == kPacked && (ym == kRowGather || ym == kKGather)) ||
+         (ym == kPacked && (xm == kRowGather || xm == kKGather));
+}
 template <int MODE>
 constexpr bool known_mode() {
   static_assert(MODE >= kRowGather && MODE <= kRunK, "unknown loader mode");

@@ -331,7 +331,7 @@ __global__ __launch_bounds__(kThreads, (kSplitWgPerCu<OffT, BM, NS, XM, YM>)) vo
       for (int j = 0; j < NB; ++j) acc[o][i][j] = f32x16{};
 
   const int g = lane / 32, r = lane % 32;
-  constexpr bool kMasked = XM == kRunK || YM == kRunK;
+  constexpr bool kMasked = masked_modes(XM, YM);
   uint32_t vw[DEPTH] = {};  // word of the void mask of the slice in each register slot
   auto stage_load = [&](auto sc, int k0) {
     constexpr int S = decltype(sc)::value;

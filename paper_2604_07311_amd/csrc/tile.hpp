@@ -23,7 +23,7 @@ struct TileJob {
   const OffT* ymn;
   const OffT* cm;
   const OffT* cn;
-  const uint32_t* kvoid;  // void mask of the contracted order (loader mode kRunK)
+  const uint32_t* kvoid;  // void mask of the contracted order (masked_modes)
   int M, N;
   int m0, n0, kbeg, kend;
   double alpha, beta;
@@ -50,7 +50,7 @@ struct PlainTile {
   static constexpr int WTM = BM / 2, WTN = BN / 2;
   static constexpr int MB = WTM / MF::BS, NB = WTN / MF::BS;
   static constexpr int KPG = BK / MF::KG;
-  static constexpr bool kMasked = XM == kRunK || YM == kRunK;
+  static constexpr bool kMasked = masked_modes(XM, YM);
   static_assert(MB >= 1 && NB >= 1 && BK % MF::KG == 0, "bad tile");
   static_assert(DEPTH == 1 || DEPTH == 2, "pipeline depth 1 or 2");
 
