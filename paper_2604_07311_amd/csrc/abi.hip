@@ -289,10 +289,11 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   finalize_split(&p->cfg, p->kd, ntiles, &p->kchunk, &p->head);
   if (ntiles * p->cfg.split * an.L >= ((int64_t)1 << 31))
     return fail(FAMLIES_ERR_UNSUPPORTED, "the tile grid exceeds 2^31 workgroups");
+  const ChainCfg chain = plan_chain(an, p->cfg, p->kd, ntiles, p->kchunk);
   double level_us = 1e30;
   if (!lean && !force && !p->table_hit && !i8) {
     bool unsplit = false;
-    p->level = choose_level(h, an, p->cfg, p->kd, &unsplit, &level_us);
+    p->level = choose_level(h, an, p->cfg, p->kd, chain, &unsplit, &level_us);
     if (unsplit) {
       p->cfg.split = 1;
       p->cfg.tail = 0;
@@ -301,9 +302,9 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   }
   LevelCfg planes_level;
   if (!lean && !force && !p->table_hit && ns && p->index_bits == 32 && !p->elem32)
-    p->planes = choose_planes(h, an, p->kd, level_us, &planes_level);
+    p->planes = choose_planes(h, an, p->kd, chain, level_us, &planes_level, &p->planes_fold);
   if (!lean && !force && !p->table_hit && !i8 && !ns && p->index_bits == 32 && !p->elem32) {
-    p->direct = choose_direct(h, an, p->cfg, level_us);
+    p->direct = choose_direct(h, an, p->cfg, chain, level_us);
     if (p->direct.bm) {
       p->level = LevelCfg();
       const int ks = 64 / an.esize;
@@ -334,7 +335,7 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   }
   if (p->planes) {
     p->planes_level = planes_level;
-    p->work_bytes = std::max(p->work_bytes, planes_work_bytes(ns, an.M, an.N, p->kd, an.L, planes_level));
+    p->work_bytes = std::max(p->work_bytes, planes_work_bytes(ns, an.M, an.N, p->kd, an.L, planes_level, p->planes_fold));
   }
   if (p->level.rem)
     p->work_bytes = std::max(p->work_bytes, (size_t)p->level.blocks() * 128 * 128 * (ns ? 8 : (size_t)an.esize));
@@ -399,7 +400,8 @@ famlies_status make_plan(famlies_handle h, famlies_plan* out, int dtype, int com
 }
 
 void log_plan(const famlies_plan_s* p) {
-  log_decision("plan", p->an, p->cfg, p->direct, p->level, p->planes, p->elem32 ? -32 : p->index_bits, p->x_vec, p->y_vec, p->work_bytes,
+  log_decision("plan", p->an, p->cfg, p->direct, p->planes ? p->planes_level : p->level, p->planes, p->planes_fold,
+               p->elem32 ? -32 : p->index_bits, p->x_vec, p->y_vec, p->work_bytes,
                p->table_hit);
 }
 
@@ -595,7 +597,8 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
         a.lev_q = lv.q;
         a.lev_part = lv.part;
         a.lev_parts = lv.parts;
-        e = launch_planes(a, ns, xp ? 3 : std::min(p->xmode, 2), yp ? 3 : std::min(p->ymode, 2), s);
+        e = launch_planes(a, ns, xp ? 3 : std::min(p->xmode, 2), yp ? 3 : std::min(p->ymode, 2),
+                          p->planes_fold, s);
       } else {
         e = launch_split(a, L, ns, s);
       }

@@ -85,12 +85,16 @@ struct DirectOperand {
   }
 };
 
-template <typename T, int MB, int NB, bool XV, bool YV, int NW>
+// CH: accumulator sets a wave takes its K steps in, in turn.  Three where the
+// planner needs the chains of additions short (DirectCfg); their registers
+// cost a wave per SIMD in the FP64 tiles of four blocks, so not elsewhere.
+template <typename T, int MB, int NB, bool XV, bool YV, int NW, int CH>
 __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a, int wk, int64_t xplane,
                                                            int64_t yplane) {
   using MF = Mfma16<T>;
   constexpr int U = 16 / (int)sizeof(T), KS = 4 * U, BM = 16 * MB, BN = 16 * NB;
   constexpr int D = 3;
+  static_assert(CH == 1 || CH == D, "one chain, or one per register slot");
   __shared__ T part[NW * BM * BN];
   const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int g = lane / 16, r = lane % 16;
@@ -113,11 +117,13 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
   DirectOperand<T, NB, YV, D> gy;
   gx.init(a.xmn, m0 + r);
   gy.init(a.ymn, n0 + r);
-  typename MF::Acc acc[MB][NB];
+  typename MF::Acc acc[CH][MB][NB];
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+  for (int c = 0; c < CH; ++c)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = typename MF::Acc{};
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[c][i][j] = typename MF::Acc{};
 
   const int ns = (kend - kbeg + KS - 1) / KS;                // K steps of the unit
   const int n = ns > wki ? (ns - wki + wk - 1) / wk : 0;     // this wave's
@@ -173,7 +179,7 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
-          for (int j = 0; j < NB; ++j) acc[i][j] = MF::mma(gx.v[S][i][u], gy.v[S][j][u], acc[i][j]);
+          for (int j = 0; j < NB; ++j) acc[S % CH][i][j] = MF::mma(gx.v[S][i][u], gy.v[S][j][u], acc[S % CH][i][j]);
       load(sc, it + D);
       gx.template fetch<S>(a.xk, kof(it + 2 * D));
       gy.template fetch<S>(a.yk, kof(it + 2 * D));
@@ -185,6 +191,12 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
     }
   }
 
+#pragma unroll
+  for (int c = 1; c < CH; ++c)
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[0][i][j] += acc[c][i][j];
   T* __restrict__ C = static_cast<T*>(a.c) + a.cl[l];
   const T al = static_cast<T>(a.alpha), be = static_cast<T>(a.beta);
   T* __restrict__ W = a.splits > 1 ? static_cast<T*>(a.work) + ((size_t)split * ntiles + t) * (size_t)(BM * BN) : nullptr;
@@ -214,7 +226,7 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
         for (int e = 0; e < 4; ++e) {
           const int m = m0 + 16 * i + MF::row(lane, e), nn = n0 + 16 * j + r;
           if (m < a.M && nn < a.N) {
-            T v = al * acc[i][j][e];
+            T v = al * acc[0][i][j][e];
             if (be != T(0)) v += be * cv[i][j][e];
             *global(at(C, cmv[i][e] + cnv[j])) = v;
           }
@@ -228,7 +240,7 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        part[wave * (BM * BN) + (16 * i + MF::row(lane, e)) * BN + 16 * j + r] = acc[i][j][e];
+        part[wave * (BM * BN) + (16 * i + MF::row(lane, e)) * BN + 16 * j + r] = acc[0][i][j][e];
   __syncthreads();
   constexpr int PER = (BM * BN + 64 * NW - 1) / (64 * NW);
 #pragma unroll
@@ -255,7 +267,10 @@ static hipError_t launch_nw(const PlainArgs<uint32_t>& a, const DirectCfg& d, in
                             hipStream_t s) {
   const int64_t units = (int64_t)a.tiles_m * a.tiles_n * a.splits * a.L;
   const int grid = (int)(d.wk == 1 ? (units + 3) / 4 : units);
-  hipLaunchKernelGGL((direct_contract<T, MB, NB, XV, YV, 4>), dim3(grid), dim3(256), 0, s, a, d.wk, xplane, yplane);
+  if (d.chains == 3)
+    hipLaunchKernelGGL((direct_contract<T, MB, NB, XV, YV, 4, 3>), dim3(grid), dim3(256), 0, s, a, d.wk, xplane, yplane);
+  else
+    hipLaunchKernelGGL((direct_contract<T, MB, NB, XV, YV, 4, 1>), dim3(grid), dim3(256), 0, s, a, d.wk, xplane, yplane);
   return hipGetLastError();
 }
 

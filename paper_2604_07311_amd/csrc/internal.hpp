@@ -106,8 +106,19 @@ struct TileCfg {
 // Configuration of the direct kernel (small and narrow problems): tile
 // bm x bn per wave, wk waves of a workgroup sharing a tile along K, K ranges
 // over workgroups.  bm == 0: the plan runs the LDS-tiled kernel.
+// A sum over K rounds as often as its longest chain of additions into one
+// accumulator is long: chains (1 or 3) accumulators per wave, taken in turn.
 struct DirectCfg {
-  int bm = 0, bn = 0, wk = 4, split = 1, kchunk = 0;
+  int bm = 0, bn = 0, wk = 4, split = 1, kchunk = 0, chains = 1;
+};
+
+// The longest chain of additions into one accumulator that a plan's tile
+// choice gives (length, in contracted entries) and the tiles at the end of
+// the tile order that it holds for (cut; 0: none is cut, the chain is all of
+// K).  The other kernels and rounds a plan may take instead keep to it, so
+// that their error against exact sums is not larger.
+struct ChainCfg {
+  int64_t length = 0, cut = 0;
 };
 
 // Levelled last round of the 128 x 128 kernels: the `rem` tiles that do not

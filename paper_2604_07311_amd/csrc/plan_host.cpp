@@ -109,7 +109,13 @@ TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_t
 // 42 -> 31, FP64 16 x 675840 x 64 142 -> 108; the other way FP32 256 x 4096 x
 // 4096 takes 78 tiled and 125 direct, so direct is not considered above 4
 // GFLOP except for narrow problems.
-DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, double level_us) {
+//
+// Chains (ChainCfg): a wave that takes K in one accumulator, against the tiled
+// kernel's K ranges, had up to 1.5 times the error in FP32 (ladder v=36 o=9,
+// 2.1e-7 -> 3.2e-7); with three, and no chain longer than the ranges', it has
+// no more.
+DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, const ChainCfg& chain,
+                        double level_us) {
   DirectCfg none;
   if (an.M == 0 || an.N == 0 || an.K == 0) return none;
   const double flops = 2.0 * (double)an.M * (double)an.N * (double)an.K * (double)an.L;
@@ -157,12 +163,16 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
         double us = 4.0 + std::max(std::max(std::ceil(steps / wk) * step_us, mfma_us), std::max(l2_us, mem_us));
         if (wk > 1) us += 0.0012 * n;  // the waves' partial tiles through LDS
         if (split > 1) us += 4.0 + (double)(split + 1) * (double)an.M * (double)an.N * es / 4.0e6;
+        const int64_t of_wave = ceil_div((int64_t)steps, wk);
+        const int chains = std::min(of_wave * ks, K) <= chain.length ? 1 : 3;
+        if (chains == 3 && ceil_div(of_wave, 3) * ks > chain.length) continue;
         if (us < best_us) {
           best_us = us;
           best.bm = sh[0];
           best.bn = sh[1];
           best.wk = wk;
           best.split = split;
+          best.chains = chains;
         }
       }
   return best;
@@ -196,12 +206,16 @@ struct RoundModel {
 constexpr double kPassRate = 7.0e6;  // bytes of partial sums per us, written then read
 
 // The fastest levelled round for `tiles` tiles of nk slices below *best us
-// (which it lowers).
-LevelCfg level_round(const RoundModel& m, int64_t tiles, int64_t nk, double* best) {
+// (which it lowers).  The last `cut` tiles run in parts of at most `chain`
+// slices each: where they are more than the last round's, all of them are
+// levelled, evenly.
+LevelCfg level_round(const RoundModel& m, int64_t tiles, int64_t nk, int64_t cut, int64_t chain, double* best) {
   LevelCfg lv;
-  const int64_t rem = tiles % m.slots, full = tiles / m.slots;
+  const bool all = cut > tiles % m.slots;
+  const int64_t rem = all ? tiles : tiles % m.slots, full = all ? 0 : tiles / m.slots;
   if (rem == 0 || tiles >= ((int64_t)1 << 30)) return lv;
   auto consider = [&](double time, int64_t q, int64_t part, int64_t parts) {
+    if (cut > 0 && std::max(q, part) > chain) return;
     time += (double)full * ((double)nk * m.slice + m.unit) + 4.0 +
             (double)(rem * (2 * (1 + parts) + 2)) * m.block / kPassRate;
     if (time >= *best) return;
@@ -213,10 +227,11 @@ LevelCfg level_round(const RoundModel& m, int64_t tiles, int64_t nk, double* bes
     lv.parts = (int)parts;
   };
   const int64_t free_slots = m.slots - rem;
-  for (int64_t parts = 1; parts <= 7; ++parts) {
+  for (int64_t parts = 1; parts <= (cut > 0 ? 15 : 7); ++parts) {
     if (nk / (parts + 1) < 4 || rem * (parts + 1) > (1 << 24)) break;
     const int64_t even = ceil_div(nk, parts + 1);
     if (nk - parts * even >= 1) consider(m.rounds(rem * (parts + 1), (double)even), nk - parts * even, even, parts);
+    if (free_slots <= 0) continue;
     // the runs take `turns` each on the free slots, the first part is as long
     // as those together
     const int64_t turns = ceil_div(rem * parts, free_slots);
@@ -231,8 +246,24 @@ LevelCfg level_round(const RoundModel& m, int64_t tiles, int64_t nk, double* bes
 }
 }  // namespace
 
-LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd, bool* unsplit,
-                      double* us) {
+ChainCfg plan_chain(const Analysis& an, const TileCfg& t, int64_t kd, int64_t ntiles, int kchunk) {
+  ChainCfg c;
+  c.length = std::max<int64_t>(kd, 1);
+  if (t.split <= 1) return c;
+  c.length = kchunk;
+  c.cut = t.tail ? t.tail : ntiles * an.L;
+  // bf16x3 drops the product of the low parts, an error that does not shrink
+  // with shorter chains: at 12544 entries in one chain and in four ranges it
+  // is the same (3.8e-6; the chain's own share is 3e-7).
+  if (split_parts(an.compute) == 2 && kd <= 12544) {
+    c.length = kd;
+    c.cut = 0;
+  }
+  return c;
+}
+
+LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd,
+                      const ChainCfg& chain, bool* unsplit, double* us) {
   *unsplit = false;
   if (t.bm != 128 || t.bn != 128 || an.M == 0 || an.N == 0 || an.K == 0) return LevelCfg();
   const int ns = split_parts(an.compute);
@@ -248,13 +279,15 @@ LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileC
     const int64_t cut = t.tail ? t.tail : tiles;
     now = m.rounds(tiles - cut, (double)nk) + m.rounds(cut * t.split, (double)ceil_div(nk, t.split)) + 4.0 +
           (double)(2 * t.split + 2) * (double)cut * m.block / 4.2e6;  // splitk_reduce, one element per thread
-    if (whole < now) {
+    if (whole < now && chain.cut == 0) {
       *unsplit = true;
       now = whole;
     }
   }
-  double best = 0.95 * now;
-  const LevelCfg lv = level_round(m, tiles, nk, &best);
+  // 5 % for the estimates' error; 2 % against K ranges, whose launch differs
+  // from parts of the same length only in the reduction
+  double best = (chain.cut ? 0.98 : 0.95) * now;
+  const LevelCfg lv = level_round(m, tiles, nk, chain.cut, chain.length / t.bk, &best);
   if (lv.rem) *unsplit = false;
   *us = lv.rem ? best : now;
   return lv;
@@ -265,12 +298,22 @@ LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileC
 // or more below it; measured on either side of the line: bf16x3 ladder o=27
 // v=93 484 us split while staging (estimated 530 through planes), ladder o=36
 // v=110 1824 -> 1552, ring o=32 v=112 363 -> 323.
-bool choose_planes(const famlies_handle_s* h, const Analysis& an, int64_t kd, double split_us, LevelCfg* lv) {
+//
+// A plan that splits every tile along K keeps its chains here by folds
+// (ChainCfg): 13 us per fold and round.
+bool choose_planes(const famlies_handle_s* h, const Analysis& an, int64_t kd, const ChainCfg& chain, double split_us,
+                   LevelCfg* lv, int* fold) {
+  *fold = 0;
   if (split_us >= 1e30) return false;  // 64 x 64 tiles: operands that small are read too few times over
   const int ns = split_parts(an.compute);
   const int64_t tiles = ceil_div(an.M, 256) * ceil_div(an.N, 128) * an.L, nk = ceil_div(kd, 32);
   const double pass = (double)(an.M + an.N) * (double)kd * (double)an.L * (4.0 + 2.0 * ns) / 5.5e6 + 8.0;
-  const RoundModel m{256, 128, h ? h->num_cus : 256, ns == 2 ? 1.4 : 2.3, 9.0, 256.0 * 128.0 * 8.0, 1.0};
+  if (chain.cut > 0) {
+    *fold = planes_fold_steps(ns, chain.length);
+    if (*fold == 0) return false;
+  }
+  const double slice = (ns == 2 ? 1.4 : 2.3) + (*fold ? 13.0 / *fold : 0.0);
+  const RoundModel m{256, 128, h ? h->num_cus : 256, slice, 9.0, 256.0 * 128.0 * 8.0, 1.0};
   double best = 0.93 * split_us - pass;
   *lv = LevelCfg();
   bool take = false;
@@ -278,7 +321,7 @@ bool choose_planes(const famlies_handle_s* h, const Analysis& an, int64_t kd, do
     best = m.rounds(tiles, (double)nk);
     take = true;
   }
-  const LevelCfg c = level_round(m, tiles, nk, &best);
+  const LevelCfg c = level_round(m, tiles, nk, 0, 0, &best);
   if (c.rem) {
     *lv = c;
     take = true;
@@ -465,7 +508,7 @@ bool log_enabled() {
 // split, index form -- index_bits 32: uint32 bytes, -32: int32 elements, 64:
 // int64 elements -- and workspace).
 void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d,
-                  const LevelCfg& lv, bool planes, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit) {
+                  const LevelCfg& lv, bool planes, int fold, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit) {
   static const char* loader[4] = {"rows", "k-gather", "packed", "k-affine"};
   const int xm = an.x_kfast ? (x_vec ? 3 : 1) : 0, ym = an.y_kfast ? (y_vec ? 3 : 1) : 0;
   static const char* int8_names[8] = {"", "", "", "int8x3", "int8x4", "int8x5", "int8x6", "int8x7"};
@@ -473,11 +516,15 @@ void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, cons
                      : an.compute == FAMLIES_BF16X6 ? "bf16x6"
                      : int8_slices(an.compute)      ? int8_names[int8_slices(an.compute)]
                                                     : "native";
-  char direct[96] = "";
-  if (d.bm) std::snprintf(direct, sizeof direct, " direct=%dx%d/%d waves/split %d", d.bm, d.bn, d.wk, d.split);
+  char direct[112] = "";
+  if (d.bm)
+    std::snprintf(direct, sizeof direct, " direct=%dx%d/%d waves/split %d/chains %d", d.bm, d.bn, d.wk, d.split,
+                  d.chains);
   if (lv.rem)
     std::snprintf(direct, sizeof direct, " level=%d whole, %d x %d + %d x %d slices", lv.head, lv.rem, lv.q, lv.parts,
                   lv.part);
+  char through[64] = "";
+  if (planes) std::snprintf(through, sizeof through, fold ? " planes 256x128 fold=%d steps" : " planes 256x128", fold);
   std::fprintf(stderr,
                "[famlies] %s %s/%s M=%lld N=%lld K=%lld L=%lld swapped=%d groups=%zu/%zu/%zu/%zu "
                "trace=%d diag=%d X=%s Y=%s tile=%dx%dx%d split=%d split_tiles=%d index=%s "
@@ -487,7 +534,7 @@ void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, cons
                an.Lm.size(), an.n_trace, an.n_diag, loader[xm], loader[ym], cfg.bm, cfg.bn, cfg.bk, cfg.split,
                cfg.split > 1 ? (cfg.tail ? cfg.tail : -1) : 0,
                index_bits == 32 ? "u32-bytes" : index_bits == -32 ? "i32-elements" : "i64-elements", work_bytes,
-               table_hit ? " (tile table)" : "", planes ? " planes 256x128" : "", direct);
+               table_hit ? " (tile table)" : "", through, direct);
 }
 
 }  // namespace famlies
@@ -520,8 +567,9 @@ static famlies_status analyze_impl(int dtype, int compute, const famlies_tensor*
   index_form(an, 0, &ib, &e32);
   const int64_t runs =  // as in make_plan: the padded contracted order
       ib != 32 || e32 ? 0 : padded_k_length(an, 16 / an.esize);
-  finalize_split(&t, runs && runs <= kMaxGemmDim ? runs : an.K, ceil_div(an.M, t.bm) * ceil_div(an.N, t.bn), &kchunk,
-                 &head);
+  const int64_t kd = runs && runs <= kMaxGemmDim ? runs : an.K, ntiles = ceil_div(an.M, t.bm) * ceil_div(an.N, t.bn);
+  finalize_split(&t, kd, ntiles, &kchunk, &head);
+  const ChainCfg chain = plan_chain(an, t, kd, ntiles, kchunk);
   std::vector<int64_t> v[9];
   bool xv = false, yv = false;
   if (an.M > 0 && an.N > 0) {
@@ -534,16 +582,17 @@ static famlies_status analyze_impl(int dtype, int compute, const famlies_tensor*
   DirectCfg d;
   LevelCfg lv, plv;
   bool planes = false;
+  int fold = 0;
   if (!int8_slices(an.compute)) {
     bool unsplit = false;
     double level_us = 1e30;
-    lv = choose_level(nullptr, an, t, runs ? runs : an.K, &unsplit, &level_us);
-    if (split_parts(an.compute) && ib == 32 && !e32) planes = choose_planes(nullptr, an, runs ? runs : an.K, level_us, &plv);
+    lv = choose_level(nullptr, an, t, kd, chain, &unsplit, &level_us);
+    if (split_parts(an.compute) && ib == 32 && !e32) planes = choose_planes(nullptr, an, kd, chain, level_us, &plv, &fold);
     if (planes) lv = plv;
-    if (!split_parts(an.compute) && ib == 32 && !e32) d = choose_direct(nullptr, an, t, level_us);
+    if (!split_parts(an.compute) && ib == 32 && !e32) d = choose_direct(nullptr, an, t, chain, level_us);
     if (d.bm) lv = LevelCfg();
   }
-  if (log_enabled()) log_decision("analyze", an, t, d, lv, planes, e32 ? -32 : ib, xv, yv, 0, false);
+  if (log_enabled()) log_decision("analyze", an, t, d, lv, planes, fold, e32 ? -32 : ib, xv, yv, 0, false);
   if (offs) {
     const int64_t need = 2 * an.M + 2 * an.K + 2 * an.N + 3 * an.L;
     if (offs_len < need) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_analyze: offsets buffer too short");

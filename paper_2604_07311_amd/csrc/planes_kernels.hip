@@ -124,9 +124,24 @@ __global__ __launch_bounds__(kThreads) void bf16_planes(PlanesArgs a, int mode) 
 template <int NS>
 constexpr int kPlStages = NS == 2 ? 3 : 2;
 
+static_assert(planes_turn(2) == 2 * kPlStages<2> && planes_turn(3) == 2 * kPlStages<3>, "steps of the K loop");
+constexpr int kPlFold = kPlBM * kPlBN;  // elements of a workgroup's running sums
+
+// fold > 0: every `fold` steps (whole turns) the hh accumulators move into
+// running sums in `sums`, so that no chain of additions is longer than the K
+// ranges of the plan's split_contract launch (ChainCfg; bf16x6 with K in one
+// chain had 1.5 to 2.2 times the error).  The addition is exact: its rounding
+// error, taken by the two-sum of Knuth and Moeller, goes to the accumulators
+// of the lower orders, which are of that size.  Two sets of accumulators and
+// the fragments leave no registers for a third, and the workgroup's 128 KB go
+// through L2, 13 us per fold and round (ring o=35 v=105, three ranges: 579 us
+// in one chain, 619 with two folds).  K ranges in workgroups of their own with
+// FP64 partial sums, as split_contract has them, move three times the bytes
+// and fill their rounds less well: 723 us.
 template <int NS>
 __global__ __launch_bounds__(512, 2) void planes_contract(PlainArgs<uint32_t> a, const unsigned char* xp,
-                                                          const unsigned char* yp, int xt, int yt, int nkb) {
+                                                          const unsigned char* yp, int xt, int yt, int nkb, int fold,
+                                                          float* sums) {
   constexpr int NW = 8, TX = kPlBM / kPlRows, TY = kPlBN / kPlRows;
   constexpr int STEP = kPlStepK / 8 * kPlChunk;  // bytes per tile of 64 rows and part
   constexpr int PART = (TX + TY) * STEP, STAGE = NS * PART;
@@ -218,13 +233,45 @@ __global__ __launch_bounds__(512, 2) void planes_contract(PlainArgs<uint32_t> a,
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  f32x4* S = reinterpret_cast<f32x4*>(sums + (size_t)blockIdx.x * kPlFold);
+  // hh into the running sums: 0 the first time, 1 again, 2 at the end (the
+  // total stays in the accumulators)
+  auto fold_sums = [&](auto howc) {
+    constexpr int how = decltype(howc)::value;
+    // recomputed here: kept over the K loop, the addresses went to scratch
+    uint32_t lane_at = (uint32_t)tid * 16u;
+    asm volatile("" : "+v"(lane_at));
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          auto* sum = global(at(S + ((i * 2 + j) * 4 + q) * 512, lane_at));
+          f32x4 v;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[c] = acc[0][i][j][4 * q + c];
+          if constexpr (how > 0) {
+            const f32x4 h = *sum;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const float t = h[c] + v[c], b = t - h[c], e = (h[c] - (t - b)) + (v[c] - b);
+              acc[1][i][j][4 * q + c] += __builtin_isfinite(t) ? e : 0.0f;
+              v[c] = t;
+            }
+          }
+          if constexpr (how < 2) *sum = v;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[0][i][j][4 * q + c] = how < 2 ? 0.0f : v[c];
+        }
+  };
   if (st0 < st1) {
     Frag fa, fb;
     fetch(s0, st0);
     fetch(s1, st0 + 1);
     if constexpr (NST == 3) fetch(s2, st0 + 2);
     join(std::integral_constant<int, (NST - 1) * PER>{});
-    read(fa, s0, 0);
     // step st: its second half's fragments, products of the first, join, the
     // loads of step st + NST into the stage just left, the next step's first
     // fragments, products of the second half; false after the last step
@@ -238,17 +285,34 @@ __global__ __launch_bounds__(512, 2) void planes_contract(PlainArgs<uint32_t> a,
       return st + 1 < st1;
     };
     // Several rounds of the stages per turn: at the head of a loop the
-    // compiler waits for every load before it reads LDS.
-    if constexpr (NST == 3) {
-      for (int st = st0;; st += 6)
-        if (!step(s0, s1, st) || !step(s1, s2, st + 1) || !step(s2, s0, st + 2) || !step(s0, s1, st + 3) ||
-            !step(s1, s2, st + 4) || !step(s2, s0, st + 5))
-          break;
-    } else {
-      for (int st = st0;; st += 4)
-        if (!step(s0, s1, st) || !step(s1, s0, st + 1) || !step(s0, s1, st + 2) || !step(s1, s0, st + 3)) break;
+    // compiler waits for every load before it reads LDS.  False after the
+    // last step.
+    auto turn = [&](int st) {
+      if constexpr (NST == 3)
+        return step(s0, s1, st) && step(s1, s2, st + 1) && step(s2, s0, st + 2) && step(s0, s1, st + 3) &&
+               step(s1, s2, st + 4) && step(s2, s0, st + 5);
+      else
+        return step(s0, s1, st) && step(s1, s0, st + 1) && step(s0, s1, st + 2) && step(s1, s0, st + 3);
+    };
+    // From fold to fold: the first fragments are read again after it, so that
+    // none are held through it (with them, 48 registers went to scratch).
+    int st = st0, end = fold > 0 ? st0 + fold : 0x7fffffff;
+    for (;;) {
+      read(fa, s0, 0);
+      bool more;
+      do {
+        more = turn(st);
+        st += planes_turn(NS);
+      } while (more && st < end);
+      if (!more) break;
+      if (end == st0 + fold)
+        fold_sums(std::integral_constant<int, 0>{});
+      else
+        fold_sums(std::integral_constant<int, 1>{});
+      end += fold;
     }
     __builtin_amdgcn_s_waitcnt(0);  // the clamped loads of the last steps have landed
+    if (fold > 0 && end > st0 + fold) fold_sums(std::integral_constant<int, 2>{});
   }
   auto total = [&](int i, int j, int e) { return (double)acc[1][i][j][e] + (double)acc[0][i][j][e]; };
   if (block >= 0) {
@@ -297,7 +361,8 @@ __global__ __launch_bounds__(512, 2) void planes_contract(PlainArgs<uint32_t> a,
   }
 }
 
-// Workspace: X planes | Y planes | blocks of partial sums (levelled rounds).
+// Workspace: X planes | Y planes | blocks of partial sums (levelled rounds) |
+// running sums of every workgroup (folds).
 struct PlanesLayout {
   int64_t nkb, xt, yt, x, y;
   PlanesLayout(int ns, int64_t M, int64_t N, int64_t K, int64_t L) {
@@ -309,9 +374,16 @@ struct PlanesLayout {
   }
 };
 
-size_t planes_work_bytes(int ns, int64_t M, int64_t N, int64_t K, int64_t L, const LevelCfg& lv) {
+// Workgroups of the launch.
+static int64_t planes_grid(int64_t tiles, const LevelCfg& lv) {
+  return lv.rem > 0 ? lv.head + (int64_t)lv.rem * (1 + lv.parts) : tiles;
+}
+
+size_t planes_work_bytes(int ns, int64_t M, int64_t N, int64_t K, int64_t L, const LevelCfg& lv, int fold) {
   const PlanesLayout lay(ns, M, N, K, L);
-  return (size_t)(lay.x + lay.y) + (size_t)lv.blocks() * (size_t)(kPlBM * kPlBN) * 8;
+  const int64_t tiles = (lay.xt / (kPlBM / kPlRows)) * (lay.yt / (kPlBN / kPlRows)) * L;
+  return (size_t)(lay.x + lay.y) + (size_t)lv.blocks() * (size_t)(kPlBM * kPlBN) * 8 +
+         (fold > 0 ? (size_t)planes_grid(tiles, lv) * kPlFold * 4 : 0);
 }
 
 size_t planes_pack_bytes(int ns, int64_t M, int64_t N, int64_t K, int64_t L, bool x) {
@@ -320,7 +392,7 @@ size_t planes_pack_bytes(int ns, int64_t M, int64_t N, int64_t K, int64_t L, boo
 }
 
 template <int NS>
-static hipError_t launch_planes_ns(const PlainArgs<uint32_t>& a0, int xmode, int ymode, bool pack_only,
+static hipError_t launch_planes_ns(const PlainArgs<uint32_t>& a0, int xmode, int ymode, bool pack_only, int fold,
                                    hipStream_t s) {
   PlainArgs<uint32_t> a = a0;
   const PlanesLayout lay(NS, a.M, a.N, a.K, a.L);
@@ -338,10 +410,14 @@ static hipError_t launch_planes_ns(const PlainArgs<uint32_t>& a0, int xmode, int
   if (pack_only) return hipGetLastError();
   const unsigned char* xq = xmode == 3 ? static_cast<const unsigned char*>(a.x) : xp;
   const unsigned char* yq = ymode == 3 ? static_cast<const unsigned char*>(a.y) : yp;
-  const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n * a.L;
-  const int grid = a.rem > 0 ? a.head + a.rem * (1 + a.lev_parts) : (int)tiles;
+  LevelCfg lv;
+  lv.head = a.head;
+  lv.rem = a.rem;
+  lv.parts = a.lev_parts;
+  const int grid = (int)planes_grid((int64_t)a.tiles_m * a.tiles_n * a.L, lv);
+  float* sums = reinterpret_cast<float*>(static_cast<char*>(a.work) + (size_t)lv.blocks() * (kPlBM * kPlBN) * 8);
   hipLaunchKernelGGL(planes_contract<NS>, dim3(grid), dim3(512), 0, s, a, xq, yq, (int)lay.xt, (int)lay.yt,
-                     (int)lay.nkb);
+                     (int)lay.nkb, fold, sums);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && a.rem > 0) e = launch_level_reduce(FAMLIES_F32, true, a, kPlBM, s);
   return e;
@@ -349,13 +425,14 @@ static hipError_t launch_planes_ns(const PlainArgs<uint32_t>& a0, int xmode, int
 
 // xmode / ymode: 0 row-gathered, 1 K-gathered, 2 in 16-byte runs along K, 3
 // planes written before (a.x / a.y point to them)
-hipError_t launch_planes(const PlainArgs<uint32_t>& a, int ns, int xmode, int ymode, hipStream_t s) {
-  return ns == 2 ? launch_planes_ns<2>(a, xmode, ymode, false, s) : launch_planes_ns<3>(a, xmode, ymode, false, s);
+hipError_t launch_planes(const PlainArgs<uint32_t>& a, int ns, int xmode, int ymode, int fold, hipStream_t s) {
+  return ns == 2 ? launch_planes_ns<2>(a, xmode, ymode, false, fold, s)
+                 : launch_planes_ns<3>(a, xmode, ymode, false, fold, s);
 }
 
 hipError_t launch_planes_pack(const PlainArgs<uint32_t>& a, int ns, bool x, int mode, hipStream_t s) {
   const int xm = x ? mode : 3, ym = x ? 3 : mode;
-  return ns == 2 ? launch_planes_ns<2>(a, xm, ym, true, s) : launch_planes_ns<3>(a, xm, ym, true, s);
+  return ns == 2 ? launch_planes_ns<2>(a, xm, ym, true, 0, s) : launch_planes_ns<3>(a, xm, ym, true, 0, s);
 }
 
 }  // namespace famlies

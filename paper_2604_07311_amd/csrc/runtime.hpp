@@ -72,6 +72,7 @@ struct famlies_plan_s {
   famlies::LevelCfg level;  // rem > 0: the 128 x 128 kernel runs with a levelled last round instead of cfg's split
   bool planes = false;     // bf16: through part planes (256 x 128 tiles)
   famlies::LevelCfg planes_level;
+  int planes_fold = 0;     // K steps between folds into running sums (0: none)
   int64_t planes_held = 0;  // bytes counted in the handle's planes_bytes
   size_t kvoid_pos = 0;    // void mask of the contracted order (byte-offset plans)
   famlies::DirectCfg direct;                // bm > 0: native kMain launches run the direct kernel
@@ -142,7 +143,7 @@ inline famlies_plan_s* plan_of(const void* tok) {
 bool log_enabled();
 void log_plan(const famlies_plan_s* p);
 void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d,
-                  const LevelCfg& lv, bool planes, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit);
+                  const LevelCfg& lv, bool planes, int fold, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit);
 
 // Internal forms of the ABI calls, on resolved objects.
 famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, const void* B, double beta,
@@ -157,16 +158,23 @@ TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_t
 // The direct kernel's configuration where it beats the LDS-tiled kernel with
 // configuration t (and level_us, the levelled tiled kernel's estimate), else
 // bm = 0.
-DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, double level_us);
+DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, const ChainCfg& chain,
+                        double level_us);
+// The chain of a plan with tile choice t (settled: ntiles tiles per batch
+// index, K ranges of kchunk entries) and contracted order length kd.
+ChainCfg plan_chain(const Analysis& an, const TileCfg& t, int64_t kd, int64_t ntiles, int kchunk);
 // A levelled last round for the 128 x 128 kernel of a plan with configuration
-// t (settled) and contracted order length kd, where it beats both t and no
-// split; *unsplit is set where no split at all is the fastest.  *us: the
-// estimated time of the fastest (untouched where the model does not apply).
-LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd, bool* unsplit,
-                      double* us);
+// t (settled) and contracted order length kd, where it beats t and keeps to
+// its chain; *unsplit is set where no split at all is the fastest (and the
+// chain allows it).  *us: the estimated time of the fastest (untouched where
+// the model does not apply).
+LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd,
+                      const ChainCfg& chain, bool* unsplit, double* us);
 // Whether a bf16 plan whose split_contract launch is estimated at split_us
 // runs faster through part planes; *lv: its levelled round (rem == 0: none).
-bool choose_planes(const famlies_handle_s* h, const Analysis& an, int64_t kd, double split_us, LevelCfg* lv);
+// fold: steps between folds that keep to the plan's chain (0: none needed).
+bool choose_planes(const famlies_handle_s* h, const Analysis& an, int64_t kd, const ChainCfg& chain, double split_us,
+                   LevelCfg* lv, int* fold);
 // Whether every aligned run of u contracted indices is contiguous.
 bool contiguous_k_runs(const std::vector<int64_t>& ks, int64_t K, int u);
 int64_t ceil_div(int64_t a, int64_t b);
@@ -226,9 +234,16 @@ inline int split_parts(int compute) { return compute == FAMLIES_BF16X6 ? 3 : com
 // planes written before (by launch_planes_pack: one operand, to a.work).
 hipError_t launch_planes_pack(const PlainArgs<uint32_t>& a, int ns, bool x, int mode, hipStream_t s);
 size_t planes_pack_bytes(int ns, int64_t M, int64_t N, int64_t K, int64_t L, bool x);
-hipError_t launch_planes(const PlainArgs<uint32_t>& a, int ns, int xmode, int ymode, hipStream_t s);
-// Its workspace: both operands' planes and the blocks of a levelled round.
-size_t planes_work_bytes(int ns, int64_t M, int64_t N, int64_t K, int64_t L, const LevelCfg& lv);
+hipError_t launch_planes(const PlainArgs<uint32_t>& a, int ns, int xmode, int ymode, int fold, hipStream_t s);
+// Its workspace: both operands' planes, the blocks of a levelled round and,
+// with fold > 0, running sums.
+size_t planes_work_bytes(int ns, int64_t M, int64_t N, int64_t K, int64_t L, const LevelCfg& lv, int fold);
+// Steps (of 32 entries) of one turn of its K loop, and the steps between folds
+// (whole turns) that keep to a chain of `chain` entries; 0 where it cannot.
+constexpr int planes_turn(int ns) { return ns == 2 ? 6 : 4; }
+constexpr int planes_fold_steps(int ns, int64_t chain) {
+  return (int)(chain / 32 / planes_turn(ns) * planes_turn(ns));
+}
 // Contraction slice (BK) of the split-bf16 kernels with ns parts per operand:
 // 32 for bf16x3, 16 for bf16x6 (three part planes per operand in LDS).
 constexpr int split_slice_k(int ns) { return ns == 3 ? 16 : 32; }
