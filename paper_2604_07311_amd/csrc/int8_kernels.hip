@@ -26,8 +26,8 @@
 //   rows of one chunk) is 512 consecutive bytes.
 // int8_gemm: one workgroup per 128 x 128 (up to six slices) or 128 x 64 tile
 //   of C, waves of 64 x 32; the S planes of X and Y for 32 contracted indices
-//   sit in one of two LDS buffers (the next step's are loaded meanwhile) and
-//   every wave keeps one int32 accumulator set per digit diagonal (S sets of
+//   sit in one of two or three LDS buffers (the next one or two steps' are
+//   loaded meanwhile) and every wave keeps one int32 accumulator set per digit diagonal (S sets of
 //   32 registers).  S is 3 to 7.
 #include "launch.hpp"
 #include "runtime.hpp"
@@ -315,8 +315,17 @@ constexpr int int8_waves() { return 2 * (BN / 32); }
 // chip); 128 x 128 tiles (eight waves, two per SIMD, S sets of 32 of their
 // 256 registers) take two thirds of it per product.  The planes go from
 // global memory straight into LDS, which frees the registers the second wave
-// needs.  Seven slices' sets do not fit two waves and stay at 128 x 64.
-template <typename OffT, int S, int BN>
+// needs.  Seven slices' sets do not fit two waves and stay at 128 x 64: one
+// wave per SIMD, with nothing else to run while it waits.
+//
+// NST: buffers.  With two, a step's loads have the time of one step before
+// they are needed, which at one wave per SIMD is too little: seven slices,
+// ring o=31 v=93, 901 us a launch, with three 695 (with the planes staged
+// through registers 818).  Fewer slices gain from three on long K (three
+// slices, 700 x 3100 x 9000: 408 -> 345 us a call; six, ring o=23 v=71: 130 ->
+// 122) and lose up to 3 % on short K, where the two steps loaded past the last
+// count (ten steps).
+template <typename OffT, int S, int BN, int NST>
 __global__ __launch_bounds__(64 * int8_waves<BN>(), int8_waves<BN>() / 4) void int8_gemm(Int8GemmArgs<OffT> g) {
   constexpr int NW = int8_waves<BN>();
   constexpr int TX = kI8BM / kI8Rows, TY = BN / kI8Rows;     // plane tiles per C tile
@@ -326,6 +335,7 @@ __global__ __launch_bounds__(64 * int8_waves<BN>(), int8_waves<BN>() / 4) void i
   // the other, so nothing waits for them before the step's end
   __shared__ __attribute__((aligned(1024))) unsigned char buf0[S * PLANE];
   __shared__ __attribute__((aligned(1024))) unsigned char buf1[S * PLANE];
+  __shared__ __attribute__((aligned(1024))) unsigned char buf2[NST == 3 ? S * PLANE : 16];
   const PlainArgs<OffT>& a = g.p;
   const int tid = threadIdx.x, lane = tid % 64, wave = scalar(tid / 64);
   const int wm = wave % 2, wn = wave / 2;  // wave tile: rows 64 wm .., columns 32 wn ..
@@ -341,12 +351,19 @@ __global__ __launch_bounds__(64 * int8_waves<BN>(), int8_waves<BN>() / 4) void i
   // loads of step st: piece q = wave + i NW of the S * PIECES pieces; within a
   // plane pieces run tile by tile (X's, then Y's), two chunks each.  A Y tile
   // past the last re-reads the last (its columns are not stored).
+  // With three buffers steps past the last re-read it and every wave issues
+  // PER loads (the last piece again), so that a count of them is a wait.
+  constexpr int PER = (S * PIECES + NW - 1) / NW;
   auto fetch = [&](unsigned char* buf, int st) {
+    if constexpr (NST == 3) st = st < st1 ? st : st1 - 1;
     const int64_t in = (int64_t)(st / kSteps) * kI8Block + (st % kSteps) * kI8StepBytes + lane * 16;
 #pragma unroll
-    for (int i = 0; i < (S * PIECES + NW - 1) / NW; ++i) {
-      const int q = wave + i * NW;
-      if ((S * PIECES) % NW != 0 && q >= S * PIECES) break;
+    for (int i = 0; i < PER; ++i) {
+      int q = wave + i * NW;
+      if constexpr (NST == 3)
+        q = min(q, S * PIECES - 1);
+      else if ((S * PIECES) % NW != 0 && q >= S * PIECES)
+        break;
       const int t2 = q / PIECES, piece = q % PIECES, tl = piece / 2, half = piece % 2;
       const int8_t* src;
       if (tl < TX)
@@ -384,23 +401,53 @@ __global__ __launch_bounds__(64 * int8_waves<BN>(), int8_waves<BN>() / 4) void i
       }
     }
   };
-  // Steps alternate between the buffers: load the next step into the other
-  // one, multiply this one, wait for the loads, barrier (every wave is then
-  // done with this buffer and sees the other).
-  auto step = [&](unsigned char* cur, unsigned char* nxt, int st) {
-    if (st + 1 < st1) fetch(nxt, st + 1);
-    multiply(cur);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-  };
-  if (st0 < st1) {
-    fetch(buf0, st0);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    for (int st = st0; st < st1; st += 2) {
-      step(buf0, buf1, st);
-      if (st + 1 < st1) step(buf1, buf0, st + 1);
+  if constexpr (NST == 2) {
+    // Steps alternate between the buffers: load the next step into the other
+    // one, multiply this one, wait for the loads, barrier (every wave is then
+    // done with this buffer and sees the other).
+    auto step = [&](unsigned char* cur, unsigned char* nxt, int st) {
+      if (st + 1 < st1) fetch(nxt, st + 1);
+      multiply(cur);
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+    };
+    if (st0 < st1) {
+      fetch(buf0, st0);
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      for (int st = st0; st < st1; st += 2) {
+        step(buf0, buf1, st);
+        if (st + 1 < st1) step(buf1, buf0, st + 1);
+      }
     }
+  } else if (st0 < st1) {
+    // Steps go round the buffers: load the step after the next into the one
+    // that the step before this left, multiply this one, wait for the next
+    // step's loads (all but the newest PER; s_waitcnt: vmcnt in bits 3:0 and
+    // 15:14, expcnt 6:4, lgkmcnt 11:8), barrier.
+    auto join = [&](auto keepc) {
+      constexpr int keep = decltype(keepc)::value;
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt((keep & 15) | ((keep >> 4) << 14) | (7 << 4));
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
+    auto step = [&](unsigned char* cur, unsigned char* free, int st) {
+      fetch(free, st + 2);
+      multiply(cur);
+      join(std::integral_constant<int, PER>{});
+      return st + 1 < st1;
+    };
+    fetch(buf0, st0);
+    fetch(buf1, st0 + 1);
+    join(std::integral_constant<int, PER>{});
+    // two rounds per turn: at the head of a loop the compiler waits for every
+    // load before it reads LDS
+    for (int st = st0;; st += 6)
+      if (!step(buf0, buf2, st) || !step(buf1, buf0, st + 1) || !step(buf2, buf1, st + 2) ||
+          !step(buf0, buf2, st + 3) || !step(buf1, buf0, st + 4) || !step(buf2, buf1, st + 5))
+        break;
+    __builtin_amdgcn_s_waitcnt(0);  // the loads past the last step have landed
   }
   // C update from the exact int32 sums of this launch's K chunk:
   // C = alpha 2^(ex+ey) sum_d 2^-7d S_d + beta C, the sum over diagonals from
@@ -503,7 +550,11 @@ static void launch_slice_y(const SliceArgs<OffT>& x, const SliceArgs<OffT>& y, i
 template <typename OffT, int S, int BN>
 static hipError_t launch_gemm(const Int8GemmArgs<OffT>& g, hipStream_t s) {
   const int grid = g.p.L * g.p.tiles_m * g.p.tiles_n * g.p.splits;
-  hipLaunchKernelGGL((int8_gemm<OffT, S, BN>), dim3(grid), dim3(64 * int8_waves<BN>()), 0, s, g);
+  const int steps = (g.p.splits > 1 ? g.kbper : g.kb1 - g.kb0) * (kI8K / kI8Step);  // of a workgroup
+  if (S == 7 || steps >= 16)
+    hipLaunchKernelGGL((int8_gemm<OffT, S, BN, 3>), dim3(grid), dim3(64 * int8_waves<BN>()), 0, s, g);
+  else
+    hipLaunchKernelGGL((int8_gemm<OffT, S, BN, S == 7 ? 3 : 2>), dim3(grid), dim3(64 * int8_waves<BN>()), 0, s, g);
   return hipGetLastError();
 }
 
