@@ -77,7 +77,8 @@ static void packed_vectors(int64_t rows, int64_t kd, int64_t kp, int br, int bk,
 }
 
 template <typename OffT>
-static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int64_t kp, std::vector<char>* image) {
+static famlies_status index_image(famlies_plan_s* p, const PlanUse& use, int64_t mp, int64_t np, int64_t kp,
+                                  std::vector<char>* image) {
   const Analysis& an = p->an;
   std::vector<int64_t> v[9];
   offsets(an.I, 0, an.M, mp, v[0]);
@@ -107,7 +108,7 @@ static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int
   // and its void mask, with byte offsets
   std::vector<uint32_t> kvoid;
   const int u = 16 / an.esize;
-  if (bytes) {
+  if (bytes && !(use.scratch && use.lean)) {  // nothing reads the mask there: no runs, nothing pre-packed
     kvoid.assign((size_t)(ceil_div(kp, 32) + 1), 0);
     KRuns kr;
     const bool padded = p->kd != an.K;
@@ -129,7 +130,7 @@ static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int
   }
   for (int i = 1; i <= 2; ++i) v[i].resize((size_t)kp);
   std::vector<uint32_t> packed[4];  // direct kernel: rows and k's of a packed X, then of a packed Y
-  if (p->direct.bm && bytes)
+  if (p->direct.bm && bytes && !use.scratch)
     for (int op = 0; op < 2; ++op) {
       const int64_t rows = op ? np : mp;
       const int br = op ? p->cfg.bn : p->cfg.bm;
@@ -166,6 +167,7 @@ static famlies_status index_image(famlies_plan_s* p, int64_t mp, int64_t np, int
     for (uint32_t x : packed[i]) o[pos++] = (OffT)x;
   }
   p->kvoid_pos = pos;
+  p->has_kvoid = !kvoid.empty();
   for (uint32_t x : kvoid) o[pos++] = (OffT)x;
   int64_t* lb = reinterpret_cast<int64_t*>(host.data() + b6);
   for (int i = 0; i < 3; ++i) {
@@ -199,7 +201,7 @@ static PlainArgs<OffT> make_args(const famlies_plan_s* p, const void* x, const v
   a.cl = lb + p->off_pos[8];
   a.M = (int32_t)p->an.M;
   a.N = (int32_t)p->an.N;
-  a.kvoid = reinterpret_cast<const uint32_t*>(o + p->kvoid_pos);
+  a.kvoid = p->has_kvoid ? reinterpret_cast<const uint32_t*>(o + p->kvoid_pos) : nullptr;
   a.K = (int32_t)p->kd;
   a.L = (int32_t)p->an.L;
   a.x_nkb = 0;
@@ -229,7 +231,9 @@ static PlainArgs<OffT> make_args(const famlies_plan_s* p, const void* x, const v
 // *image is left empty when C has no elements.
 static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int dtype, int compute,
                                    const famlies_tensor* A, const famlies_tensor* B, const famlies_tensor* C,
-                                   const TileCfg* force, std::vector<char>* image, bool lean = false) {
+                                   const PlanUse& use, std::vector<char>* image) {
+  const TileCfg* force = use.force;
+  const bool lean = use.lean;
   Analysis an;
   std::string err;
   int st = analyze(dtype, compute, A, B, C, &an, &err);
@@ -251,7 +255,7 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   if (i8) {
     // int8_tile (the narrow one in a lean plan: it pads N least), no tile table;
     // K ranges where tiles are few
-    if (!lean && an.L == 1 && p->kd <= int8_exact_k(i8)) p->cfg.split = int8_split(h, an, p->cfg, p->kd);
+    if (!lean && !use.bare && an.L == 1 && p->kd <= int8_exact_k(i8)) p->cfg.split = int8_split(h, an, p->cfg, p->kd);
   } else if (ns) {
     // the bf16 kernels split every tile or none: a tail split becomes none
     if (p->cfg.tail) {
@@ -294,6 +298,7 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   if (!lean && !force && !p->table_hit && !i8) {
     bool unsplit = false;
     p->level = choose_level(h, an, p->cfg, p->kd, chain, &unsplit, &level_us);
+    if (use.bare) p->level = LevelCfg();
     if (unsplit) {
       p->cfg.split = 1;
       p->cfg.tail = 0;
@@ -301,10 +306,11 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
     }
   }
   LevelCfg planes_level;
-  if (!lean && !force && !p->table_hit && ns && p->index_bits == 32 && !p->elem32)
+  if (use.planes && !use.bare && !lean && !force && !p->table_hit && ns && p->index_bits == 32 && !p->elem32)
     p->planes = choose_planes(h, an, p->kd, chain, level_us, &planes_level, &p->planes_fold);
   if (!lean && !force && !p->table_hit && !i8 && !ns && p->index_bits == 32 && !p->elem32) {
     p->direct = choose_direct(h, an, p->cfg, chain, level_us);
+    if (use.bare && p->direct.split > 1) p->direct = DirectCfg();
     if (p->direct.bm) {
       p->level = LevelCfg();
       const int ks = 64 / an.esize;
@@ -321,9 +327,9 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   const int64_t np = ceil_div(std::max<int64_t>(an.N, 1), p->cfg.bn) * p->cfg.bn;
   int64_t kp = ceil_div(std::max<int64_t>(p->kd, 1), p->cfg.bk) * p->cfg.bk + p->cfg.bk;
   if (p->planes) kp = std::max(kp, ceil_div(p->kd, 64) * 64);
-  st = p->index_bits == 64 ? index_image<int64_t>(p, mp, np, kp, image)
-       : p->elem32          ? index_image<int32_t>(p, mp, np, kp, image)
-                            : index_image<uint32_t>(p, mp, np, kp, image);
+  st = p->index_bits == 64 ? index_image<int64_t>(p, use, mp, np, kp, image)
+       : p->elem32          ? index_image<int32_t>(p, use, mp, np, kp, image)
+                            : index_image<uint32_t>(p, use, mp, np, kp, image);
   if (st != FAMLIES_OK) return st;
   if (i8 && an.K > 0) {
     p->work_bytes = int8_work_bytes(i8, an.M, an.N, p->kd, an.L, p->cfg.bn, p->cfg.split);  // digit planes and exponents
@@ -333,6 +339,7 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
                        : (size_t)p->cfg.split * (size_t)(ntiles - p->head) * (size_t)p->cfg.bm *
                              (size_t)p->cfg.bn * (size_t)an.esize;
   }
+  const size_t own = p->work_bytes;  // what the tile choice needs by itself
   if (p->planes) {
     p->planes_level = planes_level;
     p->work_bytes = std::max(p->work_bytes, planes_work_bytes(ns, an.M, an.N, p->kd, an.L, planes_level, p->planes_fold));
@@ -343,55 +350,65 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
     p->work_bytes = std::max(p->work_bytes, (size_t)p->direct.split * (size_t)ceil_div(an.M, p->direct.bm) *
                                                 (size_t)ceil_div(an.N, p->direct.bn) *
                                                 (size_t)(p->direct.bm * p->direct.bn) * (size_t)an.esize);
+  p->extra_bytes = (int64_t)(p->work_bytes - own);
   return FAMLIES_OK;
 }
 
 famlies_status make_plan(famlies_handle h, famlies_plan* out, int dtype, int compute,
                          const famlies_tensor* A, const famlies_tensor* B, const famlies_tensor* C,
-                         const TileCfg* force, bool lean) {
+                         const TileCfg* force) {
   if (!out) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_plan_contract: null output pointer");
   *out = nullptr;
   if (!h) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_plan_contract: invalid handle");
   DeviceGuard dg(h->device);
   if (!dg.ok) return fail(FAMLIES_ERR_DEVICE, "cannot select the handle's device");
-  auto* p = new (std::nothrow) famlies_plan_s();
-  if (!p) return fail(FAMLIES_ERR_ALLOC, "out of host memory");
+  famlies_plan_s* p = nullptr;
   struct Owner {  // frees the plan on every early return and if planning throws
     famlies_plan_s** q;
     ~Owner() {
       if (*q) delete *q;
     }
   } owner{&p};
-  std::vector<char> image;
-  famlies_status st = prepare_plan(h, p, dtype, compute, A, B, C, force, &image, lean);
-  if (st != FAMLIES_OK) return st;
-  if (p->planes) {
-    const int64_t bytes = (int64_t)p->work_bytes;
-    if (h->planes_bytes.fetch_add(bytes) + bytes > kPlanesBytesMax) {
-      h->planes_bytes.fetch_sub(bytes);
-      delete p;
-      p = nullptr;
-      return make_plan(h, out, dtype, compute, A, B, C, force, true);
+  // Where the extra workspace of the routes past the tile choice does not fit
+  // -- the handle's budget, or the device's memory -- the plan does without it,
+  // a part at a time: without part planes, without any of it, and at last with
+  // the smallest image too.
+  PlanUse use;
+  use.force = force;
+  for (int step = 0;; ++step) {
+    const bool last = step == 3 || force;
+    use.planes = step < 1;
+    use.bare = step >= 2;
+    use.lean = step == 3;
+    delete p;
+    p = new (std::nothrow) famlies_plan_s();
+    if (!p) return fail(FAMLIES_ERR_ALLOC, "out of host memory");
+    std::vector<char> image;
+    famlies_status st = prepare_plan(h, p, dtype, compute, A, B, C, use, &image);
+    if (st != FAMLIES_OK) return st;
+    if (p->extra_bytes) {
+      if (h->extra_bytes->fetch_add(p->extra_bytes) + p->extra_bytes > kExtraBytesMax) {
+        h->extra_bytes->fetch_sub(p->extra_bytes);
+        continue;
+      }
+      p->extra_held = h->extra_bytes;
     }
-    p->planes_held = bytes;
-  }
-  if (!image.empty()) {
-    hipError_t e = hipMalloc(&p->d_off, image.size());
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc(indexing vectors)");
-    e = hipMemcpy(p->d_off, image.data(), image.size(), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpy(indexing vectors)");
-  }
-  if (p->work_bytes) {
-    hipError_t e = hipMalloc(&p->d_work, p->work_bytes);
-    if (e == hipErrorOutOfMemory && p->planes) {
-      // no room for the part planes: the kernels that split while staging
-      // (their plan needs a workspace of at most the same size)
-      (void)hipGetLastError();
-      delete p;
-      p = nullptr;
-      return make_plan(h, out, dtype, compute, A, B, C, force, true);
+    hipError_t e = hipSuccess;
+    const char* what = "hipMalloc(indexing vectors)";
+    if (!image.empty()) {
+      e = hipMalloc(&p->d_off, image.size());
+      if (e == hipSuccess) {
+        e = hipMemcpy(p->d_off, image.data(), image.size(), hipMemcpyHostToDevice);
+        if (e != hipSuccess) return hip_fail(e, "hipMemcpy(indexing vectors)");
+      }
     }
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc(split-K workspace)");
+    if (e == hipSuccess && p->work_bytes) {
+      e = hipMalloc(&p->d_work, p->work_bytes);
+      what = "hipMalloc(split-K workspace)";
+    }
+    if (e == hipSuccess) break;
+    if (e != hipErrorOutOfMemory || last) return hip_fail(e, what);
+    (void)hipGetLastError();
   }
   if (log_enabled()) log_plan(p);
   *out = p;
@@ -416,7 +433,7 @@ void destroy_plan(famlies_plan_s* p) {
 famlies_plan_s::~famlies_plan_s() {
   if (owns_device && d_off) (void)hipFree(d_off);
   if (owns_device && d_work) (void)hipFree(d_work);
-  if (planes_held) h->planes_bytes.fetch_sub(planes_held);
+  if (extra_held) extra_held->fetch_sub(extra_bytes);
   if (batch) famlies::destroy_batch(batch);
 }
 
@@ -658,6 +675,31 @@ famlies_status famlies_execute_packed(famlies_plan tok, double alpha, const void
 
 }  // extern "C"
 
+// The launch of contract_noalloc: the plan's device data go to the static
+// scratch array.
+static famlies_status run_noalloc(famlies_plan_s* p, const std::vector<char>& image, size_t off_bytes, double alpha,
+                                  const void* a, const void* b, double beta, void* c, void* stream) {
+  p->owns_device = false;
+  if (off_bytes + p->work_bytes > kNoAllocScratchBytes)
+    return fail(FAMLIES_ERR_UNSUPPORTED,
+                "famlies_contract_noalloc: the call needs " + std::to_string(off_bytes + p->work_bytes) +
+                    " bytes of scratch (indexing vectors and split-K partial sums); the maximum is " +
+                    std::to_string(kNoAllocScratchBytes));
+  p->d_off = p->h->scratch;
+  p->d_work = p->work_bytes ? static_cast<char*>(p->h->scratch) + off_bytes : nullptr;
+  if (log_enabled()) log_plan(p);
+  if (!image.empty()) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    // stream-ordered after earlier work on the stream (which may still read
+    // the scratch); the wait lets the host image go when the call returns
+    hipError_t e = hipMemcpyAsync(p->d_off, image.data(), image.size(), hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(indexing vectors to scratch)");
+    e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+  }
+  return execute_impl(p, alpha, a, b, beta, c, 0, stream);
+}
+
 // famlies_plan_contract + famlies_execute in one call whose device data (the
 // indexing vectors and any split-K partial sums) live in the static scratch
 // array instead of plan-owned allocations.
@@ -669,38 +711,22 @@ static famlies_status contract_noalloc_impl(famlies_handle htok, int dtype, int 
   if (!h || !h->scratch) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_contract_noalloc: invalid handle");
   DeviceGuard dg(h->device);
   if (!dg.ok) return fail(FAMLIES_ERR_DEVICE, "cannot select the handle's device");
-  famlies_plan_s p;
-  p.owns_device = false;
+  famlies_plan_s p, small;
+  famlies_plan_s* use_plan = &p;
   std::vector<char> image;
-  famlies_status st = prepare_plan(h, &p, dtype, compute, A, B, C, nullptr, &image);
+  PlanUse use;
+  use.scratch = true;
+  famlies_status st = prepare_plan(h, &p, dtype, compute, A, B, C, use, &image);
   if (st != FAMLIES_OK) return st;
   size_t off_bytes = (image.size() + 255) & ~(size_t)255;
   if (off_bytes + p.work_bytes > kNoAllocScratchBytes) {
-    // without the direct kernel's extra vectors and the padded contracted order
-    p = famlies_plan_s();
-    p.owns_device = false;
-    st = prepare_plan(h, &p, dtype, compute, A, B, C, nullptr, &image, true);
+    use.lean = true;
+    use_plan = &small;
+    st = prepare_plan(h, &small, dtype, compute, A, B, C, use, &image);
     if (st != FAMLIES_OK) return st;
     off_bytes = (image.size() + 255) & ~(size_t)255;
   }
-  if (off_bytes + p.work_bytes > kNoAllocScratchBytes)
-    return fail(FAMLIES_ERR_UNSUPPORTED,
-                "famlies_contract_noalloc: the call needs " + std::to_string(off_bytes + p.work_bytes) +
-                    " bytes of scratch (indexing vectors and split-K partial sums); the maximum is " +
-                    std::to_string(kNoAllocScratchBytes));
-  p.d_off = h->scratch;
-  p.d_work = p.work_bytes ? static_cast<char*>(h->scratch) + off_bytes : nullptr;
-  if (log_enabled()) log_plan(&p);
-  if (!image.empty()) {
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    // stream-ordered after earlier work on the stream (which may still read
-    // the scratch); the wait lets the host image go when the call returns
-    hipError_t e = hipMemcpyAsync(p.d_off, image.data(), image.size(), hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(indexing vectors to scratch)");
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  }
-  return execute_impl(&p, alpha, a, b, beta, c, 0, stream);
+  return run_noalloc(use_plan, image, off_bytes, alpha, a, b, beta, c, stream);
 }
 
 extern "C" {

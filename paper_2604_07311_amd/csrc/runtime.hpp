@@ -2,6 +2,7 @@
 #pragma once
 
 #include <atomic>
+#include <memory>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -50,7 +51,9 @@ struct famlies_handle_s {
   // device address of the library's static scratch array on this handle's
   // device (famlies_contract_noalloc), resolved once when the handle is made
   void* scratch = nullptr;
-  std::atomic<int64_t> planes_bytes{0};  // part planes held by the handle's plans (kPlanesBytesMax)
+  // extra workspace held by the handle's plans (kExtraBytesMax); the plans
+  // share it, so that one destroyed after its handle still gives back its part
+  std::shared_ptr<std::atomic<int64_t>> extra_bytes = std::make_shared<std::atomic<int64_t>>(0);
 };
 
 struct famlies_plan_s {
@@ -73,8 +76,10 @@ struct famlies_plan_s {
   bool planes = false;     // bf16: through part planes (256 x 128 tiles)
   famlies::LevelCfg planes_level;
   int planes_fold = 0;     // K steps between folds into running sums (0: none)
-  int64_t planes_held = 0;  // bytes counted in the handle's planes_bytes
-  size_t kvoid_pos = 0;    // void mask of the contracted order (byte-offset plans)
+  int64_t extra_bytes = 0;  // workspace past what the tile choice needs by itself
+  std::shared_ptr<std::atomic<int64_t>> extra_held;  // the handle's count that holds them (null: not counted)
+  size_t kvoid_pos = 0;    // void mask of the contracted order (byte-offset plans, unless made lean for the scratch array)
+  bool has_kvoid = false;
   famlies::DirectCfg direct;                // bm > 0: native kMain launches run the direct kernel
   bool dx_vec = false, dy_vec = false;      // every run of 16 bytes of X / Y along K is contiguous
   bool pk_fits[2] = {false, false};         // direct kernel: 32-bit offsets reach all of the pre-packed X / Y
@@ -113,11 +118,22 @@ famlies_status no_throw(const char* where, F&& f) {
   }
 }
 
-// Part planes are as large as the operands (1.5 times in bf16x6).  The plans
-// of a handle hold at most this much of them together, so that a long list of
-// live plans leaves the device's memory to the caller's tensors; a plan past
-// it splits while staging and needs none.
-constexpr int64_t kPlanesBytesMax = (int64_t)16 << 30;
+// Part planes are as large as the operands (1.5 times in bf16x6), blocks of a
+// levelled round up to a few hundred MB.  The plans of a handle hold at most
+// this much of such workspace together (under 3 % of the card), so that a long
+// list of live plans leaves the device's memory to the caller's tensors; a
+// plan past it does without (make_plan).
+constexpr int64_t kExtraBytesMax = (int64_t)8 << 30;
+
+// What a plan is made for.  force (may be null) overrides the tile choice;
+// planes, bare: without part planes; without any workspace past the tile
+// choice's own; lean: the smallest image and workspace (plain contracted
+// order, no direct kernel, levelled round or part planes); scratch: run once
+// from the static scratch array (nothing for pre-packed operands).
+struct PlanUse {
+  const TileCfg* force = nullptr;
+  bool planes = true, bare = false, lean = false, scratch = false;
+};
 
 // GEMM dimensions the single-contraction kernels index with 32-bit ints.
 constexpr int64_t kMaxGemmDim = ((int64_t)1 << 31) - 1024;
@@ -216,12 +232,10 @@ famlies_status batch_execute_impl(famlies_plan_s* p, double alpha, double beta, 
                                   const void* const* B_dev, void* const* C_dev, void* stream);
 // Tile class of the batched kernel with tile BM x BN (each 64 or 128).
 int batch_class_of(int bm, int bn);
-// Plan one contraction; `force` (may be null) overrides the tile choice;
-// lean: as the smallest scratch needs it (plain contracted order, no direct
-// kernel, levelled round or part planes).
+// Plan one contraction; `force` (may be null) overrides the tile choice.
 famlies_status make_plan(famlies_handle_s* h, famlies_plan_s** out, int dtype, int compute,
                          const famlies_tensor* A, const famlies_tensor* B, const famlies_tensor* C,
-                         const TileCfg* force, bool lean = false);
+                         const TileCfg* force);
 
 // Split-bf16 kernels: ns = 2 (bf16x3) or 3 (bf16x6) parts per operand.
 hipError_t launch_split(const PlainArgs<uint32_t>& a, const PlainLaunch& L, int ns, hipStream_t s);
