@@ -181,7 +181,14 @@ famlies_status famlies_plan_contract(famlies_handle h, famlies_plan *out, int dt
 
 /* Run a plan on device pointers A, B, C (each the address of the element
  * with all-zero multi-index) on `stream`.  Checks pointer alignment and that
- * C's address span does not overlap A's or B's.  Asynchronous. */
+ * C's address span does not overlap A's or B's.  Asynchronous.
+ * Executions of an INT8 plan, or of one with split_k > 1, use one workspace
+ * and must not overlap in time; others may, on any streams.  Where such a plan
+ * has a faster route that needs a workspace, the first stream to execute it
+ * has that route, and each capture of a graph counts as a stream of its own
+ * (results differ in rounding between the routes, not from call to call on a
+ * stream); to have it on several streams, or in a graph after running on the
+ * captured stream, make a plan for each. */
 famlies_status famlies_execute(famlies_plan p, double alpha, const void *A, const void *B,
                                double beta, void *C, void *stream);
 

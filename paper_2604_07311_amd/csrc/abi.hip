@@ -180,7 +180,7 @@ static famlies_status index_image(famlies_plan_s* p, const PlanUse& use, int64_t
 
 template <typename OffT>
 static PlainArgs<OffT> make_args(const famlies_plan_s* p, const void* x, const void* y, void* c,
-                                 double alpha, double beta) {
+                                 double alpha, double beta, bool extra) {
   PlainArgs<OffT> a;
   const OffT* o = static_cast<const OffT*>(p->d_off);
   const int64_t* lb = reinterpret_cast<const int64_t*>(static_cast<const char*>(p->d_off) + p->batch_off_bytes);
@@ -211,7 +211,7 @@ static PlainArgs<OffT> make_args(const famlies_plan_s* p, const void* x, const v
   a.splits = p->cfg.split;
   a.kchunk = p->kchunk;
   a.head = p->head;
-  a.rem = p->level.rem;
+  a.rem = extra ? p->level.rem : 0;
   if (a.rem) {
     a.splits = 1;
     a.head = p->level.head;
@@ -351,6 +351,7 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
                                                 (size_t)ceil_div(an.N, p->direct.bn) *
                                                 (size_t)(p->direct.bm * p->direct.bn) * (size_t)an.esize);
   p->extra_bytes = (int64_t)(p->work_bytes - own);
+  p->choice_alone = own == 0 && p->extra_bytes > 0;
   return FAMLIES_OK;
 }
 
@@ -540,8 +541,26 @@ static bool overlaps(const void* p, int64_t plo, int64_t phi, const void* q, int
 
 namespace famlies {
 
+// Whether an execution on stream s may use the plan's extra workspace: the
+// first stream to ask has it, for good, and a stream that is captured counts
+// as a stream of its own per capture (its graph may be launched anywhere).
+// The per-thread default stream is a stream per thread and never has it.
+static bool takes_extra(famlies_plan_s* p, hipStream_t s) {
+  if (s == hipStreamPerThread) return false;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  if (hipStreamGetCaptureInfo(s, &st, &id) != hipSuccess) (void)hipGetLastError();  // the launch will report it
+  if (st != hipStreamCaptureStatusActive) id = 0;
+  if (!p->extra_taken) {
+    p->extra_taken = true;
+    p->extra_stream = s;
+    p->extra_capture = id;
+  }
+  return p->extra_stream == s && p->extra_capture == id;
+}
+
 famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, const void* B, double beta,
-                            void* C, int packed, void* stream) {
+                            void* C, int packed, void* stream, bool ordered) {
   if (!p || p->batch) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_execute: invalid plan");
   const Analysis& an = p->an;
   if (an.M == 0 || an.N == 0) return FAMLIES_OK;
@@ -585,17 +604,38 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
   hipError_t e;
   const int ns = split_parts(an.compute);
   const int i8 = int8_slices(an.compute);
+  // The launches of one execution through the workspace follow each other on
+  // their stream (threads may share a plan and a stream), and a plan whose tile
+  // choice needs no workspace stays free to run on several streams at once:
+  // the others than the workspace's run that choice.
+  std::unique_lock<std::mutex> in_order(p->work_mu, std::defer_lock);
+  bool extra = true;
+  if (p->work_bytes && L.kind == PlainLaunch::kMain) {
+    in_order.lock();
+    if (!ordered && p->choice_alone) extra = takes_extra(p, s);
+    if (!extra && p->planes && xp != yp) {
+      // no other kernel reads a packed operand of this plan, and the partner's
+      // planes go to the workspace: wait until it is free, and take it over
+      hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone) {
+        e = hipDeviceSynchronize();
+        if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
+      }
+      p->extra_taken = false;
+      extra = takes_extra(p, s) || s == hipStreamPerThread;
+    }
+  }
   if (i8 && (pa || pb)) return fail(FAMLIES_ERR_UNSUPPORTED, "famlies_execute_packed: no packed operands for INT8 plans");
   if (i8 && L.kind == PlainLaunch::kMain) {
     const int xm = std::min(p->xmode, 2), ym = std::min(p->ymode, 2);  // 16-byte runs of any form: 2
     e = p->index_bits == 32
-            ? launch_int8(make_args<uint32_t>(p, x, y, C, alpha, beta), i8, p->cfg.bn, xm, ym, s)
-            : launch_int8(make_args<int64_t>(p, x, y, C, alpha, beta), i8, p->cfg.bn, xm, ym, s);
+            ? launch_int8(make_args<uint32_t>(p, x, y, C, alpha, beta, extra), i8, p->cfg.bn, xm, ym, s)
+            : launch_int8(make_args<int64_t>(p, x, y, C, alpha, beta, extra), i8, p->cfg.bn, xm, ym, s);
   } else if (ns && L.kind == PlainLaunch::kMain) {
     if (p->elem32) {
-      e = launch_split(make_args<int32_t>(p, x, y, C, alpha, beta), L, ns, s);
+      e = launch_split(make_args<int32_t>(p, x, y, C, alpha, beta, extra), L, ns, s);
     } else if (p->index_bits == 32) {
-      PlainArgs<uint32_t> a = make_args<uint32_t>(p, x, y, C, alpha, beta);
+      PlainArgs<uint32_t> a = make_args<uint32_t>(p, x, y, C, alpha, beta, extra);
       if (xp) {  // the packed buffer is addressed from its start, not through offsets
         a.x = x;
         a.x_nkb = (int32_t)((p->kd + L.bk - 1) / L.bk);
@@ -604,8 +644,8 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
         a.y = y;
         a.y_nkb = (int32_t)((p->kd + L.bk - 1) / L.bk);
       }
-      if (p->planes) {
-        const LevelCfg& lv = p->planes_level;
+      if (p->planes && (extra || xp)) {  // (without the workspace: both operands pre-packed)
+        const LevelCfg lv = extra ? p->planes_level : LevelCfg();
         a.tiles_m = (int32_t)ceil_div(an.M, 256);
         a.tiles_n = (int32_t)ceil_div(an.N, 128);
         a.splits = 1;
@@ -620,12 +660,12 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
         e = launch_split(a, L, ns, s);
       }
     } else {
-      e = launch_split(make_args<int64_t>(p, x, y, C, alpha, beta), L, ns, s);
+      e = launch_split(make_args<int64_t>(p, x, y, C, alpha, beta, extra), L, ns, s);
     }
   } else if (p->elem32) {
-    e = launch_plain(an.dtype, make_args<int32_t>(p, x, y, C, alpha, beta), L, s);
+    e = launch_plain(an.dtype, make_args<int32_t>(p, x, y, C, alpha, beta, extra), L, s);
   } else if (p->index_bits == 32) {
-    PlainArgs<uint32_t> a = make_args<uint32_t>(p, x, y, C, alpha, beta);
+    PlainArgs<uint32_t> a = make_args<uint32_t>(p, x, y, C, alpha, beta, extra);
     if (xp) {
       a.x = x;
       a.x_nkb = (int32_t)((p->kd + L.bk - 1) / L.bk);
@@ -634,7 +674,7 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
       a.y = y;
       a.y_nkb = (int32_t)((p->kd + L.bk - 1) / L.bk);
     }
-    if (p->direct.bm && L.kind == PlainLaunch::kMain && (!xp || p->pk_fits[0]) && (!yp || p->pk_fits[1])) {
+    if (p->direct.bm && (extra || p->direct.split == 1) && L.kind == PlainLaunch::kMain && (!xp || p->pk_fits[0]) && (!yp || p->pk_fits[1])) {
       const DirectCfg& d = p->direct;
       const uint32_t* o = static_cast<const uint32_t*>(p->d_off);
       if (xp) a.xmn = o + p->pk_pos[0], a.xk = o + p->pk_pos[1];
@@ -652,7 +692,7 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
       e = launch_plain(an.dtype, a, L, s);
     }
   } else {
-    e = launch_plain(an.dtype, make_args<int64_t>(p, x, y, C, alpha, beta), L, s);
+    e = launch_plain(an.dtype, make_args<int64_t>(p, x, y, C, alpha, beta, extra), L, s);
   }
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return FAMLIES_OK;

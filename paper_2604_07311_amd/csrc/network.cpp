@@ -248,7 +248,8 @@ famlies_status famlies_network_execute(famlies_network tok, void* stream) {
       (op == 0 ? A : B) = s.packed[op];
       mask |= 1 << op;
     }
-    famlies_status st = execute_impl(s.plan, s.alpha, A, B, s.beta, tc.ptr, mask, stream);
+    famlies_status st = execute_impl(s.plan, s.alpha, A, B, s.beta, tc.ptr, mask, stream,
+                                     true);  // the steps share the network's tensors, so its runs never overlap
     if (st != FAMLIES_OK) return st;
   }
   return FAMLIES_OK;

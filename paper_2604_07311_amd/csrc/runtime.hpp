@@ -3,6 +3,7 @@
 
 #include <atomic>
 #include <memory>
+#include <mutex>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -77,6 +78,13 @@ struct famlies_plan_s {
   famlies::LevelCfg planes_level;
   int planes_fold = 0;     // K steps between folds into running sums (0: none)
   int64_t extra_bytes = 0;  // workspace past what the tile choice needs by itself
+  bool choice_alone = false;  // the tile choice needs no workspace, the plan's route has one
+  // held while the launches of an execution that use the workspace are issued
+  std::mutex work_mu;
+  // who the workspace belongs to where choice_alone (takes_extra), under work_mu
+  bool extra_taken = false;
+  hipStream_t extra_stream = nullptr;
+  unsigned long long extra_capture = 0;
   std::shared_ptr<std::atomic<int64_t>> extra_held;  // the handle's count that holds them (null: not counted)
   size_t kvoid_pos = 0;    // void mask of the contracted order (byte-offset plans, unless made lean for the scratch array)
   bool has_kvoid = false;
@@ -162,8 +170,9 @@ void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, cons
                   const LevelCfg& lv, bool planes, int fold, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit);
 
 // Internal forms of the ABI calls, on resolved objects.
+// ordered: executions of the plan never overlap (the caller sees to it).
 famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, const void* B, double beta,
-                            void* C, int packed, void* stream);
+                            void* C, int packed, void* stream, bool ordered = false);
 famlies_status pack_size_impl(famlies_plan_s* p, int operand, size_t* bytes);
 famlies_status pack_impl(famlies_plan_s* p, int operand, const void* src, void* dst, void* stream);
 void destroy_plan(famlies_plan_s* p);
