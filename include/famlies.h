@@ -289,7 +289,9 @@ famlies_status famlies_network_destroy(famlies_network n);
  * the winners to table_path (text, one line per class, as read by
  * famlies_load_tune_table); the handle then uses them.
  *   plain entries: tile shape and split-K of the single-contraction kernels
- *     (FP64, FP32 and bf16x3), timed on one GEMM-shaped contraction;
+ *     (FP64, FP32 and bf16x3), timed on one GEMM-shaped contraction against
+ *     the planner's own choice of kernel, which the entry keeps (bk 0) unless
+ *     a tile is 3 % faster;
  *   batch entries: tile class (BM, BN in {64, 128}) of the persistent
  *     batched kernel (FP64 and FP32), timed on batched launches of that
  *     kernel with enough identical problems to fill the device.
@@ -306,7 +308,8 @@ famlies_status famlies_tune(famlies_handle h, const char *table_path, int flags)
  * one entry per line:
  *   <plain|batch> <dtype> <compute> <log2 M> <log2 N> <log2 K> <bm> <bn> <bk> <split> [<index bits> [<split tiles>]]
  * A plan takes the entry of its size class (or the nearest one within two
- * classes).  The optional index bits 64 makes such plans use 64-bit indexing
+ * classes).  It runs the tiled kernel with that tile; a plain entry with bk 0
+ * leaves the choice of kernel and tile to the planner, as without a table.  The optional index bits 64 makes such plans use 64-bit indexing
  * vectors even when 32 bits reach every element, e32 makes them use 32-bit
  * element offsets wherever those reach (0 or 32: automatic).  The optional
  * split tiles n > 0 (plain FP64/FP32 plans with split > 1) cuts only the last

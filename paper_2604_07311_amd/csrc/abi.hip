@@ -244,7 +244,7 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
   p->h = h;
   p->an = an;
   const int i8 = int8_slices(compute);
-  p->cfg = i8 ? int8_tile(i8, lean ? 64 : an.N) : force ? *force : choose_tiles(h, an, &p->table_hit);
+  p->cfg = i8 ? int8_tile(i8, lean ? 64 : an.N) : force ? *force : choose_tiles(h, an, &p->table_hit, use.table);
   if (i8 && force) p->cfg.index_bits = force->index_bits;
   index_form(an, p->cfg.index_bits, &p->index_bits, &p->elem32);
   const int ns = split_parts(compute);
@@ -357,7 +357,7 @@ static famlies_status prepare_plan(famlies_handle_s* h, famlies_plan_s* p, int d
 
 famlies_status make_plan(famlies_handle h, famlies_plan* out, int dtype, int compute,
                          const famlies_tensor* A, const famlies_tensor* B, const famlies_tensor* C,
-                         const TileCfg* force) {
+                         const TileCfg* force, bool table) {
   if (!out) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_plan_contract: null output pointer");
   *out = nullptr;
   if (!h) return fail(FAMLIES_ERR_INVALID_ARG, "famlies_plan_contract: invalid handle");
@@ -376,6 +376,7 @@ famlies_status make_plan(famlies_handle h, famlies_plan* out, int dtype, int com
   // the smallest image too.
   PlanUse use;
   use.force = force;
+  use.table = table;
   for (int step = 0;; ++step) {
     const bool last = step == 3 || force;
     use.planes = step < 1;

@@ -101,6 +101,8 @@ struct TileCfg {
   // split > 1: how many tiles, the last ones in tile order, run as `split`
   // K slices each; the others run whole K first (0: every tile is split)
   int tail = 0;
+  // table entries: measured, the planner's own choice was the fastest
+  bool planner() const { return bk == 0; }
 };
 
 // Configuration of the direct kernel (small and narrow problems): tile

@@ -41,15 +41,19 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // only the tiles of the last round are cut into K slices, so that round
 // spreads over every CU instead of leaving most of them idle.  The model
 // only ranks candidates; it is not a timing.
-TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_table) {
+TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_table, bool use_table) {
   TileCfg t;
   const int bk = an.dtype == FAMLIES_F64 ? 8 : 32;
   t.bk = bk;
   if (from_table) *from_table = false;
   if (an.M == 0 || an.N == 0 || an.K == 0) return t;
-  if (h && h->table.lookup_plain(an, &t)) {
-    if (from_table) *from_table = true;
-    return t;
+  if (h && use_table && h->table.lookup_plain(an, &t)) {
+    if (!t.planner()) {
+      if (from_table) *from_table = true;
+      return t;
+    }
+    t = TileCfg();
+    t.bk = bk;
   }
   const int cus = h ? h->num_cus : 256;
   // CU throughput in flop/s and HBM bandwidth in bytes/s (MI355X-class)

@@ -133,14 +133,14 @@ famlies_status no_throw(const char* where, F&& f) {
 // plan past it does without (make_plan).
 constexpr int64_t kExtraBytesMax = (int64_t)8 << 30;
 
-// What a plan is made for.  force (may be null) overrides the tile choice;
-// planes, bare: without part planes; without any workspace past the tile
+// What a plan is made for.  force (may be null) overrides the tile choice,
+// table: the handle's tile table may; planes, bare: without part planes; without any workspace past the tile
 // choice's own; lean: the smallest image and workspace (plain contracted
 // order, no direct kernel, levelled round or part planes); scratch: run once
 // from the static scratch array (nothing for pre-packed operands).
 struct PlanUse {
   const TileCfg* force = nullptr;
-  bool planes = true, bare = false, lean = false, scratch = false;
+  bool table = true, planes = true, bare = false, lean = false, scratch = false;
 };
 
 // GEMM dimensions the single-contraction kernels index with 32-bit ints.
@@ -177,7 +177,8 @@ famlies_status pack_size_impl(famlies_plan_s* p, int operand, size_t* bytes);
 famlies_status pack_impl(famlies_plan_s* p, int operand, const void* src, void* dst, void* stream);
 void destroy_plan(famlies_plan_s* p);
 // from_table (may be null) is set when the handle's tile table decided.
-TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_table = nullptr);
+TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_table = nullptr,
+                     bool use_table = true);
 
 // Host planning helpers (plan_host.cpp).
 // The direct kernel's configuration where it beats the LDS-tiled kernel with
@@ -241,10 +242,11 @@ famlies_status batch_execute_impl(famlies_plan_s* p, double alpha, double beta, 
                                   const void* const* B_dev, void* const* C_dev, void* stream);
 // Tile class of the batched kernel with tile BM x BN (each 64 or 128).
 int batch_class_of(int bm, int bn);
-// Plan one contraction; `force` (may be null) overrides the tile choice.
+// Plan one contraction; `force` (may be null) overrides the tile choice,
+// table: the handle's tile table may.
 famlies_status make_plan(famlies_handle_s* h, famlies_plan_s** out, int dtype, int compute,
                          const famlies_tensor* A, const famlies_tensor* B, const famlies_tensor* C,
-                         const TileCfg* force);
+                         const TileCfg* force, bool table = true);
 
 // Split-bf16 kernels: ns = 2 (bf16x3) or 3 (bf16x6) parts per operand.
 hipError_t launch_split(const PlainArgs<uint32_t>& a, const PlainLaunch& L, int ns, hipStream_t s);

@@ -54,7 +54,8 @@ void TileTable::put(const Entry& e) {
 // indexing vectors even when 32 bits reach every element, e32 makes them use
 // 32-bit element offsets wherever those reach (0 or 32: automatic), and
 // split tiles > 0 splits only that many tiles, the last in tile order (0:
-// every tile when split > 1).
+// every tile when split > 1).  A plain entry with bk 0 leaves its class to the
+// planner (TileCfg::planner; bm, bn and split are then what it chose).
 bool TileTable::load(const std::string& path, std::string* err) {
   std::ifstream f(path);
   if (!f) {
@@ -72,8 +73,8 @@ bool TileTable::load(const std::string& path, std::string* err) {
     Entry e;
     if (!(is >> kind >> e.dtype >> e.compute >> e.lm >> e.ln >> e.lk >> e.cfg.bm >> e.cfg.bn >>
           e.cfg.bk >> e.cfg.split) ||
-        (kind != "plain" && kind != "batch") || e.cfg.bm <= 0 || e.cfg.bn <= 0 || e.cfg.bk <= 0 ||
-        e.cfg.split <= 0) {
+        (kind != "plain" && kind != "batch") || e.cfg.bm <= 0 || e.cfg.bn <= 0 || e.cfg.bk < 0 ||
+        (e.cfg.bk == 0 && kind != "plain") || e.cfg.split <= 0) {
       *err = path + ":" + std::to_string(ln) + ": malformed entry";
       return false;
     }

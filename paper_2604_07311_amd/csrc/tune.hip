@@ -124,17 +124,26 @@ famlies_status tune_plain(famlies_handle_s* h, const Buffers& buf, int64_t cap, 
                 cands.push_back(t);
               }
           }
+          // The planner's own plan first (direct kernel, levelled rounds and
+          // part planes among its routes; a tile entry switches them off): a
+          // forced tile has to beat it by more than the timing's scatter.
           float best = 1e30f;
-          TileCfg bcfg = cands[0];
-          for (const TileCfg& t : cands) {
+          TileCfg bcfg;
+          for (int c = -1; c < (int)cands.size(); ++c) {
             famlies_plan_s* p = nullptr;
-            famlies_status st = make_plan(h, &p, md.dtype, md.compute, &A, &B, &C, &t);
+            famlies_status st = make_plan(h, &p, md.dtype, md.compute, &A, &B, &C, c < 0 ? nullptr : &cands[(size_t)c],
+                                          false);
             if (st != FAMLIES_OK) return st;
-            const TileCfg eff = p->cfg;  // split after the planner's rounding
+            TileCfg eff = p->cfg;  // split after the planner's rounding
+            eff.tail = c < 0 ? 0 : eff.tail;
             float ms = 0.f;
             st = time_plan(p, buf, s, reps, &ms);
             destroy_plan(p);
             if (st != FAMLIES_OK) return st;
+            if (c < 0) {
+              eff.bk = 0;
+              ms *= 0.97f;
+            }
             if (ms < best) {
               best = ms;
               bcfg = eff;
@@ -143,7 +152,7 @@ famlies_status tune_plain(famlies_handle_s* h, const Buffers& buf, int64_t cap, 
           if (log_enabled())
             std::fprintf(stderr, "[famlies] tune plain dtype %d compute %d M %lld N %lld K %lld: %dx%dx%d split %d %.4f ms\n",
                          md.dtype, md.compute, (long long)M, (long long)N, (long long)K, bcfg.bm, bcfg.bn, bcfg.bk,
-                         bcfg.split, best);
+                         bcfg.split, bcfg.planner() ? best / 0.97f : best);
           TileTable::Entry en;
           en.kind = 0;
           en.dtype = md.dtype;
