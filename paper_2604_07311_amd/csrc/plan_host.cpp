@@ -269,6 +269,11 @@ ChainCfg plan_chain(const Analysis& an, const TileCfg& t, int64_t kd, int64_t nt
 LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd,
                       const ChainCfg& chain, bool* unsplit, double* us) {
   *unsplit = false;
+  if (t.bm == 256) {  // one workgroup per CU; measured at 4096^3 with unit strides on neither side, 1090 us
+    const RoundModel tall{256, 128, h ? h->num_cus : 256, 4.2, 9.0, 256.0 * 128.0 * 8.0, 1.0};
+    *us = tall.rounds(ceil_div(an.M, 256) * ceil_div(an.N, 128) * an.L, (double)ceil_div(kd, t.bk));
+    return LevelCfg();
+  }
   if (t.bm != 128 || t.bn != 128 || an.M == 0 || an.N == 0 || an.K == 0) return LevelCfg();
   const int ns = split_parts(an.compute);
   // a slice of the bf16 kernel: 16-deep in bf16x6; 32-deep in bf16x3, where
@@ -295,6 +300,26 @@ LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileC
   if (lv.rem) *unsplit = false;
   *us = lv.rem ? best : now;
   return lv;
+}
+
+// bf16x3 on large problems: a 256 x 128 tile (128 x 64 per wave) halves the
+// LDS bytes per MFMA of the 128 x 128 tile (bf16x6 stays at 128 x 128 with
+// 16-deep slices, two workgroups per CU).  It has registers for one slice in
+// flight and one workgroup per CU, so it is taken only when both operands are
+// element-gathered along K: a row-gathered operand keeps the 128 x 128 tile
+// with two slices in flight (ring o=48 v=192: 186 -> 201 TFLOP/s
+// FP32-equivalent), and an operand in runs the 128 x 128 tile at two
+// workgroups per CU (ladder v=128 o=32: 284 -> 307).  Where the operands meet
+// enough tiles part planes, which gather each element once, replace it
+// (choose_planes).
+bool tall_tile(const Analysis& an, const TileCfg& t, int64_t runs) {
+  if (split_parts(an.compute) != 2 || an.M < 1024 || an.N < 512 || t.split != 1 || !an.x_kfast || !an.y_kfast)
+    return false;
+  std::vector<int64_t> v[9];
+  bool xv = false, yv = false;
+  all_offsets(an, v);
+  vec_flags(an, 32, index_bits_for(an), v, &xv, &yv);
+  return !(xv || (runs && an.P[0].sx == 1)) && !(yv || (runs && an.P[0].sy == 1));
 }
 
 // The pass over the operands at 5.5 TB/s and tiles of twice the size, one per
@@ -590,7 +615,9 @@ static famlies_status analyze_impl(int dtype, int compute, const famlies_tensor*
   if (!int8_slices(an.compute)) {
     bool unsplit = false;
     double level_us = 1e30;
-    lv = choose_level(nullptr, an, t, kd, chain, &unsplit, &level_us);
+    TileCfg run = t;
+    if (an.M > 0 && an.N > 0 && tall_tile(an, t, runs)) run.bm = 256;
+    lv = choose_level(nullptr, an, run, kd, chain, &unsplit, &level_us);
     if (split_parts(an.compute) && ib == 32 && !e32) planes = choose_planes(nullptr, an, kd, chain, level_us, &plv, &fold);
     if (planes) lv = plv;
     if (!split_parts(an.compute) && ib == 32 && !e32) d = choose_direct(nullptr, an, t, chain, level_us);

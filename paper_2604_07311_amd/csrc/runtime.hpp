@@ -196,6 +196,9 @@ ChainCfg plan_chain(const Analysis& an, const TileCfg& t, int64_t kd, int64_t nt
 // the model does not apply).
 LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileCfg& t, int64_t kd,
                       const ChainCfg& chain, bool* unsplit, double* us);
+// Whether a bf16x3 plan with tile choice t and padded contracted order length
+// runs (0: plain) takes 256 x 128 tiles where it splits while staging.
+bool tall_tile(const Analysis& an, const TileCfg& t, int64_t runs);
 // Whether a bf16 plan whose split_contract launch is estimated at split_us
 // runs faster through part planes; *lv: its levelled round (rem == 0: none).
 // fold: steps between folds that keep to the plan's chain (0: none needed).
