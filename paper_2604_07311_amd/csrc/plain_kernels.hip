@@ -109,17 +109,16 @@ __global__ __launch_bounds__(kThreads, FAMLIES_PLAIN_WAVES_PER_EU) void plain_co
 // the partial sums (T; double in the bf16 kernels).
 template <typename T, typename P, typename OffT>
 __global__ __launch_bounds__(kThreads) void splitk_reduce(PlainArgs<OffT> a, int bm, int bn) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const int ntail = a.tiles_m * a.tiles_n - a.head;
-  const int64_t per = (int64_t)bm * bn;
-  if (i >= ntail * per) return;
-  const int tt = (int)(i / per), r = (int)(i % per);
-  const int t = a.head + tt;
-  const int m = (t % a.tiles_m) * bm + r / bn, n = (t / a.tiles_m) * bn + r % bn;
+  // whole workgroups per block (bm * bn is a multiple of 256, bn a power of two)
+  const int ntail = a.tiles_m * a.tiles_n - a.head, per = bm * bn, wgs = per / kThreads;
+  const int tt = scalar((int)blockIdx.x / wgs), r = ((int)blockIdx.x - tt * wgs) * kThreads + threadIdx.x;
+  const int t = a.head + tt, pn = scalar(t / a.tiles_m), pm = t - pn * a.tiles_m;
+  const int ri = r >> __builtin_ctz(bn), m = pm * bm + ri, n = pn * bn + (r & (bn - 1));
   if (m >= a.M || n >= a.N) return;
-  const P* W = static_cast<const P*>(a.work);
+  const P* W = static_cast<const P*>(a.work) + (size_t)tt * per + r;
   P s = P(0);
-  for (int k = 0; k < a.splits; ++k) s += W[((size_t)k * ntail + tt) * per + r];
+#pragma unroll 4
+  for (int k = 0; k < a.splits; ++k) s += *global(W + (size_t)k * ntail * per);
   T* cp = at(static_cast<T*>(a.c), (OffT)(a.cm[m] + a.cn[n]));
   const P al = static_cast<P>(a.alpha), be = static_cast<P>(a.beta);
   P v = al * s;
@@ -129,26 +128,30 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce(PlainArgs<OffT> a, int
 
 // The levelled tiles: C = alpha * (their blocks of partial sums in order) +
 // beta * C.  P is the type of the partial sums (and of the update): T for the
-// plain kernels, double for the bf16 kernels.  A workgroup takes 16 rows of a
-// tile, its lanes consecutive columns, eight rows per thread in flight; bound
-// by HBM (partial sums read once, C read and written).
+// plain kernels, double for the bf16 kernels.  A workgroup takes eight rows of
+// a tile, its lanes consecutive columns, four rows of four blocks per thread in
+// flight; bound by HBM (partial sums read once, C read and written), by latency
+// where the tiles are few (75 x 4882, 13 blocks a tile: 11.3 us with 16 rows of
+// one block in flight, 9.6).
+constexpr int kLevelRows = 8;
 template <typename T, typename P, typename OffT>
 __global__ __launch_bounds__(kThreads) void level_reduce(PlainArgs<OffT> a, int bm) {
-  constexpr int B = 128, RW = 16, RT = RW / 2;  // B: columns of a tile
+  constexpr int B = 128, RW = kLevelRows, RT = RW / 2;  // B: columns of a tile
   const int i = blockIdx.x / (bm / RW), row0 = (blockIdx.x % (bm / RW)) * RW + threadIdx.x / B;
   const size_t per = (size_t)bm * B;
   const int ntiles = a.tiles_m * a.tiles_n;
   const int t = a.head + i, l = t / ntiles, tl = t % ntiles;
   const int m0 = (tl % a.tiles_m) * bm + row0, n = (tl / a.tiles_m) * B + threadIdx.x % B;
+  if (m0 >= a.M || n >= a.N) return;  // past the edges of a ragged tile: nothing to read either
   const P* W = static_cast<const P*>(a.work) + (size_t)row0 * B + threadIdx.x % B;
   P s[RT];
 #pragma unroll
   for (int q = 0; q < RT; ++q) s[q] = *global(W + i * per + q * 2 * B);
+#pragma unroll 4
   for (int w = 0; w < a.lev_parts; ++w)
 #pragma unroll
     for (int q = 0; q < RT; ++q)
       s[q] += *global(W + ((size_t)a.rem + (size_t)i * a.lev_parts + w) * per + q * 2 * B);
-  if (n >= a.N) return;
   T* C = static_cast<T*>(a.c) + a.cl[l];
   const OffT cn = a.cn[n];
   const P al = static_cast<P>(a.alpha), be = static_cast<P>(a.beta);
@@ -172,7 +175,7 @@ __global__ __launch_bounds__(kThreads) void level_reduce(PlainArgs<OffT> a, int 
 // bf16: the partial sums are FP64.
 template <typename OffT>
 hipError_t launch_level_reduce(int dtype, bool bf16, const PlainArgs<OffT>& a, int bm, hipStream_t s) {
-  const dim3 grid(a.rem * (bm / 16));
+  const dim3 grid(a.rem * (bm / kLevelRows));
   if (dtype == FAMLIES_F64)
     hipLaunchKernelGGL((level_reduce<double, double, OffT>), grid, dim3(kThreads), 0, s, a, bm);
   else if (bf16)
