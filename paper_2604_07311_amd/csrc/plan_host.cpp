@@ -276,11 +276,19 @@ LevelCfg choose_level(const famlies_handle_s* h, const Analysis& an, const TileC
   }
   if (t.bm != 128 || t.bn != 128 || an.M == 0 || an.N == 0 || an.K == 0) return LevelCfg();
   const int ns = split_parts(an.compute);
-  // a slice of the bf16 kernel: 16-deep in bf16x6; 32-deep in bf16x3, where
-  // gathered rows take their staging registers from the products
-  const double bf16 = ns == 3 ? 1.5 : an.x_kfast && an.y_kfast ? 1.55 : 1.85;
-  const RoundModel m{128, 128, 2 * (int64_t)(h ? h->num_cus : 256), ns ? bf16 : an.esize == 8 ? 1.95 : 3.8, 9.0,
-                     128.0 * 128.0 * (ns ? 8.0 : (double)an.esize), 0.77};
+  // a slice of the bf16 kernels (16-deep in bf16x6, 32-deep in bf16x3) by how
+  // the operands are gathered: rows, and elements along K without unit stride,
+  // take staging registers and load instructions (bf16x3 with two such operands
+  // of a kind has one workgroup per CU).  Measured at 1024 x 4096 x 4096.
+  const bool runs = padded_k_length(an, 16 / an.esize) != 0;
+  const int strided = (an.x_kfast && !(runs && an.P[0].sx == 1)) + (an.y_kfast && !(runs && an.P[0].sy == 1));
+  const int rows = !an.x_kfast + !an.y_kfast;
+  const bool alone = ns == 2 && (strided == 2 || rows == 2);
+  const double bf16 = ns == 3 ? (strided == 2 ? 2.25 : strided ? 1.6 : rows == 2 ? 1.85 : 1.5)
+                              : strided == 2 ? 2.15 : rows == 2 ? 1.15 : strided ? 2.4 : rows ? 1.85 : 1.55;
+  const RoundModel m{128, 128, (alone ? 1 : 2) * (int64_t)(h ? h->num_cus : 256),
+                     ns ? bf16 : an.esize == 8 ? 1.95 : 3.8, 9.0, 128.0 * 128.0 * (ns ? 8.0 : (double)an.esize),
+                     alone ? 1.0 : 0.77};
   const int64_t tiles = ceil_div(an.M, 128) * ceil_div(an.N, 128) * an.L, nk = ceil_div(kd, t.bk);
   const double whole = m.rounds(tiles, (double)nk);
   double now = whole;

@@ -11,7 +11,7 @@ import pytest
 from tests.famlies_testutil import U64, bf16x3_bound, gamma
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SIZES = [(4096, 4096, 4096), (3001, 2999, 3003), (2048, 2048, 1024)]  # the last one's pass costs too much
+SIZES = [(4096, 4096, 4096), (3001, 2999, 3003), (1024, 1024, 64)]  # the last is too small
 
 
 def _descs(fm, m, n, k):
