@@ -129,9 +129,11 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
   const int u = 16 / an.esize, ks = 4 * u;
   const int64_t kr = padded_k_length(an, u), K = kr ? kr : an.K;
   // an operand gathered along K but not in 16-byte runs touches a cache line
-  // per element
+  // per element, one gathered by rows without unit stride two lines for one
   const bool xrun = kr && an.P[0].sx == 1, yrun = kr && an.P[0].sy == 1;
-  const double xw = an.x_kfast && !xrun ? 2.5 : 1.0, yw = an.y_kfast && !yrun ? 2.5 : 1.0;
+  const bool xlines = an.x_kfast && !xrun, ylines = an.y_kfast && !yrun;
+  const double xw = xlines ? 2.5 : !an.x_kfast && an.I[0].sx != 1 ? 2.0 : 1.0;
+  const double yw = ylines ? 2.5 : !an.y_kfast && an.J[0].sy != 1 ? 2.0 : 1.0;
   const double unique = ((double)an.M * an.K + (double)an.N * an.K + (double)an.M * an.N) * (double)an.L * es;
   const double hbm_us = unique / 4.3e6;
 
@@ -142,7 +144,7 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
   const double slices = (double)ceil_div(ceil_div(an.K, split_tiles == tiles ? t.split : 1), an.esize == 8 ? 8 : 32);
   const bool full = units > cus;  // two workgroups share a CU
   const double slice_us = t.bm == 64 ? (an.esize == 8 ? (full ? 0.72 : 0.45) : (full ? 1.5 : 0.92))
-                                     : (an.esize == 8 ? 1.9 : xw + yw > 2.0 ? 5.0 : 3.8);
+                                     : (an.esize == 8 ? 1.9 : xlines || ylines ? 5.0 : 3.8);
   double tiled = 3.5 + std::max(std::max(1.0, units / (2.0 * cus)) * slices * slice_us, hbm_us);
   if (t.split > 1) tiled += 4.0 + (double)(t.split + 1) * (double)split_tiles * t.bm * t.bn * es / 4.0e6;
 
@@ -164,7 +166,13 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
         // narrow tiles touch memory in short segments: FP64 16 x 675840 x 64
         // takes 130 us in 16 x 16 tiles, 120 in 32 x 32, 108 in 16 x 64
         const double mem_us = hbm_us * (sh[0] * sh[1] == 256 ? 1.25 : sh[0] == sh[1] ? 1.1 : 1.0);
-        double us = 4.0 + std::max(std::max(std::ceil(steps / wk) * step_us, mfma_us), std::max(l2_us, mem_us));
+        // elements gathered along K: up to 64 lines per load, which the larger
+        // tiles wait for (FP32 300^3 strided on both sides: 17.7 us in 32 x 32
+        // tiles, 9.8 in 16 x 16, tiled 11.1)
+        const double lines = 64.0 * u * ((xlines ? sh[0] : 0) + (ylines ? sh[1] : 0)) / 16.0;
+        const double line_us = std::ceil(n / cus) * steps * lines / (sh[0] * sh[1] == 256 ? 3.0e3 : 1.5e3);
+        double us = 4.0 + std::max(std::max(std::max(std::ceil(steps / wk) * step_us, mfma_us), std::max(l2_us, mem_us)),
+                                   line_us);
         if (wk > 1) us += 0.0012 * n;  // the waves' partial tiles through LDS
         if (split > 1) us += 4.0 + (double)(split + 1) * (double)an.M * (double)an.N * es / 4.0e6;
         const int64_t of_wave = ceil_div((int64_t)steps, wk);
