@@ -164,8 +164,12 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
         const double step_us = sh[0] * sh[1] == 256 ? (an.esize == 8 ? 0.20 : 0.27) : 0.43;
         const double mfma_us = n * sh[0] * sh[1] * steps * ks * 2.0 / (an.esize == 8 ? 6.0e7 : 1.2e8);
         // narrow tiles touch memory in short segments: FP64 16 x 675840 x 64
-        // takes 130 us in 16 x 16 tiles, 120 in 32 x 32, 108 in 16 x 64
-        const double mem_us = hbm_us * (sh[0] * sh[1] == 256 ? 1.25 : sh[0] == sh[1] ? 1.1 : 1.0);
+        // takes 130 us in 16 x 16 tiles, 120 in 32 x 32, 108 in 16 x 64; with
+        // its 64 side on the short side a tile is as narrow as 16 x 16 and does
+        // four times the products (FP64 500000 x 16 x 64:
+        // 175 us in 16 x 64 tiles, 74 in 64 x 16, tiled 114)
+        const int64_t reach = std::max(std::min<int64_t>(sh[0], an.M), std::min<int64_t>(sh[1], an.N));
+        const double mem_us = hbm_us * (reach <= 16 ? 1.25 : reach <= 32 ? 1.1 : 1.0);
         // elements gathered along K: up to 64 lines per load, which the larger
         // tiles wait for (FP32 300^3 strided on both sides: 17.7 us in 32 x 32
         // tiles, 9.8 in 16 x 16, tiled 11.1)

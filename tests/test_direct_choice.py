@@ -37,3 +37,14 @@ def test_strided_operands_do_not_take_large_direct_tiles():
     # a small one keeps the direct kernel
     assert all(routes([_strided(1, 24, 24, 200)]))
 
+
+def test_long_sides_are_walked_in_long_segments():
+    """64 x 16 wave tiles where the kernel's M is the long side, 16 x 64 where N
+    is (or 32 x 32), so that memory is touched in segments of 64 elements."""
+    for dt in (1, 2):
+        for big, k in ((500000, 64), (799223, 64)):
+            tall = [dt, [[big, k], [1, big]], [[k, 14], [1, k]], [14, 1]]
+            wide = [dt, [[14, k], [k, 1]], [[k, big], [big, 1]], [big, 1]]
+            t, w = routes([tall, wide])
+            assert t and t[:2] in ((64, 16), (32, 32)), (dt, big, k, t)
+            assert w and w[:2] in ((16, 64), (32, 32)), (dt, big, k, w)
