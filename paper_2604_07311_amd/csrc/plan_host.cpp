@@ -132,8 +132,8 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
   // per element, one gathered by rows without unit stride two lines for one
   const bool xrun = kr && an.P[0].sx == 1, yrun = kr && an.P[0].sy == 1;
   const bool xlines = an.x_kfast && !xrun, ylines = an.y_kfast && !yrun;
-  const double xw = xlines ? 2.5 : !an.x_kfast && an.I[0].sx != 1 ? 2.0 : 1.0;
-  const double yw = ylines ? 2.5 : !an.y_kfast && an.J[0].sy != 1 ? 2.0 : 1.0;
+  const double xw = xlines ? 2.5 : !an.x_kfast && !an.I.empty() && an.I[0].sx != 1 ? 2.0 : 1.0;
+  const double yw = ylines ? 2.5 : !an.y_kfast && !an.J.empty() && an.J[0].sy != 1 ? 2.0 : 1.0;
   const double unique = ((double)an.M * an.K + (double)an.N * an.K + (double)an.M * an.N) * (double)an.L * es;
   const double hbm_us = unique / 4.3e6;
 
