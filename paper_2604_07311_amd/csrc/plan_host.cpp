@@ -356,13 +356,13 @@ bool choose_planes(const famlies_handle_s* h, const Analysis& an, int64_t kd, co
   if (split_us >= 1e30) return false;  // 64 x 64 tiles: operands that small are read too few times over
   const int ns = split_parts(an.compute);
   const int64_t tiles = ceil_div(an.M, 256) * ceil_div(an.N, 128) * an.L, nk = ceil_div(kd, 32);
-  const double pass = (double)(an.M + an.N) * (double)kd * (double)an.L * (4.0 + 2.0 * ns) / 5.5e6 + 8.0;
+  const double pass = (double)(an.M + an.N) * (double)kd * (double)an.L * (4.0 + 2.0 * ns) / 5.5e6 + 11.0;
   if (chain.cut > 0) {
     *fold = planes_fold_steps(ns, chain.length);
     if (*fold == 0) return false;
   }
   const double slice = (ns == 2 ? 1.4 : 2.3) + (*fold ? 13.0 / *fold : 0.0);
-  const RoundModel m{256, 128, h ? h->num_cus : 256, slice, 9.0, 256.0 * 128.0 * 8.0, 1.0};
+  const RoundModel m{256, 128, h ? h->num_cus : 256, slice, 11.0, 256.0 * 128.0 * 8.0, 1.0};
   double best = 0.93 * split_us - pass;
   *lv = LevelCfg();
   bool take = false;

@@ -127,7 +127,7 @@ constexpr int kPlStages = NS == 2 ? 3 : 2;
 static_assert(planes_turn(2) == 2 * kPlStages<2> && planes_turn(3) == 2 * kPlStages<3>, "steps of the K loop");
 constexpr int kPlFold = kPlBM * kPlBN;  // elements of a workgroup's running sums
 
-// fold > 0: every `fold` steps (whole turns) the hh accumulators move into
+// FOLD: every `fold` steps (whole turns) the hh accumulators move into
 // running sums in `sums`, so that no chain of additions is longer than the K
 // ranges of the plan's split_contract launch (ChainCfg; bf16x6 with K in one
 // chain had 1.5 to 2.2 times the error).  The addition is exact: its rounding
@@ -138,7 +138,7 @@ constexpr int kPlFold = kPlBM * kPlBN;  // elements of a workgroup's running sum
 // in one chain, 619 with two folds).  K ranges in workgroups of their own with
 // FP64 partial sums, as split_contract has them, move three times the bytes
 // and fill their rounds less well: 723 us.
-template <int NS>
+template <int NS, bool FOLD>
 __global__ __launch_bounds__(512, 2) void planes_contract(PlainArgs<uint32_t> a, const unsigned char* xp,
                                                           const unsigned char* yp, int xt, int yt, int nkb, int fold,
                                                           float* sums) {
@@ -267,6 +267,7 @@ __global__ __launch_bounds__(512, 2) void planes_contract(PlainArgs<uint32_t> a,
         }
   };
   if (st0 < st1) {
+    bool folded = false;
     Frag fa, fb;
     fetch(s0, st0);
     fetch(s1, st0 + 1);
@@ -285,34 +286,49 @@ __global__ __launch_bounds__(512, 2) void planes_contract(PlainArgs<uint32_t> a,
       return st + 1 < st1;
     };
     // Several rounds of the stages per turn: at the head of a loop the
-    // compiler waits for every load before it reads LDS.  False after the
-    // last step.
-    auto turn = [&](int st) {
-      if constexpr (NST == 3)
-        return step(s0, s1, st) && step(s1, s2, st + 1) && step(s2, s0, st + 2) && step(s0, s1, st + 3) &&
-               step(s1, s2, st + 4) && step(s2, s0, st + 5);
-      else
-        return step(s0, s1, st) && step(s1, s0, st + 1) && step(s0, s1, st + 2) && step(s1, s0, st + 3);
-    };
-    // From fold to fold: the first fragments are read again after it, so that
-    // none are held through it (with them, 48 registers went to scratch).
-    int st = st0, end = fold > 0 ? st0 + fold : 0x7fffffff;
-    for (;;) {
+    // compiler waits for every load before it reads LDS.
+    if constexpr (!FOLD) {  // (apart: with the loop below bf16x3 was 4 % slower)
       read(fa, s0, 0);
-      bool more;
-      do {
-        more = turn(st);
-        st += planes_turn(NS);
-      } while (more && st < end);
-      if (!more) break;
-      if (end == st0 + fold)
-        fold_sums(std::integral_constant<int, 0>{});
-      else
-        fold_sums(std::integral_constant<int, 1>{});
-      end += fold;
+      if constexpr (NST == 3) {
+        for (int st = st0;; st += 6)
+          if (!step(s0, s1, st) || !step(s1, s2, st + 1) || !step(s2, s0, st + 2) || !step(s0, s1, st + 3) ||
+              !step(s1, s2, st + 4) || !step(s2, s0, st + 5))
+            break;
+      } else {
+        for (int st = st0;; st += 4)
+          if (!step(s0, s1, st) || !step(s1, s0, st + 1) || !step(s0, s1, st + 2) || !step(s1, s0, st + 3)) break;
+      }
+    } else {
+      // a turn; false after the last step
+      auto turn = [&](int st) {
+        if constexpr (NST == 3)
+          return step(s0, s1, st) && step(s1, s2, st + 1) && step(s2, s0, st + 2) && step(s0, s1, st + 3) &&
+                 step(s1, s2, st + 4) && step(s2, s0, st + 5);
+        else
+          return step(s0, s1, st) && step(s1, s0, st + 1) && step(s0, s1, st + 2) && step(s1, s0, st + 3);
+      };
+      // From fold to fold: the first fragments are read again after it, so that
+      // none are held through it (with them, 48 registers went to scratch).
+      int end = st0 + fold;
+      for (int st = st0;;) {
+        read(fa, s0, 0);
+        bool more;
+        do {
+          more = turn(st);
+          st += planes_turn(NS);
+        } while (more && st < end);
+        if (!more) break;
+        if (end == st0 + fold)
+          fold_sums(std::integral_constant<int, 0>{});
+        else
+          fold_sums(std::integral_constant<int, 1>{});
+        end += fold;
+      }
+      folded = end > st0 + fold;
     }
     __builtin_amdgcn_s_waitcnt(0);  // the clamped loads of the last steps have landed
-    if (fold > 0 && end > st0 + fold) fold_sums(std::integral_constant<int, 2>{});
+    if constexpr (FOLD)
+      if (folded) fold_sums(std::integral_constant<int, 2>{});
   }
   auto total = [&](int i, int j, int e) { return (double)acc[1][i][j][e] + (double)acc[0][i][j][e]; };
   if (block >= 0) {
@@ -416,8 +432,12 @@ static hipError_t launch_planes_ns(const PlainArgs<uint32_t>& a0, int xmode, int
   lv.parts = a.lev_parts;
   const int grid = (int)planes_grid((int64_t)a.tiles_m * a.tiles_n * a.L, lv);
   float* sums = reinterpret_cast<float*>(static_cast<char*>(a.work) + (size_t)lv.blocks() * (kPlBM * kPlBN) * 8);
-  hipLaunchKernelGGL(planes_contract<NS>, dim3(grid), dim3(512), 0, s, a, xq, yq, (int)lay.xt, (int)lay.yt,
-                     (int)lay.nkb, fold, sums);
+  if (fold > 0)
+    hipLaunchKernelGGL((planes_contract<NS, true>), dim3(grid), dim3(512), 0, s, a, xq, yq, (int)lay.xt, (int)lay.yt,
+                       (int)lay.nkb, fold, sums);
+  else
+    hipLaunchKernelGGL((planes_contract<NS, false>), dim3(grid), dim3(512), 0, s, a, xq, yq, (int)lay.xt,
+                       (int)lay.yt, (int)lay.nkb, fold, sums);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && a.rem > 0) e = launch_level_reduce(FAMLIES_F32, true, a, kPlBM, s);
   return e;
