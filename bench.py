@@ -301,6 +301,19 @@ def plan_signature(info):
                                                    info["index_bits"])
 
 
+def launch_shape(info):
+    """The kernel that a plan's launches run: its tile and K ranges (the direct
+    kernel's are not in the plan's summary)."""
+    tile = [info["tile_m"], info["tile_n"], info["tile_k"]]
+    if info["kernel"] & 256:
+        return {"tile": [256, 128, 32], "split_k": 1, "route": "part planes"}
+    if info["kernel"] & 128:
+        return {"tile": tile, "split_k": 1, "route": "levelled last round"}
+    if info["kernel"] & 64:
+        return {"tile": None, "split_k": None, "route": "direct"}
+    return {"tile": tile, "split_k": info["split_k"], "route": "tiled"}
+
+
 def traffic(key, info):
     rec = TRAFFIC.get(key)
     if rec is None or rec["sources"] != kernel_sources_sha() or rec["plan"] != plan_signature(info):
@@ -360,8 +373,7 @@ def wl_ladder(args):
                       {"workload": "ccsd_ladder_v%d_o%d" % (args.v, args.o),
                        "contraction": "C[a,b,i,j] += sum_ef W[a,b,e,f] T[e,f,i,j]; W stored (e,a,f,b)",
                        "m": r["info"]["m"], "n": r["info"]["n"], "k": r["info"]["k"],
-                       "tile": [r["info"]["tile_m"], r["info"]["tile_n"], r["info"]["tile_k"]],
-                       "split_k": r["info"]["split_k"]})
+                       **launch_shape(r["info"])})
     out["pct_mfma_peak"] = round(100 * flops / (r["ms"] * 1e-3) / PEAK[head], 2)
     out["error_vs_fp64"] = r["check"]
     out["roofline"] = roofline(flops, r["launch"], PEAK[head], key=("ladder", head, args.v, args.o),
@@ -439,8 +451,7 @@ def ring_precisions(args):
         name = "fp64" if dtype == "f64" else ("fp32" if comp == "native" else comp)
         res[name] = {"value": round(flops / (ms * 1e-3) / 1e9, 2), "unit": "GFLOP/s (2MNK/t)",
                      "ms_per_step": round(ms, 4), "error_vs_fp64": check,
-                     "tile": [s.info["tile_m"], s.info["tile_n"], s.info["tile_k"]],
-                     "split_k": s.info["split_k"], "kernel": s.info["kernel"],
+                     **launch_shape(s.info), "kernel": s.info["kernel"],
                      "roofline": roofline(issued * flops, launch, PEAK[peak])}
         log("ring %s %s: %.3f ms (%.1f GFLOP/s) check %s" % (dtype, comp, ms, flops / ms / 1e6, check))
         s.close()
@@ -546,8 +557,7 @@ def wl_plain16(args):
     flops = s.info["flops"]
     out = base_record(args, flops / (ms * 1e-3) / 1e9, ms, "f64",
                       {"workload": "plain16", "m": 256, "n": 256, "k": 256,
-                       "tile": [s.info["tile_m"], s.info["tile_n"], s.info["tile_k"]],
-                       "split_k": s.info["split_k"]})
+                       **launch_shape(s.info)})
     out["latency_us_single_call"] = round(ms * 1e3, 2)
     out["latency_us_per_call_in_graph"] = round(per_call_graph * 1e3, 2)
     out["gflops_in_graph"] = round(flops / (per_call_graph * 1e-3) / 1e9, 2)

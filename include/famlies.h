@@ -151,7 +151,11 @@ typedef struct {
                                offsets, see index_elements; 64: element offsets) */
   int32_t kernel;           /* 1 plain, 3 bf16x3, 4 bf16x6 (1 + bf16 parts per operand), 8 + s FP64 on INT8 with s
                                slices; +16 / +32 when the kernel reads X / Y from affine unit-stride K blocks with
-                               16-byte loads (block strides) */
+                               16-byte loads (block strides).  famlies_plan_get_info adds the route that the plan's
+                               launches take instead of the tile choice reported here (tile_*, split_k,
+                               split_tiles), which then only lays out pre-packed operands: +64 the direct kernel,
+                               +128 the tiles with a levelled last round instead of split_k, +256 part planes in
+                               256 x 128 tiles with 32-deep steps */
   int32_t split_tiles;      /* split_k > 1: how many tiles run as K slices (the last ones in
                                tile order; the others run whole first); 0 without split-K */
   double flops;             /* 2*batch*m*n*k */

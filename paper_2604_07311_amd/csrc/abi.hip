@@ -509,7 +509,8 @@ famlies_status famlies_plan_get_info(famlies_plan tok, famlies_plan_info* info) 
     batch_info(p->batch, info);
     return FAMLIES_OK;
   }
-  fill_info(p->an, p->cfg, p->index_bits, kernel_code(p->an, p->x_vec, p->y_vec), info);
+  const int route = p->planes ? 256 : p->direct.bm ? 64 : p->level.rem ? 128 : 0;
+  fill_info(p->an, p->cfg, p->index_bits, kernel_code(p->an, p->x_vec, p->y_vec) + route, info);
   info->index_elements = p->index_bits == 64 || p->elem32;
   return FAMLIES_OK;
 }
