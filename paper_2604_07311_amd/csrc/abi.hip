@@ -66,14 +66,13 @@ DeviceGuard::~DeviceGuard() {
   if (prev >= 0) (void)hipSetDevice(prev);
 }
 
-// Rows and contracted offsets of an operand's pre-packed form -- block
-// (tile, kb) of br x bk elements, [row][k] -- for the direct kernel, which
-// then reads a packed operand like any other and sums in the same order.
-static void packed_vectors(int64_t rows, int64_t kd, int64_t kp, int br, int bk, int64_t es, uint32_t* pr,
-                           uint32_t* pk) {
-  const int64_t nkb = ceil_div(kd, bk);
-  for (int64_t r = 0; r < rows; ++r) pr[r] = (uint32_t)((r / br * nkb * br * bk + r % br * bk) * es);
-  for (int64_t k = 0; k < kp; ++k) pk[k] = k < nkb * bk ? (uint32_t)((k / bk * br * bk + k % bk) * es) : 0u;
+// Contracted offsets of an operand's pre-packed form -- block (tile, kb) of br x
+// bk elements, [row][k] -- for the direct kernel, which then reads a packed
+// operand like any other and sums in the same order (it works out the rows).
+static void packed_ks(int64_t kd, int br, int bk, int64_t es, std::vector<uint32_t>* pk) {
+  const int64_t n = ceil_div(kd, bk) * bk;
+  for (int64_t k = 0; k < (int64_t)pk->size(); ++k)
+    (*pk)[(size_t)k] = k < n ? (uint32_t)((k / bk * br * bk + k % bk) * es) : 0u;
 }
 
 template <typename OffT>
@@ -129,14 +128,13 @@ static famlies_status index_image(famlies_plan_s* p, const PlanUse& use, int64_t
     if (an.y_kfast) p->ymode = p->dy_vec ? run : 1;
   }
   for (int i = 1; i <= 2; ++i) v[i].resize((size_t)kp);
-  std::vector<uint32_t> packed[4];  // direct kernel: rows and k's of a packed X, then of a packed Y
+  std::vector<uint32_t> packed[2];  // direct kernel: k's of a packed X, of a packed Y
   if (p->direct.bm && bytes && !use.scratch)
     for (int op = 0; op < 2; ++op) {
       const int64_t rows = op ? np : mp;
       const int br = op ? p->cfg.bn : p->cfg.bm;
-      packed[2 * op].resize((size_t)rows);
-      packed[2 * op + 1].resize((size_t)kp);
-      packed_vectors(rows, p->kd, kp, br, p->cfg.bk, es, packed[2 * op].data(), packed[2 * op + 1].data());
+      packed[op].resize((size_t)kp);
+      packed_ks(p->kd, br, p->cfg.bk, es, &packed[op]);
       p->pk_fits[op] = rows * ceil_div(p->kd, p->cfg.bk) * p->cfg.bk * es < ((int64_t)1 << 32);
     }
   // rows and contracted offsets are rebased each by its own lowest, so every
@@ -162,7 +160,7 @@ static famlies_status index_image(famlies_plan_s* p, const PlanUse& use, int64_t
         o[pos++] = (OffT)x;
     }
   }
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < 2; ++i) {
     p->pk_pos[i] = pos;
     for (uint32_t x : packed[i]) o[pos++] = (OffT)x;
   }
@@ -663,16 +661,27 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
     if (p->direct.bm && (extra || p->direct.split == 1) && L.kind == PlainLaunch::kMain && (!xp || p->pk_fits[0]) && (!yp || p->pk_fits[1])) {
       const DirectCfg& d = p->direct;
       const uint32_t* o = static_cast<const uint32_t*>(p->d_off);
-      if (xp) a.xmn = o + p->pk_pos[0], a.xk = o + p->pk_pos[1];
-      if (yp) a.ymn = o + p->pk_pos[2], a.yk = o + p->pk_pos[3];
-      const int64_t xplane = xp ? (int64_t)a.tiles_m * a.x_nkb * L.bm * L.bk : 0;
-      const int64_t yplane = yp ? (int64_t)a.tiles_n * a.y_nkb * L.bn * L.bk : 0;
+      DirectPacked xd, yd;
+      auto packed = [&](DirectPacked* q, int tiles, int nkb, int br) {
+        q->plane = (int64_t)tiles * nkb * br * L.bk;
+        q->shift = __builtin_ctz((unsigned)br);
+        q->row = (uint32_t)(L.bk * an.esize);
+        q->tile = (uint32_t)nkb * (uint32_t)br * q->row;
+      };
+      if (xp) {
+        a.xk = o + p->pk_pos[0];
+        packed(&xd, a.tiles_m, a.x_nkb, L.bm);
+      }
+      if (yp) {
+        a.yk = o + p->pk_pos[1];
+        packed(&yd, a.tiles_n, a.y_nkb, L.bn);
+      }
       a.tiles_m = (int32_t)ceil_div(an.M, d.bm);
       a.tiles_n = (int32_t)ceil_div(an.N, d.bn);
       a.splits = d.split;
       a.kchunk = d.kchunk;
       a.head = 0;
-      e = launch_direct(an.dtype, a, d, xp || p->dx_vec, yp || p->dy_vec, xplane, yplane, s);
+      e = launch_direct(an.dtype, a, d, xp || p->dx_vec, yp || p->dy_vec, xd, yd, s);
       if (e == hipSuccess && d.split > 1) e = launch_splitk_reduce(an.dtype, false, a, d.bm, d.bn, s);
     } else {
       e = launch_plain(an.dtype, a, L, s);

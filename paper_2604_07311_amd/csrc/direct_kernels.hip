@@ -60,9 +60,12 @@ struct DirectOperand {
   off_t ko[D];
   T v[D][NBK][U];
 
-  __device__ __forceinline__ void init(const uint32_t* __restrict__ rows, int row0) {
+  __device__ __forceinline__ void init(const uint32_t* __restrict__ rows, const DirectPacked& p, int row0) {
 #pragma unroll
-    for (int i = 0; i < NBK; ++i) mn[i] = rows[row0 + 16 * i];
+    for (int i = 0; i < NBK; ++i) {
+      const uint32_t row = (uint32_t)(row0 + 16 * i);
+      mn[i] = p.plane ? (row >> p.shift) * p.tile + (row & ((1u << p.shift) - 1u)) * p.row : rows[row];
+    }
   }
   // contracted offsets of this lane's run at k (a multiple of U)
   template <int S>
@@ -89,8 +92,8 @@ struct DirectOperand {
 // planner needs the chains of additions short (DirectCfg); their registers
 // cost a wave per SIMD in the FP64 tiles of four blocks, so not elsewhere.
 template <typename T, int MB, int NB, bool XV, bool YV, int NW, int CH>
-__global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a, int wk, int64_t xplane,
-                                                           int64_t yplane) {
+__global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a, int wk, DirectPacked xp,
+                                                           DirectPacked yp) {
   using MF = Mfma16<T>;
   constexpr int U = 16 / (int)sizeof(T), KS = 4 * U, BM = 16 * MB, BN = 16 * NB;
   constexpr int D = 3;
@@ -109,14 +112,14 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
   const int ls = (int)(unit / ntiles);
   const int l = ls / a.splits, split = ls % a.splits;
   const int m0 = (t % a.tiles_m) * BM, n0 = (t / a.tiles_m) * BN;
-  const T* X = static_cast<const T*>(a.x) + (xplane ? l * xplane : a.xl[l]);
-  const T* Y = static_cast<const T*>(a.y) + (yplane ? l * yplane : a.yl[l]);
+  const T* X = static_cast<const T*>(a.x) + (xp.plane ? l * xp.plane : a.xl[l]);
+  const T* Y = static_cast<const T*>(a.y) + (yp.plane ? l * yp.plane : a.yl[l]);
   const int kbeg = split * a.kchunk, kend = min(a.K, kbeg + a.kchunk);
 
   DirectOperand<T, MB, XV, D> gx;
   DirectOperand<T, NB, YV, D> gy;
-  gx.init(a.xmn, m0 + r);
-  gy.init(a.ymn, n0 + r);
+  gx.init(a.xmn, xp, m0 + r);
+  gy.init(a.ymn, yp, n0 + r);
   typename MF::Acc acc[CH][MB][NB];
 #pragma unroll
   for (int c = 0; c < CH; ++c)
@@ -263,40 +266,40 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
 }
 
 template <typename T, int MB, int NB, bool XV, bool YV>
-static hipError_t launch_nw(const PlainArgs<uint32_t>& a, const DirectCfg& d, int64_t xplane, int64_t yplane,
+static hipError_t launch_nw(const PlainArgs<uint32_t>& a, const DirectCfg& d, const DirectPacked& xp, const DirectPacked& yp,
                             hipStream_t s) {
   const int64_t units = (int64_t)a.tiles_m * a.tiles_n * a.splits * a.L;
   const int grid = (int)(d.wk == 1 ? (units + 3) / 4 : units);
   if (d.chains == 3)
-    hipLaunchKernelGGL((direct_contract<T, MB, NB, XV, YV, 4, 3>), dim3(grid), dim3(256), 0, s, a, d.wk, xplane, yplane);
+    hipLaunchKernelGGL((direct_contract<T, MB, NB, XV, YV, 4, 3>), dim3(grid), dim3(256), 0, s, a, d.wk, xp, yp);
   else
-    hipLaunchKernelGGL((direct_contract<T, MB, NB, XV, YV, 4, 1>), dim3(grid), dim3(256), 0, s, a, d.wk, xplane, yplane);
+    hipLaunchKernelGGL((direct_contract<T, MB, NB, XV, YV, 4, 1>), dim3(grid), dim3(256), 0, s, a, d.wk, xp, yp);
   return hipGetLastError();
 }
 
 template <typename T, int MB, int NB>
-static hipError_t launch_modes(const PlainArgs<uint32_t>& a, const DirectCfg& d, bool xv, bool yv, int64_t xplane,
-                               int64_t yplane, hipStream_t s) {
-  if (xv && yv) return launch_nw<T, MB, NB, true, true>(a, d, xplane, yplane, s);
-  if (xv) return launch_nw<T, MB, NB, true, false>(a, d, xplane, yplane, s);
-  if (yv) return launch_nw<T, MB, NB, false, true>(a, d, xplane, yplane, s);
-  return launch_nw<T, MB, NB, false, false>(a, d, xplane, yplane, s);
+static hipError_t launch_modes(const PlainArgs<uint32_t>& a, const DirectCfg& d, bool xv, bool yv, const DirectPacked& xp,
+                               const DirectPacked& yp, hipStream_t s) {
+  if (xv && yv) return launch_nw<T, MB, NB, true, true>(a, d, xp, yp, s);
+  if (xv) return launch_nw<T, MB, NB, true, false>(a, d, xp, yp, s);
+  if (yv) return launch_nw<T, MB, NB, false, true>(a, d, xp, yp, s);
+  return launch_nw<T, MB, NB, false, false>(a, d, xp, yp, s);
 }
 
 template <typename T>
-static hipError_t launch_direct_t(const PlainArgs<uint32_t>& a, const DirectCfg& d, bool xv, bool yv, int64_t xplane,
-                                  int64_t yplane, hipStream_t s) {
-  if (d.bm == 16 && d.bn == 16) return launch_modes<T, 1, 1>(a, d, xv, yv, xplane, yplane, s);
-  if (d.bm == 32 && d.bn == 32) return launch_modes<T, 2, 2>(a, d, xv, yv, xplane, yplane, s);
-  if (d.bm == 16 && d.bn == 64) return launch_modes<T, 1, 4>(a, d, xv, yv, xplane, yplane, s);
-  if (d.bm == 64 && d.bn == 16) return launch_modes<T, 4, 1>(a, d, xv, yv, xplane, yplane, s);
+static hipError_t launch_direct_t(const PlainArgs<uint32_t>& a, const DirectCfg& d, bool xv, bool yv, const DirectPacked& xp,
+                                  const DirectPacked& yp, hipStream_t s) {
+  if (d.bm == 16 && d.bn == 16) return launch_modes<T, 1, 1>(a, d, xv, yv, xp, yp, s);
+  if (d.bm == 32 && d.bn == 32) return launch_modes<T, 2, 2>(a, d, xv, yv, xp, yp, s);
+  if (d.bm == 16 && d.bn == 64) return launch_modes<T, 1, 4>(a, d, xv, yv, xp, yp, s);
+  if (d.bm == 64 && d.bn == 16) return launch_modes<T, 4, 1>(a, d, xv, yv, xp, yp, s);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_direct(int dtype, const PlainArgs<uint32_t>& a, const DirectCfg& d, bool xv, bool yv,
-                         int64_t xplane, int64_t yplane, hipStream_t s) {
-  return dtype == FAMLIES_F64 ? launch_direct_t<double>(a, d, xv, yv, xplane, yplane, s)
-                              : launch_direct_t<float>(a, d, xv, yv, xplane, yplane, s);
+                         const DirectPacked& xp, const DirectPacked& yp, hipStream_t s) {
+  return dtype == FAMLIES_F64 ? launch_direct_t<double>(a, d, xv, yv, xp, yp, s)
+                              : launch_direct_t<float>(a, d, xv, yv, xp, yp, s);
 }
 
 }  // namespace famlies

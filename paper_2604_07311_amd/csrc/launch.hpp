@@ -18,8 +18,16 @@ struct PlainLaunch {
 hipError_t launch_plain(int dtype, const PlainArgs<uint32_t>& a, const PlainLaunch& L, hipStream_t s);
 hipError_t launch_plain(int dtype, const PlainArgs<int32_t>& a, const PlainLaunch& L, hipStream_t s);
 hipError_t launch_plain(int dtype, const PlainArgs<int64_t>& a, const PlainLaunch& L, hipStream_t s);
+// A pre-packed operand of the direct kernel: elements of a batch plane (0: not
+// packed), rows of a tile (their logarithm), bytes of a tile of rows over all
+// of K and between rows of a block.
+struct DirectPacked {
+  int64_t plane = 0;
+  int32_t shift = 0;
+  uint32_t tile = 0, row = 0;
+};
 hipError_t launch_direct(int dtype, const PlainArgs<uint32_t>& a, const DirectCfg& d, bool xv, bool yv,
-                         int64_t xplane, int64_t yplane, hipStream_t s);
+                         const DirectPacked& xp, const DirectPacked& yp, hipStream_t s);
 // C = alpha * sum over K ranges of W + beta * C for the split tiles (bm x bn blocks of partial sums).
 // bf16: the partial sums are FP64 (split-bf16 kernels).
 template <typename OffT>

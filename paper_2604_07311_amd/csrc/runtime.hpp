@@ -91,7 +91,7 @@ struct famlies_plan_s {
   famlies::DirectCfg direct;                // bm > 0: native kMain launches run the direct kernel
   bool dx_vec = false, dy_vec = false;      // every run of 16 bytes of X / Y along K is contiguous
   bool pk_fits[2] = {false, false};         // direct kernel: 32-bit offsets reach all of the pre-packed X / Y
-  size_t pk_pos[4] = {0, 0, 0, 0};          // direct kernel, pre-packed operands: X rows, X k, Y rows, Y k
+  size_t pk_pos[2] = {0, 0};                // direct kernel, pre-packed operands: contracted offsets of X, of Y
   bool table_hit = false;  // the tile came from the handle's tile table
   void* d_work = nullptr;  // split-K partial sums
   size_t work_bytes = 0;
