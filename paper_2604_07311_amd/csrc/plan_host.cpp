@@ -109,8 +109,8 @@ TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_t
 // pays a barrier and a memory round trip per K slice and, with split-K, a
 // second launch.  Both are estimated in microseconds from constants measured
 // on MI355X and the smaller wins.  Examples, tiled -> direct: FP64 256^3
-// 11.0 -> 5.8 us, FP64 144 x 1444 x 1444 34 -> 26, FP32 900^3 (runs of 30)
-// 42 -> 31, FP64 16 x 675840 x 64 142 -> 108; the other way FP32 256 x 4096 x
+// 12.2 -> 5.6 us, FP64 144 x 1444 x 1444 33 -> 24, FP32 900^3 (runs of 30)
+// 39 -> 27, FP64 16 x 675840 x 64 132 -> 108; the other way FP32 256 x 4096 x
 // 4096 takes 78 tiled and 125 direct, so direct is not considered above 4
 // GFLOP except for narrow problems.
 //
@@ -201,11 +201,12 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
 // the CU's rate.  Two ways to cut the last round's tiles are weighed: evenly
 // into 2 to 8 runs, or a long first part beside shorter runs on the slots
 // that are free; the second moves fewer bytes, but its workgroups are at
-// different places of K and share less in L2 (6 % charged).  Measured against
-// no split and the best even split with a plain reduction: FP32 ladder v=93
-// o=27 (408 tiles) 1104 and 960 -> 924 us in five even runs, 945 uneven; FP32
-// ring o=31 v=115 981 and 894 -> 808; bf16x6 ring o=31 v=115 638 and 727 ->
-// 585; bf16x3 ring o=48 v=192 5590 -> 5500.
+// different places of K and share less in L2 (6 % charged): FP32 ladder v=93
+// o=27 (408 tiles), unsplit 1104 us, five even runs 924, uneven 945.  Where
+// the tile choice cuts every tile along K the runs keep its chains (ChainCfg),
+// which costs a little of that; measured against K ranges of every tile with
+// a plain reduction: that ladder 1092 -> 958 us, FP32 ring o=31 v=115 896 ->
+// 814.
 namespace {
 struct RoundModel {
   int bm, bn;
@@ -345,11 +346,12 @@ bool tall_tile(const Analysis& an, const TileCfg& t, int64_t runs) {
 // The pass over the operands at 5.5 TB/s and tiles of twice the size, one per
 // CU, against the estimate of the kernel that splits while staging.  Taken 7 %
 // or more below it; measured on either side of the line: bf16x3 ladder o=27
-// v=93 484 us split while staging (estimated 530 through planes), ladder o=36
-// v=110 1824 -> 1552, ring o=32 v=112 363 -> 323.
+// v=93 489 us split while staging (estimated 530 through planes), ladder o=36
+// v=110 1824 -> 1582, ring o=32 v=112 363 -> 308.
 //
 // A plan that splits every tile along K keeps its chains here by folds
-// (ChainCfg): 13 us per fold and round.
+// (ChainCfg): 13 us per fold and round (bf16x6 ring o=31 v=115: 526 us without
+// them, 561 with, 719 split while staging).
 bool choose_planes(const famlies_handle_s* h, const Analysis& an, int64_t kd, const ChainCfg& chain, double split_us,
                    LevelCfg* lv, int* fold) {
   *fold = 0;
@@ -557,7 +559,8 @@ bool log_enabled() {
 // split, index form -- index_bits 32: uint32 bytes, -32: int32 elements, 64:
 // int64 elements -- and workspace).
 void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d,
-                  const LevelCfg& lv, bool planes, int fold, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit) {
+                  const LevelCfg& lv, bool planes, int fold, int index_bits, bool x_vec, bool y_vec,
+                  size_t work_bytes, bool table_hit) {
   static const char* loader[4] = {"rows", "k-gather", "packed", "k-affine"};
   const int xm = an.x_kfast ? (x_vec ? 3 : 1) : 0, ym = an.y_kfast ? (y_vec ? 3 : 1) : 0;
   static const char* int8_names[8] = {"", "", "", "int8x3", "int8x4", "int8x5", "int8x6", "int8x7"};

@@ -12,11 +12,14 @@
 // element meets many tiles (the planner's estimate).  An operand that the
 // caller keeps pre-packed is kept as its planes.
 //
-// Bound by the matrix cores at the clock they hold under full load, then by
-// the pass.  Measured against split_contract (pass included): ring o=48 v=192
-// bf16x3 5.46 -> 4.44 ms, bf16x6 8.99 -> 7.9 ms; ring o=31 v=115 bf16x3 418
-// -> 317 us, bf16x6 605 -> 520 us; ladder o=36 v=110 bf16x3 1.82 -> 1.55 ms.
-// The pass alone: 113 us for the 340 MB operand of the large ring.
+// Bound by the matrix cores together with the planes' way from the memory-side
+// cache: ring o=48 v=192 bf16x3 has them 58 % busy while 25 GB pass L2 (33 %
+// hits, 5.4 TB/s; the tile order of an XCD shares one operand's panel only);
+// ring o=31 v=115 bf16x6 50 %, 58 % hits.  Measured against split_contract
+// (pass included): ring o=48 v=192 bf16x3 5.58 -> 4.50 ms, bf16x6 9.25 -> 8.12
+// ms; ring o=31 v=115 bf16x3 418 -> 316 us, bf16x6 (with folds) 719 -> 561 us;
+// ladder o=36 v=110 bf16x3 1.82 -> 1.58 ms.  The pass alone: 128 us for the
+// 340 MB operand of the large ring.
 //
 // bf16_planes writes [l][part][tile of 64 rows][64-k block][8-k chunk][row][8
 // k]: a chunk of a tile is 1 KB, moved by one wave in one instruction, and a

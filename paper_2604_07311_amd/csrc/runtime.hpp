@@ -134,8 +134,8 @@ famlies_status no_throw(const char* where, F&& f) {
 constexpr int64_t kExtraBytesMax = (int64_t)8 << 30;
 
 // What a plan is made for.  force (may be null) overrides the tile choice,
-// table: the handle's tile table may; planes, bare: without part planes; without any workspace past the tile
-// choice's own; lean: the smallest image and workspace (plain contracted
+// table: the handle's tile table may; planes: part planes may be taken; bare:
+// no workspace past the tile choice's own; lean: the smallest image and workspace (plain contracted
 // order, no direct kernel, levelled round or part planes); scratch: run once
 // from the static scratch array (nothing for pre-packed operands).
 struct PlanUse {
@@ -167,7 +167,8 @@ inline famlies_plan_s* plan_of(const void* tok) {
 bool log_enabled();
 void log_plan(const famlies_plan_s* p);
 void log_decision(const char* what, const Analysis& an, const TileCfg& cfg, const DirectCfg& d,
-                  const LevelCfg& lv, bool planes, int fold, int index_bits, bool x_vec, bool y_vec, size_t work_bytes, bool table_hit);
+                  const LevelCfg& lv, bool planes, int fold, int index_bits, bool x_vec, bool y_vec,
+                  size_t work_bytes, bool table_hit);
 
 // Internal forms of the ABI calls, on resolved objects.
 // ordered: executions of the plan never overlap (the caller sees to it).
