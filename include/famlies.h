@@ -255,7 +255,11 @@ famlies_status famlies_batch_execute(famlies_plan p, double alpha, double beta,
 famlies_status famlies_pack_size(famlies_plan p, int operand, size_t *bytes);
 famlies_status famlies_pack(famlies_plan p, int operand, const void *src, void *dst, void *stream);
 /* As famlies_execute, where bit 0 of `packed` says A points to a buffer
- * written by famlies_pack (operand 0) and bit 1 the same for B. */
+ * written by famlies_pack (operand 0) and bit 1 the same for B.  A plan whose
+ * kernel reads part planes (+256 in famlies_plan_info.kernel) needs its workspace
+ * where exactly one operand is packed: on another stream than the last such
+ * execution's the call first waits for the device, and a captured one must not
+ * be replayed while another execution of the plan runs. */
 famlies_status famlies_execute_packed(famlies_plan p, double alpha, const void *A, const void *B,
                                       double beta, void *C, int packed, void *stream);
 
