@@ -29,7 +29,10 @@ struct Buffers {
   }
 };
 
-// Median time (ms) of `reps` launches of a plan, after two warm-up launches.
+// Median time (ms) of one execution of a plan over `reps` spans, after two
+// warm-up executions.  A span is as many executions as take about 0.2 ms (at
+// most 32): events around a single short one add microseconds that differ from
+// call to call, more than the routes of a small product do.
 famlies_status time_plan(famlies_plan_s* p, const Buffers& buf, hipStream_t s, int reps, float* ms) {
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess) return fail(FAMLIES_ERR_DEVICE, "hipEventCreate");
@@ -39,14 +42,16 @@ famlies_status time_plan(famlies_plan_s* p, const Buffers& buf, hipStream_t s, i
   }
   std::vector<float> t;
   famlies_status st = FAMLIES_OK;
+  int n = 1;
   for (int r = 0; r < reps + 2 && st == FAMLIES_OK; ++r) {
     (void)hipEventRecord(e0, s);
-    st = execute_impl(p, 1.0, buf.a, buf.b, 0.0, buf.c, 0, s);
+    for (int i = 0; i < n && st == FAMLIES_OK; ++i) st = execute_impl(p, 1.0, buf.a, buf.b, 0.0, buf.c, 0, s);
     (void)hipEventRecord(e1, s);
     if (hipEventSynchronize(e1) != hipSuccess) st = fail(FAMLIES_ERR_DEVICE, "hipEventSynchronize");
     float x = 0.f;
     (void)hipEventElapsedTime(&x, e0, e1);
-    if (r >= 2) t.push_back(x);
+    if (r >= 2) t.push_back(x / (float)n);
+    if (r == 1) n = std::max(1, std::min(32, (int)std::ceil(0.2f / std::max(x, 1e-3f))));
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
@@ -126,8 +131,9 @@ famlies_status tune_plain(famlies_handle_s* h, const Buffers& buf, int64_t cap, 
           }
           // The planner's own plan first (direct kernel, levelled rounds and
           // part planes among its routes; a tile entry switches them off): a
-          // forced tile has to beat it by more than the timing's scatter.
-          float best = 1e30f;
+          // forced tile has to beat it by more than the timing's scatter, which
+          // for calls of 5 to 10 us was up to 0.4 us between runs.
+          float best = 1e30f, own = 0.f;
           TileCfg bcfg;
           for (int c = -1; c < (int)cands.size(); ++c) {
             famlies_plan_s* p = nullptr;
@@ -142,7 +148,8 @@ famlies_status tune_plain(famlies_handle_s* h, const Buffers& buf, int64_t cap, 
             if (st != FAMLIES_OK) return st;
             if (c < 0) {
               eff.bk = 0;
-              ms *= 0.97f;
+              own = ms;
+              ms = 0.97f * ms - 0.0004f;
             }
             if (ms < best) {
               best = ms;
@@ -152,7 +159,7 @@ famlies_status tune_plain(famlies_handle_s* h, const Buffers& buf, int64_t cap, 
           if (log_enabled())
             std::fprintf(stderr, "[famlies] tune plain dtype %d compute %d M %lld N %lld K %lld: %dx%dx%d split %d %.4f ms\n",
                          md.dtype, md.compute, (long long)M, (long long)N, (long long)K, bcfg.bm, bcfg.bn, bcfg.bk,
-                         bcfg.split, bcfg.planner() ? best / 0.97f : best);
+                         bcfg.split, bcfg.planner() ? own : best);
           TileTable::Entry en;
           en.kind = 0;
           en.dtype = md.dtype;

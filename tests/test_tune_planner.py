@@ -39,7 +39,8 @@ def test_tuner_leaves_small_products_to_the_planner(tmp_path):
     fm.famlies_tune(h, path, fm.FAMLIES_TUNE_QUICK | fm.FAMLIES_TUNE_PLAIN_ONLY)
     fm.famlies_destroy(h)
     rows = [ln.split() for ln in open(path) if ln.strip() and not ln.startswith("#")]
-    # 64 x 64 x 1024: one direct launch takes half the time of tiles and their reduction
+    # 64 x 64 x 1024: one direct launch takes no longer than tiles and their
+    # reduction (FP64 8.1 against 9.2 us, FP32 7.5 against 7.4: a tie)
     small = [r for r in rows if r[3:6] == ["6", "6", "10"] and r[2] == "0"]
     assert len(small) == 2 and all(r[8] == "0" for r in small), small
 
