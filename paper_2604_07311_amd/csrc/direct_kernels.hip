@@ -107,16 +107,20 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
   const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int g = lane / 16, r = lane % 16;
   const int ntiles = a.tiles_m * a.tiles_n;
-  // units: (batch index, K range, tile), tile fastest, M fastest within
+  // units: (batch index, K range, tile), tile fastest; within, the side of
+  // fewer tiles, so that the run of tiles of an XCD reads the long operand once
   const int64_t units = (int64_t)ntiles * a.splits * a.L;
   const int64_t wg = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t unit = wk == 1 ? wg * NW + wave : wg;
   if (unit >= units) return;  // wk == 1 only: whole waves, and no barrier follows
   const int wki = wk == 1 ? 0 : wave;
-  const int t = (int)(unit % ntiles);
-  const int ls = (int)(unit / ntiles);
+  const int ls = (int)(unit / ntiles), o = (int)(unit - (int64_t)ls * ntiles);
   const int l = ls / a.splits, split = ls % a.splits;
-  const int m0 = (t % a.tiles_m) * BM, n0 = (t / a.tiles_m) * BN;
+  const bool n_first = a.tiles_n < a.tiles_m;
+  const int fewer = n_first ? a.tiles_n : a.tiles_m, oq = o / fewer, rest = o - oq * fewer;
+  const int pm = n_first ? oq : rest, pn = n_first ? rest : oq;
+  const int t = pn * a.tiles_m + pm;  // blocks of partial sums: M fastest
+  const int m0 = pm * BM, n0 = pn * BN;
   const T* X = static_cast<const T*>(a.x) + (xp.plane ? l * xp.plane : a.xl[l]);
   const T* Y = static_cast<const T*>(a.y) + (yp.plane ? l * yp.plane : a.yl[l]);
   const int kbeg = split * a.kchunk, kend = min(a.K, kbeg + a.kchunk);
