@@ -102,6 +102,13 @@ TileCfg choose_tiles(const famlies_handle_s* h, const Analysis& an, bool* from_t
   return pick;
 }
 
+// Whether the FP64 rows of X or Y lie whole cache lines apart.
+static bool line_strides(const std::vector<Mode>& rows, bool x) {
+  for (const Mode& m : rows)
+    if ((x ? m.sx : m.sy) % 16) return false;
+  return !rows.empty();
+}
+
 // The direct kernel reads every operand element once per tile of the other
 // side, so it is bound by L2 (about 9 TB/s measured over its shapes: 32 x 32
 // tiles 107 to 2147 MB in 17.8 to 241 us) where there are many tiles, and by
@@ -134,6 +141,8 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
   const bool xlines = an.x_kfast && !xrun, ylines = an.y_kfast && !yrun;
   const double xw = xlines ? 2.5 : !an.x_kfast && !an.I.empty() && an.I[0].sx != 1 ? 2.0 : 1.0;
   const double yw = ylines ? 2.5 : !an.y_kfast && !an.J.empty() && an.J[0].sy != 1 ? 2.0 : 1.0;
+  // FP64 rows read along K and whole cache lines apart (the longer side's)
+  const bool by_lines = es == 8 && (an.M >= an.N ? xrun && line_strides(an.I, true) : yrun && line_strides(an.J, false));
   const double unique = ((double)an.M * an.K + (double)an.N * an.K + (double)an.M * an.N) * (double)an.L * es;
   const double hbm_us = unique / 4.3e6;
 
@@ -150,6 +159,7 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
 
   tiled = std::min(tiled, level_us);
   DirectCfg best = none;
+  double crowded_us = 0.0;
   double best_us = 0.88 * tiled;  // the estimates are good to about a tenth
   const int shapes[4][2] = {{16, 16}, {32, 32}, {16, 64}, {64, 16}};
   for (const auto& sh : shapes)
@@ -175,8 +185,9 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
         // tiles, 9.8 in 16 x 16, tiled 11.1)
         const double lines = 64.0 * u * ((xlines ? sh[0] : 0) + (ylines ? sh[1] : 0)) / 16.0;
         const double line_us = std::ceil(n / cus) * steps * lines / (sh[0] * sh[1] == 256 ? 3.0e3 : 1.5e3);
-        double us = 4.0 + std::max(std::max(std::max(std::ceil(steps / wk) * step_us, mfma_us), std::max(l2_us, mem_us)),
-                                   line_us);
+        const double bound = std::max(
+            std::max(std::max(std::ceil(steps / wk) * step_us, mfma_us), std::max(l2_us, mem_us)), line_us);
+        double us = 4.0 + bound;
         if (wk > 1) us += 0.0012 * n;  // the waves' partial tiles through LDS
         if (split > 1) us += 4.0 + (double)(split + 1) * (double)an.M * (double)an.N * es / 4.0e6;
         const int64_t of_wave = ceil_div((int64_t)steps, wk);
@@ -184,6 +195,12 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
         if (chains == 3 && ceil_div(of_wave, 3) * ks > chain.length) continue;
         if (us < best_us) {
           best_us = us;
+          const double wgs = n * wk / (4.0 * cus), rm = (double)std::min<int64_t>(an.M, sh[0]),
+                       rn = (double)std::min<int64_t>(an.N, sh[1]);
+          crowded_us = us;
+          if (by_lines && wgs > 1.0)
+            crowded_us += std::max(0.0, l2_us * std::max(1.0, std::ceil(wgs - 0.1) / wgs) *
+                                                (std::ceil(rm / 16) + std::ceil(rn / 16)) * 16 / (rm + rn) - bound);
           best.bm = sh[0];
           best.bn = sh[1];
           best.wk = wk;
@@ -191,6 +208,12 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
           best.chains = chains;
         }
       }
+  // FP64 rows whole cache lines apart crowd some of L2's channels: the CUs that
+  // run a workgroup more than others do not catch up, and rows past an edge
+  // cost as much as others (6000 x 64 x 800, 376 workgroups on 256 CUs: 30 us,
+  // tiled 23; 51 x 5324 x 784 26.5 and 23; but 100 x 4000 x 700, 500 of them
+  // and rows 43.75 lines apart, 21.5, tiled 27)
+  if (crowded_us > 0.9 * tiled) return none;
   return best;
 }
 

@@ -48,3 +48,13 @@ def test_long_sides_are_walked_in_long_segments():
             t, w = routes([tall, wide])
             assert t and t[:2] in ((64, 16), (32, 32)), (dt, big, k, t)
             assert w and w[:2] in ((16, 64), (32, 32)), (dt, big, k, w)
+
+
+def test_rows_whole_lines_apart_on_unevenly_filled_units():
+    """FP64 rows whole cache lines apart: one and a half direct workgroups per
+    CU took 30 us at 6000 x 64 x 800 where the tiles take 23, 17 against 14 at 458
+    x 150 x 832.  Rows off the lines, or full rounds, keep the direct kernel."""
+    def kk(m, n, k):
+        return [1, [[m, k], [k, 1]], [[k, n], [1, k]], [n, 1]]
+    assert routes([kk(6000, 64, 800), kk(64, 6000, 800), kk(458, 150, 832)]) == [None] * 3
+    assert all(routes([kk(100, 4000, 700), kk(4000, 64, 1024), kk(2000, 100, 800)]))
