@@ -171,7 +171,11 @@ DirectCfg choose_direct(const famlies_handle_s* h, const Analysis& an, const Til
         const double steps = (double)ceil_div(ceil_div(K, split), ks);
         const double rows = xw * (double)std::min<int64_t>(an.M, sh[0]) + yw * (double)std::min<int64_t>(an.N, sh[1]);
         const double l2_us = n * rows * steps * ks * es / 9.0e6;
-        const double step_us = sh[0] * sh[1] == 256 ? (an.esize == 8 ? 0.20 : 0.27) : 0.43;
+        // 16 x 64 and 64 x 16 load five blocks of rows per step, 32 x 32 four; where
+        // that fills as well and both operands come in runs, the difference shows
+        // (FP32 2000 x 64 x 800 12.6 us in 16 x 64 tiles)
+        const bool five = sh[0] != sh[1] && xrun && yrun && std::min(an.M, an.N) > 32;
+        const double step_us = sh[0] * sh[1] == 256 ? (an.esize == 8 ? 0.20 : 0.27) : five ? 0.54 : 0.43;
         const double mfma_us = n * sh[0] * sh[1] * steps * ks * 2.0 / (an.esize == 8 ? 6.0e7 : 1.2e8);
         // narrow tiles touch memory in short segments: FP64 16 x 675840 x 64
         // takes 130 us in 16 x 16 tiles, 120 in 32 x 32, 108 in 16 x 64; with

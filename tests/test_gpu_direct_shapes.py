@@ -50,7 +50,7 @@ CASES = [
     ("f32", (16, 64, 1), 1, 0, "kk", 2, 128162, 59), ("f32", (16, 64, 1), 1, 0, "kr", 1, 102408, 141),
     ("f32", (16, 64, 1), 1, 0, "rk", 3, 36647, 175), ("f32", (16, 64, 1), 1, 0, "rr", 2, 198276, 41),
     ("f32", (16, 64, 4), 1, 0, "kk", 3, 11478, 114), ("f32", (16, 64, 4), 1, 0, "rk", 3, 5560, 233),
-    ("f32", (16, 64, 4), 3, 0, "kk", 197, 799, 1137), ("f32", (32, 32, 1), 1, 0, "kk", 21982, 25, 232),
+    ("f32", (16, 64, 4), 3, 0, "kk", 33, 5003, 779), ("f32", (32, 32, 1), 1, 0, "kk", 21982, 25, 232),
     ("f32", (32, 32, 1), 1, 0, "kr", 52, 17944, 33), ("f32", (32, 32, 1), 1, 0, "rk", 39098, 17, 299),
     ("f32", (32, 32, 1), 1, 0, "rr", 23047, 26, 210), ("f32", (32, 32, 4), 1, 0, "kk", 6244, 58, 99),
     ("f32", (32, 32, 4), 1, 0, "rk", 53, 7154, 129), ("f32", (32, 32, 4), 1, 1, "kk", 412, 151, 2846),
@@ -58,7 +58,7 @@ CASES = [
     ("f32", (32, 32, 4), 3, 0, "rk", 727, 364, 1133), ("f32", (64, 16, 1), 1, 0, "kk", 30790, 3, 258),
     ("f32", (64, 16, 1), 1, 0, "kr", 210979, 8, 13), ("f32", (64, 16, 1), 1, 0, "rk", 50324, 4, 109),
     ("f32", (64, 16, 1), 1, 0, "rr", 175511, 13, 13), ("f32", (64, 16, 4), 1, 0, "kk", 5491, 29, 51),
-    ("f32", (64, 16, 4), 1, 0, "rk", 10077, 6, 141), ("f32", (64, 16, 4), 3, 0, "kk", 637, 226, 779),
+    ("f32", (64, 16, 4), 1, 0, "rk", 10077, 6, 141), ("f32", (64, 16, 4), 3, 0, "kk", 5003, 33, 779),
 ]
 
 
