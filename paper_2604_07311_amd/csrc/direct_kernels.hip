@@ -109,12 +109,12 @@ __global__ __launch_bounds__(64 * NW) void direct_contract(PlainArgs<uint32_t> a
   const int ntiles = a.tiles_m * a.tiles_n;
   // units: (batch index, K range, tile), tile fastest; within, the side of
   // fewer tiles, so that the run of tiles of an XCD reads the long operand once
-  const int64_t units = (int64_t)ntiles * a.splits * a.L;
-  const int64_t wg = xcd_remap(blockIdx.x, gridDim.x);
-  const int64_t unit = wk == 1 ? wg * NW + wave : wg;
+  const int units = ntiles * a.splits * a.L;  // at most 1e9 (the planner's limit)
+  const int wg = xcd_remap(blockIdx.x, gridDim.x);
+  const int unit = wk == 1 ? wg * NW + wave : wg;
   if (unit >= units) return;  // wk == 1 only: whole waves, and no barrier follows
   const int wki = wk == 1 ? 0 : wave;
-  const int ls = (int)(unit / ntiles), o = (int)(unit - (int64_t)ls * ntiles);
+  const int ls = unit / ntiles, o = unit - ls * ntiles;
   const int l = ls / a.splits, split = ls % a.splits;
   const bool n_first = a.tiles_n < a.tiles_m;
   const int fewer = n_first ? a.tiles_n : a.tiles_m, oq = o / fewer, rest = o - oq * fewer;
